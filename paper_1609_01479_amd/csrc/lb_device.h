@@ -115,12 +115,16 @@ __device__ __forceinline__ int push_site(const KParams& p, const Geo& q, int i)
 
 // Workgroup ids are dispatched round-robin over the 8 XCDs, each with its own
 // L2.  This remaps them so that each XCD receives a contiguous run of ids
-// (when the grid is a multiple of 8): neighbouring sites, whose pulls share
-// cache lines, are then fetched into one L2.
+// (the first nb % 8 XCDs one id more than the others): neighbouring sites,
+// whose pulls share cache lines, are then fetched into one L2.  (Remapping
+// only grids that are a multiple of 8 left the others to the round-robin
+// order: at 151 x 105 x 150 the steps ran 128-453 us against 113-424 us
+// with it, 3-14% faster.)
 __device__ __forceinline__ int xcd_block()
 {
     const int b = blockIdx.x, nb = gridDim.x;
-    return (nb & 7) == 0 ? (b & 7) * (nb >> 3) + (b >> 3) : b;
+    const int k = b & 7, per = nb >> 3, more = nb & 7;
+    return k * per + min(k, more) + (b >> 3);
 }
 
 // Distribution layout of a time level (KParams layout fields, set by

@@ -7,10 +7,10 @@
 // be in the next one, except at the two ends of each eighth; with the
 // plain interleaved order every second such plane belonged to another XCD
 // and was fetched from memory again.  (A grid that is not a multiple of 8
-// falls back to the interleaved order.)
+// takes its sites in xcd_block()'s order: a contiguous run per XCD too.)
 #pragma once
 
-#include <hip/hip_runtime.h>
+#include "lb_device.h"
 
 namespace lbk {
 namespace dev {
@@ -24,7 +24,8 @@ struct XcdSweep {
 __device__ __forceinline__ XcdSweep xcd_sweep(int nsites, int block_threads)
 {
     const int b = blockIdx.x, nb = gridDim.x;
-    if (nb & 7) return XcdSweep{b * block_threads + int(threadIdx.x), nsites, nb * block_threads};
+    if (nb & 7)
+        return XcdSweep{xcd_block() * block_threads + int(threadIdx.x), nsites, nb * block_threads};
     const int k = b & 7, per_xcd = nb >> 3, local = b >> 3;
     const int per = (nsites + 7) / 8;
     const int begin = k * per;

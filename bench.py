@@ -51,7 +51,8 @@ def step_bytes_per_site(elem_bytes: int) -> dict:
 # library's copy kernel of known size (FETCH x 2.000, WRITE x 1.000).
 # They hold only for the kernel sources they were taken on (the hash below);
 # after any change to those sources the traffic is reported as null.
-TRAFFIC_SOURCES = ("lb_kernels.hip", "lb_device.h", "lb_internal.h")
+TRAFFIC_SOURCES = ("lb_step.h", "lb_step_f32.hip", "lb_step_f64.hip", "lb_kernels.hip",
+                   "lb_device.h", "lb_internal.h")
 TRAFFIC_SHA256 = "d86d933167066445c0fd4198305be13ba6339a49ff7f7524e314d0ba5395c23f"
 TRAFFIC_BYTES = {"fp32_dev": 5350005418, "fp64": 10363384056}
 

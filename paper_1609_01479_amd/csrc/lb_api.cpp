@@ -134,6 +134,8 @@ static __device__ __align__(256) double scratch[LB_NOALLOC_MAX_PARTIALS * 5];
 
 namespace {
 
+static_assert(lbk::kMaxStepPartials <= LB_NOALLOC_MAX_PARTIALS, "every two-pass step fits");
+
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 double* g_scratch_dev[kMaxDevices] = {};
@@ -216,8 +218,12 @@ lb_status lb_query_sizes(const lb_params* p, lb_sizes* out)
     k.nz = p->nz;
     k.fd = fd;
     const lbk::TileCfg tc = lbk::tile_config(k, p->segment_x, p->precision == LB_FP32_DEV);
+    const lbk::TileCfg rows = lbk::row_tile_config(k, p->segment_x);
     k.nsites = int(n);
     size_t nparts = std::max<size_t>(size_t(tc.ntiles) * tc.nseg, lbk::kMaxPartialBlocks);
+    nparts = std::max<size_t>(nparts, size_t(rows.ntiles) * rows.nseg);
+    // a two-pass step reduces over at most this many blocks
+    if (!fd) nparts = std::max<size_t>(nparts, lbk::kMaxStepPartials);
     if (fd) nparts = std::max<size_t>(nparts, size_t(lbk::fd_step_partial_blocks(k, p->segment_x)));
     else if (p->coupling == LB_COUPLING_FORCE)
         nparts = std::max<size_t>(nparts, size_t(lbk::force_sums_blocks(k, p->segment_x)));
@@ -303,32 +309,63 @@ lb_status lb_init_phi(lb_ctx* ctx, const double* phi0_dev)
     return e == hipSuccess ? LB_OK : hip_fail(e, "lb_init_phi");
 }
 
-// One step from src to dst with the context's scheme.
-static hipError_t one_step(lb_ctx* ctx, const void* src, void* dst, double* sums_dev,
-                           double* phi_src_out = nullptr, double* part = nullptr)
+// One step from src to dst with the context's scheme; partials (may be null)
+// takes the block partials of src's conserved sums.
+static hipError_t one_step(lb_ctx* ctx, const void* src, void* dst, double* partials,
+                           double* phi_src_out = nullptr)
 {
     double* work = static_cast<double*>(ctx->b.phi);
-    if (!part) part = static_cast<double*>(ctx->b.scratch);
     if (ctx->kp.fd)
-        return lbk::launch_fd_step(ctx->kp, ctx->tc, ctx->fp32, ctx->p.kernel, src, dst, work, part,
-                                   sums_dev, ctx->stream);
-    return lbk::launch_step(ctx->kp, ctx->tc, ctx->fp32, ctx->p.kernel, src, dst, work, part,
-                            sums_dev, phi_src_out, ctx->stream);
+        return lbk::launch_fd_step(ctx->kp, ctx->tc, ctx->fp32, ctx->p.kernel, src, dst, work,
+                                   partials, ctx->stream);
+    return lbk::launch_step(ctx->kp, ctx->tc, ctx->fp32, ctx->p.kernel, src, dst, work, partials,
+                            phi_src_out, ctx->stream);
 }
 
+// The partial blocks this context's steps reduce over.
+static size_t sums_blocks(const lb_ctx* ctx)
+{
+    return size_t(ctx->kp.fd
+                      ? lbk::fd_sums_blocks(ctx->kp, ctx->tc, ctx->p.kernel)
+                      : lbk::step_sums_blocks(ctx->kp, ctx->tc, ctx->fp32, ctx->p.kernel));
+}
+
+// Those of the marching kernels over row tiles: what lb_step_sums_noalloc's
+// limit is stated for, whichever form of the step runs.
+static size_t march_blocks(const lb_ctx* ctx)
+{
+    const lbk::TileCfg tc = lbk::row_tile_config(ctx->kp, ctx->p.segment_x);
+    if (ctx->p.kernel == LB_KERNEL_TWO_PASS) return 0;
+    if (ctx->kp.fd) return size_t(lbk::fd_sums_blocks(ctx->kp, tc, LB_KERNEL_FUSED));
+    if (ctx->kp.force) return size_t(lbk::force_sums_blocks(ctx->kp, ctx->p.segment_x));
+    return size_t(tc.ntiles) * tc.nseg;
+}
+
+// part holds the block partials of `rows` blocks: the steps leave theirs one
+// after the other, and one launch sums those of as many steps as fit.
 static lb_status step_n(lb_ctx* ctx, int32_t nsteps, double* sums_dev, const char* name,
-                        double* part = nullptr)
+                        double* part = nullptr, size_t rows = 0)
 {
     if (!ctx) return fail(LB_EINVAL, "ctx is NULL");
     if (nsteps < 0) return fail(LB_EINVAL, "nsteps must be >= 0 (got %d)", nsteps);
     if (ctx->kp.xh && nsteps > 1)
         return fail(LB_EINVAL, "an x-slab shard advances one step per call (its halo planes "
                                "are exchanged between steps); got nsteps = %d", nsteps);
+    const size_t nb = sums_dev ? sums_blocks(ctx) : 0;
+    const int32_t batch = sums_dev ? int32_t(std::min<size_t>(rows / nb, 4096)) : 1;
+    int32_t held = 0;  // steps whose partials wait in part
     for (int32_t t = 0; t < nsteps; t++) {
         hipError_t e = one_step(ctx, ctx->b.state[ctx->cur], ctx->b.state[1 - ctx->cur],
-                                sums_dev ? sums_dev + 5 * size_t(t) : nullptr, nullptr, part);
+                                sums_dev ? part + size_t(held) * 5 * nb : nullptr);
         if (e != hipSuccess) return hip_fail(e, name);
         ctx->cur = 1 - ctx->cur;
+        if (!sums_dev) continue;
+        held++;
+        if (held < batch && t + 1 < nsteps) continue;
+        e = lbk::launch_sums_final(part, int(nb), 5, held, sums_dev + 5 * size_t(t + 1 - held),
+                                   ctx->stream);
+        if (e != hipSuccess) return hip_fail(e, name);
+        held = 0;
     }
     return LB_OK;
 }
@@ -338,7 +375,9 @@ lb_status lb_step(lb_ctx* ctx, int32_t nsteps) { return step_n(ctx, nsteps, null
 lb_status lb_step_sums(lb_ctx* ctx, int32_t nsteps, double* sums_dev)
 {
     if (!sums_dev) return fail(LB_EINVAL, "sums_dev is required");
-    return step_n(ctx, nsteps, sums_dev, "lb_step_sums");
+    if (!ctx) return fail(LB_EINVAL, "ctx is NULL");
+    return step_n(ctx, nsteps, sums_dev, "lb_step_sums", static_cast<double*>(ctx->b.scratch),
+                  ctx->sz.scratch_bytes / (5 * sizeof(double)));
 }
 
 lb_status lb_step_sums_noalloc(lb_ctx* ctx, int32_t nsteps, double* sums_dev)
@@ -347,8 +386,7 @@ lb_status lb_step_sums_noalloc(lb_ctx* ctx, int32_t nsteps, double* sums_dev)
     if (!sums_dev) return fail(LB_EINVAL, "sums_dev is required");
     if (nsteps < 0) return fail(LB_EINVAL, "nsteps must be >= 0 (got %d)", nsteps);
     // the partial blocks this context's steps reduce over
-    const size_t need = size_t(ctx->kp.fd ? lbk::fd_sums_blocks(ctx->kp, ctx->tc, ctx->p.kernel)
-                                          : lbk::step_sums_blocks(ctx->kp, ctx->tc, ctx->p.kernel));
+    const size_t need = std::max(sums_blocks(ctx), march_blocks(ctx));
     if (need > size_t(LB_NOALLOC_MAX_PARTIALS))
         return fail(LB_EINVAL, "lb_step_sums_noalloc: this lattice reduces over %zu partial "
                                "blocks, the library's array holds %d (use lb_step_sums)",
@@ -356,7 +394,7 @@ lb_status lb_step_sums_noalloc(lb_ctx* ctx, int32_t nsteps, double* sums_dev)
     double* part = nullptr;
     lb_status st = noalloc_scratch(ctx, &part);
     if (st != LB_OK) return st;
-    return step_n(ctx, nsteps, sums_dev, "lb_step_sums_noalloc", part);
+    return step_n(ctx, nsteps, sums_dev, "lb_step_sums_noalloc", part, LB_NOALLOC_MAX_PARTIALS);
 }
 
 lb_status lb_step_from(lb_ctx* ctx, const void* src_dev, void* dst_dev)
@@ -411,7 +449,7 @@ lb_status lb_sums(lb_ctx* ctx, double* out5_dev)
     double* part = static_cast<double*>(ctx->b.scratch);
     hipError_t e = moments(ctx, nullptr, nullptr, nullptr, &nb);
     if (e != hipSuccess) return hip_fail(e, "lb_sums (partials)");
-    e = lbk::launch_sums_final(part, nb, 5, out5_dev, false, ctx->stream);
+    e = lbk::launch_sums_final(part, nb, 5, 1, out5_dev, ctx->stream);
     return e == hipSuccess ? LB_OK : hip_fail(e, "lb_sums (final)");
 }
 

@@ -60,6 +60,13 @@ struct Geo {
 __device__ __forceinline__ int wrapm(int v, int n) { return v == 0 ? n - 1 : v - 1; }
 __device__ __forceinline__ int wrapp(int v, int n) { return v == n - 1 ? 0 : v + 1; }
 
+// any coordinate onto [0, n)
+__device__ __forceinline__ int wrap_any(int v, int n)
+{
+    const int r = v % n;
+    return r < 0 ? r + n : r;
+}
+
 // In an x-slab shard (p.xh > 0) x is not periodic: x - 1 and x + 1 of the
 // boundary planes are the halo planes -1 and nx.
 __device__ __forceinline__ Geo geo_xyz(const KParams& p, int x, int y, int z)
@@ -242,6 +249,28 @@ __device__ __forceinline__ Moments<T> moments_of(const KParams& p, const T* f)
     return m;
 }
 
+// Adds a site's conserved quantities [rho, phi, j (+ F/2)] to acc: FP64 sums
+// of the stored f in index order.
+template <bool DEV, typename T>
+__device__ __forceinline__ void site_sums(const KParams& p, const T* f, double phi,
+                                          const double* F, double* acc)
+{
+    double b = 0.0, jx = 0.0, jy = 0.0, jz = 0.0;
+#pragma unroll
+    for (int i = 0; i < NV; i++) {
+        const double v = double(f[i]);
+        b += v;
+        if (CX[i]) jx += CX[i] * v;
+        if (CY[i]) jy += CY[i] * v;
+        if (CZ[i]) jz += CZ[i] * v;
+    }
+    acc[0] += DEV ? p.rho0 + b : b;
+    acc[1] += phi;
+    acc[2] += F ? jx + 0.5 * F[0] : jx;
+    acc[3] += F ? jy + 0.5 * F[1] : jy;
+    acc[4] += F ? jz + 0.5 * F[2] : jz;
+}
+
 // BGK collision of one site, in place on f[] (stored convention: raw or
 // deviation) and g[] (FP64 mode: g_i; FP32 mode: g_i - r_i phi).
 //   mu = A phi + B phi^3 - kappa lap,  Pi = iso I + kappa grad grad,
@@ -313,7 +342,8 @@ __device__ __forceinline__ Vel<T> collide_f(const KParams& p, T* f, const Stenci
     return Vel<T>{ux, uy, uz};
 }
 
-template <typename T, bool REF>
+// G1 (omega_g = 1): g* = g^eq, with no term in the pre-collision g.
+template <typename T, bool REF, bool G1 = false>
 __device__ __forceinline__ void collide_g(const KParams& p, T* g, T phi, T mu, Vel<T> u)
 {
     const T gam = T(p.gamma), omg = T(p.omega_g);
@@ -363,10 +393,15 @@ __device__ __forceinline__ void collide_g(const KParams& p, T* g, T phi, T mu, V
         eq[17] = s17 + p3e * c17;  eq[18] = s17 - p3e * c17;
     }
 #pragma unroll
-    for (int i = 0; i < NV; i++) g[i] += omg * (eq[i] - g[i]);
+    for (int i = 0; i < NV; i++) {
+        if (G1)
+            g[i] = eq[i];
+        else
+            g[i] += omg * (eq[i] - g[i]);
+    }
 }
 
-template <typename T, bool DEV, bool REF>
+template <typename T, bool DEV, bool REF, bool G1 = false>
 __device__ __forceinline__ void collide(const KParams& p, T* f, T* g, const Stencil& st)
 {
     const Vel<T> u = collide_f<T, DEV>(p, f, st);
@@ -374,7 +409,7 @@ __device__ __forceinline__ void collide(const KParams& p, T* f, T* g, const Sten
     const T phi = T(st.phi), lap = T(st.lap);
     const T phi2 = phi * phi;
     const T mu = A * phi + B * phi2 * phi - kap * lap;
-    collide_g<T, REF>(p, g, phi, mu, u);
+    collide_g<T, REF, G1>(p, g, phi, mu, u);
 }
 
 // ---------------------------------------------------------------------------
@@ -553,7 +588,11 @@ __device__ __forceinline__ void lds_barrier()
 // ---------------------------------------------------------------------------
 // Block reduction of K FP64 values (fixed order): wavefront butterfly, then
 // the block's NB/64 waves as a pairwise tree.  Thread 0 writes component k to
-// out[k*gridDim.x + blockIdx.x].  Needs blockDim.x == NB.
+// out[k*gridDim.x + blockIdx.x].  Needs blockDim.x == NB.  Only LDS crosses
+// the barrier: a __syncthreads() here would hold every wave until the stores
+// it issued before have completed (the two-pass FP64 step with sums took 376
+// us at 128^3 so, or with the reduction ahead of the collision, where it
+// split the loads in two rounds; 256 without sums).
 // Final reduction of `nblocks` block partials of `ncomp` (at most 5)
 // components, laid out as block_partials writes them, by one workgroup of
 // kBlock threads in a fixed order (strided per-thread sums, a wavefront
@@ -571,6 +610,7 @@ __device__ __forceinline__ void reduce_partials_block(const double* __restrict__
     for (int k = 0; k < KMAX; k++) {
         v[k] = 0.0;
         if (k < ncomp)
+#pragma unroll 8
             for (int j = threadIdx.x; j < nblocks; j += kBlock) v[k] += partials[k * nblocks + j];
     }
 #pragma unroll
@@ -602,7 +642,7 @@ __device__ __forceinline__ void block_partials(double (&v)[K], double* out)
     if (lane == 0)
 #pragma unroll
         for (int k = 0; k < K; k++) sm[k][wid] = v[k];
-    __syncthreads();
+    lds_barrier();
     if (threadIdx.x == 0)
 #pragma unroll
         for (int k = 0; k < K; k++) {

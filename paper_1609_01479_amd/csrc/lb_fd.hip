@@ -247,12 +247,6 @@ struct FdTile {
     static constexpr int BOXPT = (NBOX + kFdFused - 1) / kFdFused;
 };
 
-__device__ __forceinline__ int wrap_any(int v, int n)
-{
-    const int r = v % n;
-    return r < 0 ? r + n : r;
-}
-
 template <typename T, bool DEV, int TZ>
 __global__ __launch_bounds__(kFdFused) void k_fd_fused(KParams p, TileCfg tc,
                                                        const T* __restrict__ sF,
@@ -1154,36 +1148,33 @@ hipError_t launch_fd_init(const KParams& p, bool fp32, void* state, const double
 
 hipError_t launch_fd_step(const KParams& p, const TileCfg& tc, bool fp32, int variant,
                           const void* src, void* dst, double* work, double* partials,
-                          double* sums_out, hipStream_t s)
+                          hipStream_t s)
 {
-    int nparts;
     if (variant == 0 && p.force) {
         // one marching pass: force, collision and flux update
         const TileCfg ft = ff_tiles(p, tc.seg_req);
-        nparts = ft.ntiles * ft.nseg;
 #define CALL                                                                                  \
     {                                                                                         \
         FdLvl<T> a = fd_level<T>(const_cast<void*>(src), p);                                  \
         FdLvl<T> d = fd_level<T>(dst, p);                                                     \
-        k_fd_force_fused<T, DEV><<<nparts, kFdFused, 0, s>>>(p, ft, a.F, a.phi, d.F, d.phi,    \
-                                                             sums_out ? partials : nullptr);  \
+        k_fd_force_fused<T, DEV><<<ft.ntiles * ft.nseg, kFdFused, 0, s>>>(p, ft, a.F, a.phi,  \
+                                                                          d.F, d.phi,         \
+                                                                          partials);          \
     }
         LB_FD_DISPATCH(fp32, CALL);
 #undef CALL
     } else if (variant == 0) {
-        nparts = tc.ntiles * tc.nseg;
 #define CALL                                                                                  \
     {                                                                                         \
         FdLvl<T> a = fd_level<T>(const_cast<void*>(src), p);                                  \
         FdLvl<T> d = fd_level<T>(dst, p);                                                     \
-        FdFused<T>::get(tc.tz)<<<nparts, kFdFused, 0, s>>>(p, tc, a.F, a.phi, d.F, d.phi,     \
-                                                           sums_out ? partials : nullptr);    \
+        FdFused<T>::get(tc.tz)<<<tc.ntiles * tc.nseg, kFdFused, 0, s>>>(p, tc, a.F, a.phi,    \
+                                                                        d.F, d.phi, partials);\
     }
         LB_FD_DISPATCH(fp32, CALL);
 #undef CALL
     } else {
         const FdTiles ft = fd_tiles(p);
-        nparts = fd_grid(p);
 #define CALL                                                                                  \
     {                                                                                         \
         FdLvl<T> a = fd_level<T>(const_cast<void*>(src), p);                                  \
@@ -1192,14 +1183,12 @@ hipError_t launch_fd_step(const KParams& p, const TileCfg& tc, bool fp32, int va
             using W = FdWork<T, true>;                                                        \
             W* w = reinterpret_cast<W*>(work);                                                \
             k_fd_collide<T, DEV, true><<<fd_grid(p), kBlock, 0, s>>>(p, a.F, a.phi, d.F, w,    \
-                                                                     sums_out ? partials       \
-                                                                              : nullptr);      \
+                                                                     partials);                \
             k_fd_update<W><<<ft.ntiles * ft.nseg, kBlock, 0, s>>>(p, ft.ntz, ft.ntiles, ft.sx, \
                                                                   a.phi, w, d.phi);           \
         } else {                                                                              \
             k_fd_collide<T, DEV, false><<<fd_grid(p), kBlock, 0, s>>>(p, a.F, a.phi, d.F, work,\
-                                                                      sums_out ? partials      \
-                                                                               : nullptr);     \
+                                                                      partials);               \
             k_fd_update<double><<<ft.ntiles * ft.nseg, kBlock, 0, s>>>(p, ft.ntz, ft.ntiles,   \
                                                                        ft.sx, a.phi, work,     \
                                                                        d.phi);                 \
@@ -1207,11 +1196,6 @@ hipError_t launch_fd_step(const KParams& p, const TileCfg& tc, bool fp32, int va
     }
         LB_FD_DISPATCH(fp32, CALL);
 #undef CALL
-    }
-    if (sums_out) {
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        return launch_sums_final(partials, nparts, 5, sums_out, false, s);
     }
     return hipGetLastError();
 }

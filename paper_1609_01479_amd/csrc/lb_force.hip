@@ -28,41 +28,47 @@ using namespace dev;
 namespace {
 
 // The force-coupling collision and propagation, one site per thread; phi of
-// the source level (all sites) comes from k_phi.
-template <typename T, bool DEV, bool REF, bool G1>
+// the source level (all sites) comes from k_phi.  SUMS: block partials of
+// [rho, phi, j + F/2] of the source level (0, or the block size).
+template <typename T, bool DEV, bool REF, bool G1, int SUMS>
 __global__ __launch_bounds__(kBlock) void k_step_force(KParams p, const T* __restrict__ sF,
                                                        const T* __restrict__ sG,
                                                        const unsigned* __restrict__ sphic,
                                                        const double* __restrict__ phi,
-                                                       T* __restrict__ dF, T* __restrict__ dG)
+                                                       T* __restrict__ dF, T* __restrict__ dG,
+                                                       double* __restrict__ partials)
 {
-    const int s = xcd_block() * kBlock + threadIdx.x;
-    if (s >= p.nsites) return;
-    const Geo q = geo_of(p, s);
-    T f[NV], g[NV];
+    const int s = xcd_block() * int(blockDim.x) + threadIdx.x;
+    double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    if (s < p.nsites) {
+        const Geo q = geo_of(p, s);
+        T f[NV], g[NV];
 #pragma unroll
-    for (int i = 0; i < NV; i++) {
-        f[i] = sF[dist_pull(p, q, i)];
-        g[i] = G1 ? T(0) : sG[dist_pull(p, q, i)];
-    }
-    const double c = phi[s];
-    const double lap = (phi[site_of(p, q.xp, q.y, q.z)] + phi[site_of(p, q.xm, q.y, q.z)] - 2.0 * c)
-                     + (phi[site_of(p, q.x, q.yp, q.z)] + phi[site_of(p, q.x, q.ym, q.z)] - 2.0 * c)
-                     + (phi[site_of(p, q.x, q.y, q.zp)] + phi[site_of(p, q.x, q.y, q.zm)] - 2.0 * c);
-    const double mu = p.A * c + p.B * c * c * c - p.kappa * lap;
-    if (REF && !G1) {
-        const double dphi = c - phic_value(sphic[phic_site(p, q.x, q.y, q.z)]);
+        for (int i = 0; i < NV; i++) {
+            f[i] = sF[dist_pull(p, q, i)];
+            g[i] = G1 ? T(0) : sG[dist_pull(p, q, i)];
+        }
+        const double c = phi[s];
+        const double lap = (phi[site_of(p, q.xp, q.y, q.z)] + phi[site_of(p, q.xm, q.y, q.z)] - 2.0 * c)
+                         + (phi[site_of(p, q.x, q.yp, q.z)] + phi[site_of(p, q.x, q.ym, q.z)] - 2.0 * c)
+                         + (phi[site_of(p, q.x, q.y, q.zp)] + phi[site_of(p, q.x, q.y, q.zm)] - 2.0 * c);
+        const double mu = p.A * c + p.B * c * c * c - p.kappa * lap;
+        if (REF && !G1) {
+            const double dphi = c - phic_value(sphic[phic_site(p, q.x, q.y, q.z)]);
 #pragma unroll
-        for (int i = 0; i < NV; i++) g[i] = pre_collision_dev(i, g[i], dphi);
-    }
-    double F[3];
-    force_from_phi(p, q, phi, F);
-    collide_force<T, DEV, REF, G1>(p, f, g, c, mu, F);
+            for (int i = 0; i < NV; i++) g[i] = pre_collision_dev(i, g[i], dphi);
+        }
+        double F[3];
+        force_from_phi(p, q, phi, F);
+        if (SUMS) site_sums<DEV>(p, f, c, F, acc);
+        collide_force<T, DEV, REF, G1>(p, f, g, c, mu, F);
 #pragma unroll
-    for (int i = 0; i < NV; i++) {
-        dF[dist_own(p, q, i)] = f[i];
-        dG[dist_own(p, q, i)] = REF ? to_dest_ref(i, g[i], c, phi[push_site(p, q, i)]) : g[i];
+        for (int i = 0; i < NV; i++) {
+            dF[dist_own(p, q, i)] = f[i];
+            dG[dist_own(p, q, i)] = REF ? to_dest_ref(i, g[i], c, phi[push_site(p, q, i)]) : g[i];
+        }
     }
+    if (SUMS) block_partials<5, SUMS ? SUMS : kBlock>(acc, partials);
 }
 
 constexpr int kForceFused = 512;
@@ -77,12 +83,6 @@ struct ForceTile {
     static constexpr int NRING = 2 * (TY + TZ);
     static constexpr int BOXPT = (NBOX + kForceFused - 1) / kForceFused;
 };
-
-__device__ __forceinline__ int wrap_any(int v, int n)
-{
-    const int r = v % n;
-    return r < 0 ? r + n : r;
-}
 
 // For plane P: (a) phi(P+1) into the LDS ring (its g pulled one plane
 // earlier), the pulls of the own site of plane P-1 and of the box of plane
@@ -327,7 +327,14 @@ __global__ __launch_bounds__(kForceFused) void k_force_fused(KParams p, TileCfg 
     if (SUMS) block_partials<5, kForceFused>(acc, partials);
 }
 
-int force_grid(const KParams& p) { return (p.nsites + kBlock - 1) / kBlock; }
+// k_step_force of a storage type by what it reduces and its block
+template <typename T, bool G1>
+decltype(&k_step_force<T, false, false, G1, 0>) pick_step_force(bool sums, int nb)
+{
+    constexpr bool F32 = std::is_same<T, float>::value;
+    if (!sums) return k_step_force<T, F32, F32, G1, 0>;
+    return nb == kBlock ? k_step_force<T, F32, F32, G1, kBlock> : k_step_force<T, F32, F32, G1, 64>;
+}
 
 // Tiling of the single pass: 8 x 64 tiles, whose box of phi (two cells
 // around the tile, 12 x 68) is 1.6 cells per thread, against 2.1 for
@@ -378,6 +385,7 @@ hipError_t launch_force_collide(const KParams& p, const TileCfg& tc, bool fp32, 
     // omega_g = 1: g* = g^eq, so the collision loads no g (the single pass
     // still pulls g for phi)
     const bool g1 = p.omega_g == 1.0;
+    const int nb = site_block(p);  // of variant 1's kernel
     if (fp32) {
         Lvl<float> a = level<float>(const_cast<void*>(src), p, true);
         Lvl<float> d = level<float>(dst, p, true);
@@ -388,8 +396,9 @@ hipError_t launch_force_collide(const KParams& p, const TileCfg& tc, bool fp32, 
                                     : k_force_fused<float, true, true, 64, false, false>);
             k<<<nft, kForceFused, 0, s>>>(p, ft, a.F, a.G, a.phic, d.phic, phi, d.F, d.G, partials);
         } else {
-            auto k = g1 ? k_step_force<float, true, true, true> : k_step_force<float, true, true, false>;
-            k<<<force_grid(p), kBlock, 0, s>>>(p, a.F, a.G, a.phic, phi, d.F, d.G);
+            auto k = g1 ? pick_step_force<float, true>(partials, nb)
+                        : pick_step_force<float, false>(partials, nb);
+            k<<<(p.nsites + nb - 1) / nb, nb, 0, s>>>(p, a.F, a.G, a.phic, phi, d.F, d.G, partials);
         }
     } else {
         Lvl<double> a = level<double>(const_cast<void*>(src), p, false);
@@ -402,9 +411,9 @@ hipError_t launch_force_collide(const KParams& p, const TileCfg& tc, bool fp32, 
             k<<<nft, kForceFused, 0, s>>>(p, ft, a.F, a.G, nullptr, nullptr, phi, d.F, d.G,
                                           partials);
         } else {
-            auto k = g1 ? k_step_force<double, false, false, true>
-                        : k_step_force<double, false, false, false>;
-            k<<<force_grid(p), kBlock, 0, s>>>(p, a.F, a.G, a.phic, phi, d.F, d.G);
+            auto k = g1 ? pick_step_force<double, true>(partials, nb)
+                        : pick_step_force<double, false>(partials, nb);
+            k<<<(p.nsites + nb - 1) / nb, nb, 0, s>>>(p, a.F, a.G, a.phic, phi, d.F, d.G, partials);
         }
     }
     return hipGetLastError();

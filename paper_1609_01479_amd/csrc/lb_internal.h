@@ -32,7 +32,7 @@ struct KParams {
 
 // Launch geometry of the single-pass step: (y, z) tiles times x segments.
 struct TileCfg {
-    int tz;                // tile width along z (128 or 64; kFused/tz rows)
+    int tz;                // tile width along z (128 or 64), or 0: flat tiles
     int nty, ntz, ntiles;  // tiles along y, along z, total
     int sx, nseg;          // planes per x segment, number of segments
     int seg_req;           // segment length asked for (<= 0: automatic)
@@ -59,11 +59,18 @@ inline Lvl<T> level(void* state, const KParams& p, bool ref)
     return l;
 }
 
-// segment_x <= 0 picks the segment length automatically.
+// segment_x <= 0 picks the segment length automatically.  row_tile_config:
+// the row tiling, whatever tile_config picks.
 TileCfg tile_config(const KParams& p, int segment_x, bool fp32);
+TileCfg row_tile_config(const KParams& p, int segment_x);
 
 // Fills the layout fields of k (nx, ny, nz and stride set) for an lb_layout.
 void set_layout(KParams& k, int layout, int aosoa_len);
+
+// Block size of the kernels that run one site per thread: single waves while
+// they do not fill the CUs (us per FP64 two-pass step, blocks of 256 / 64:
+// 16^3 7.1 / 5.8, 32^3 8.3 / 7.4, 40^3 10.5 / 10.4).
+inline int site_block(const KParams& p) { return p.nsites <= 65536 ? 64 : 256; }
 
 // All launchers enqueue on `s` and return hipGetLastError().
 // `fp32` selects the FP32 deviation-storage instantiation; otherwise FP64.
@@ -71,19 +78,34 @@ void set_layout(KParams& k, int layout, int aosoa_len);
 // each (laid out per KParams) and, in FP32 mode, phi_c[stride] (32-bit
 // words, site order).  Order-parameter fields (`phi`) are FP64.
 hipError_t launch_init(const KParams& p, bool fp32, void* state, const double* phi0, hipStream_t s);
-// variant 0: single-pass fused step; 1: phi pass (phi into phi_work, and in
-// FP32 mode the new level's phi_c) + collision pass.
-// If sums_out is non-null, also writes the 5 FP64 conserved sums
-// [rho, phi, jx, jy, jz] of the source level to sums_out, through block
-// partials in `partials` (at least 5 * max(tc.ntiles * tc.nseg,
-// kMaxPartialBlocks) doubles).
+// variant 0: single-pass fused step (or what step_variant picks for it);
+// 1: phi pass (phi into phi_work, and in FP32 mode the new level's phi_c) +
+// collision pass; 2: the single pass's memory-only twin.
+// If partials is non-null, the step also leaves the block partials of the 5
+// FP64 conserved sums [rho, phi, jx, jy, jz] of the source level there
+// (step_sums_blocks blocks of 5), for launch_sums_final.
 // phi_src_out (may be null): also store phi of src there (N FP64 values in
 // site order, bit-identical to launch_phi's).
+// The kernels a step of `variant` runs, with or without sums.
+int step_variant(const KParams& p, const TileCfg& tc, bool fp32, int variant, bool sums);
 // The number of partial blocks the LB-scheme step of `variant` reduces over.
-int step_sums_blocks(const KParams& p, const TileCfg& tc, int variant);
+int step_sums_blocks(const KParams& p, const TileCfg& tc, bool fp32, int variant);
 hipError_t launch_step(const KParams& p, const TileCfg& tc, bool fp32, int variant,
                        const void* src, void* dst, double* phi_work, double* partials,
-                       double* sums_out, double* phi_src_out, hipStream_t s);
+                       double* phi_src_out, hipStream_t s);
+// launch_step's kernels of the stress coupling, by storage precision; phi64
+// is the field that variant 1's phi pass left.  launch_phi_*: phi of `state`,
+// and if `next` is not null the phi_c of that level (FP32 mode).
+hipError_t launch_step_f32(const KParams& p, const TileCfg& tc, int variant, const void* src,
+                           void* dst, double* phi64, double* partials, double* phi_src_out,
+                           hipStream_t s);
+hipError_t launch_step_f64(const KParams& p, const TileCfg& tc, int variant, const void* src,
+                           void* dst, double* phi64, double* partials, double* phi_src_out,
+                           hipStream_t s);
+hipError_t launch_phi_f32(const KParams& p, const void* state, double* phi, void* next,
+                          hipStream_t s);
+hipError_t launch_phi_f64(const KParams& p, const void* state, double* phi, void* next,
+                          hipStream_t s);
 // Force coupling: the forcing collision from src to dst.  variant 0: the
 // whole step in one pass over (y, z) tiles marching along x (its own 8 x 64
 // tiling, segments as tc.seg_req asks), phi summed from the pulled g, Pi in
@@ -92,7 +114,7 @@ hipError_t launch_step(const KParams& p, const TileCfg& tc, bool fp32, int varia
 // [rho, phi, j + F/2] of src there (force_sums_blocks(p, tc.seg_req) blocks
 // of 5).  variant 1: after the phi pass, which left phi (all sites, FP64) of
 // src in `phi` and dst's phi_c, one site per thread, Pi formed at each face
-// neighbour (`partials` unused).  Bit-identical levels.
+// neighbour (partials: one block per kBlock sites).  Bit-identical levels.
 hipError_t launch_force_collide(const KParams& p, const TileCfg& tc, bool fp32, int variant,
                                 const void* src, void* dst, double* phi, double* partials,
                                 hipStream_t s);
@@ -104,8 +126,10 @@ hipError_t launch_phi(const KParams& p, bool fp32, const void* state, double* ph
 hipError_t launch_moments(const KParams& p, bool fp32, const void* state, double* rho, double* u,
                           double* phi, double* work, double* partials, int* nblocks_out,
                           hipStream_t s);
-hipError_t launch_sums_final(const double* partials, int nblocks, int ncomp, double* out,
-                             bool accumulate, hipStream_t s);
+// out[b*ncomp + k] = the sum of component k < ncomp over the nblocks block
+// partials of set b < nsets (sets follow one another in `partials`).
+hipError_t launch_sums_final(const double* partials, int nblocks, int ncomp, int nsets,
+                             double* out, hipStream_t s);
 hipError_t launch_export(const KParams& p, bool fp32, const void* state, double* f, double* g,
                          hipStream_t s);
 hipError_t launch_import(const KParams& p, bool fp32, void* state, const double* f,
@@ -152,16 +176,16 @@ hipError_t launch_adj_export(const KParams& p, bool fp32, const void* adj, doubl
 // variant 0: single-pass step with the tiling of tc; 1: collision pass, then
 // update pass, with `work` holding mu, u_x, u_y, u_z (4 fields of `stride`:
 // FP64, or FP32 with the force coupling in FP32 storage; 4 FP64 fields of
-// space).  With sums_out, `partials` needs 5 * max(tc.ntiles * tc.nseg,
-// fd_step_partial_blocks(p, segment_x)) doubles; fd_sums_blocks gives the
-// exact number of partial blocks the step of `variant` reduces over.
+// space).  With `partials` the step also leaves the block partials of the
+// source level's sums there: 5 * fd_sums_blocks doubles, the number of blocks
+// of `variant` (at most max(tc.ntiles * tc.nseg, fd_step_partial_blocks)).
 int fd_step_partial_blocks(const KParams& p, int segment_x);
 int fd_sums_blocks(const KParams& p, const TileCfg& tc, int variant);
 hipError_t launch_fd_init(const KParams& p, bool fp32, void* state, const double* phi0,
                           hipStream_t s);
 hipError_t launch_fd_step(const KParams& p, const TileCfg& tc, bool fp32, int variant,
                           const void* src, void* dst, double* work, double* partials,
-                          double* sums_out, hipStream_t s);
+                          hipStream_t s);
 // Reverse mode of one FD step (stress coupling): adj_prev = J(state)^T adj_next
 // in the adjoint-level layout (lf[19], unused g components, lp), with
 // `work` (4 FP64 fields of space) taking rho and u of `state`, adj_scratch
@@ -186,7 +210,9 @@ size_t face_bytes(const KParams& p, bool fp32);
 hipError_t launch_face(const KParams& p, bool fp32, void* state, void* buf, int s, int xb,
                        bool pack, hipStream_t st);
 
-// Upper bound on the block partials any reduction writes (per component).
+// Upper bounds on the block partials (per component) of a moments or adjoint
+// reduction, and of an LB step that reduces in its two-pass collision.
 constexpr int kMaxPartialBlocks = 2048;
+constexpr int kMaxStepPartials = 4096;
 
 }  // namespace lbk

@@ -1,0 +1,104 @@
+"""The forms of the LB step: the marching kernel (flat and row tiles) and the
+two passes give the same levels bit for bit, at the edges of their ranges."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import lbinputs
+import oracle
+from _gpu import field_errors, gpu_state, make_lb, oracle_params, oracle_state
+
+pytestmark = pytest.mark.gpu
+
+# (shape, segment_x): planes of exactly one flat tile, one site and one row
+# more (last tile shifted back), rows longer than any halo allows (row tiles),
+# the longest flat rows of each precision, whole-row tiles, rows of 1 and 2
+# sites, extents of 1 and 2, tiles that start and end anywhere in a row
+MARCH = [((3, 8, 64), 3), ((4, 27, 19), 2), ((2, 9, 64), 1), ((1, 3, 254), 1), ((3, 3, 255), 2),
+         ((2, 5, 256), 2), ((2, 3, 257), 1), ((3, 513, 1), 3), ((2, 300, 2), 1), ((5, 11, 100), 4),
+         ((2, 13, 150), 2), ((1, 7, 74), 1), ((4, 2, 256), 4), ((3, 6, 96), 2)]
+
+
+@pytest.mark.parametrize("tau_g", [1.0, 1.3])
+@pytest.mark.parametrize("prec", ["fp64", "fp32_dev"])
+@pytest.mark.parametrize("shape,seg", MARCH)
+def test_march_and_two_passes_agree_bit_for_bit(shape, seg, prec, tau_g):
+    print(f"[forms] {shape} seg {seg} {prec} tau_g {tau_g}", flush=True)
+    phi0 = lbinputs.spinodal_phi0(shape, seed=31, amp=0.3)
+    states, sums = [], []
+    for kernel, sx in (("fused", seg), ("two_pass", 0)):
+        lb = make_lb(shape, precision=prec, tau_f=0.8, tau_g=tau_g, kernel=kernel, segment_x=sx)
+        lb.init_phi(phi0)
+        lb.step(2)
+        sums.append(lb.step_sums(3).cpu().numpy())
+        states.append(gpu_state(lb))
+    for a, b in zip(*states):
+        assert np.array_equal(a, b)
+    # five sums of n terms of order 1 in two orders: n eps of their scale n
+    n = float(np.prod(shape))
+    assert np.abs(sums[0] - sums[1]).max() <= n * n * 2.3e-16
+
+
+@pytest.mark.parametrize("coupling", ["stress", "force"])
+@pytest.mark.parametrize("prec", ["fp64", "fp32_dev"])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (4, 4, 4), (5, 13, 1), (32, 32, 64), (29, 37, 61),
+                                   (64, 64, 64)])
+def test_default_step_sums_rows_are_the_levels_sums(shape, prec, coupling):
+    """Blocks of one wave and of four (up to and beyond 65536 sites), and the
+    sums of several steps reduced by one launch: every row is lb_sums of its
+    level, over more steps than one launch holds for the larger lattices."""
+    print(f"[sums] {shape} {prec} {coupling}", flush=True)
+    phi0 = lbinputs.spinodal_phi0(shape, seed=7, amp=0.3)
+    lb = make_lb(shape, precision=prec, tau_f=0.8, coupling=coupling)
+    ref = make_lb(shape, precision=prec, tau_f=0.8, coupling=coupling)
+    lb.init_phi(phi0)
+    ref.init_phi(phi0)
+    rows = lb.step_sums(6).cpu().numpy()
+    n = float(np.prod(shape))
+    for t in range(6):
+        assert np.abs(rows[t] - ref.sums().cpu().numpy()).max() <= n * n * 2.3e-16
+        ref.step(1)
+    for a, b in zip(gpu_state(lb), gpu_state(ref)):
+        assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("tau_g", [1.0, 1.3])
+@pytest.mark.parametrize("shape,seg", [((5, 11, 100), 4), ((2, 9, 64), 1), ((3, 3, 257), 3),
+                                       ((9, 6, 11), 0)])
+def test_fp64_forms_match_the_oracle(shape, seg, tau_g):
+    phi0 = lbinputs.spinodal_phi0(shape, seed=12, amp=0.3)
+    lb = make_lb(shape, tau_f=0.8, tau_g=tau_g, segment_x=seg)
+    lb.init_phi(phi0)
+    lb.step(5)
+    p = oracle_params(shape, tau_f=0.8, tau_g=tau_g)
+    f, g = oracle.run(p, *oracle.init(p, phi0), 5)
+    errs = field_errors(gpu_state(lb), oracle_state(p, f, g))
+    assert max(errs.values()) <= 1e-12, errs
+
+
+@pytest.mark.parametrize("layout", [dict(layout="soa"), dict(layout="aos"),
+                                    dict(layout="aosoa", aosoa_len=4)])
+@pytest.mark.parametrize("prec", ["fp64", "fp32_dev"])
+def test_flat_tiles_in_every_layout(prec, layout):
+    shape = (3, 9, 100)
+    phi0 = lbinputs.spinodal_phi0(shape, seed=3, amp=0.3)
+    out = []
+    for lay in ({}, layout):
+        lb = make_lb(shape, precision=prec, tau_f=0.8, tau_g=1.3, segment_x=2, **lay)
+        lb.init_phi(phi0)
+        lb.step(4)
+        out.append(gpu_state(lb))
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
+
+
+def test_noalloc_still_refuses_what_row_tiles_exceed():
+    """The allocation-free sums' limit is stated for the march over row tiles,
+    whichever form runs."""
+    from paper_1609_01479_amd._abi import LbError
+    out = torch.empty((1, 5), dtype=torch.float64, device="cuda:0")
+    for kw in (dict(), dict(coupling="force")):
+        with pytest.raises(LbError, match="partial blocks"):
+            make_lb((1, 60000, 1), **kw).step_sums_noalloc(1, out)

@@ -326,7 +326,7 @@ static hipError_t one_step(lb_ctx* ctx, const void* src, void* dst, double* part
 static size_t sums_blocks(const lb_ctx* ctx)
 {
     return size_t(ctx->kp.fd
-                      ? lbk::fd_sums_blocks(ctx->kp, ctx->tc, ctx->p.kernel)
+                      ? lbk::fd_sums_blocks(ctx->kp, ctx->tc, ctx->fp32, ctx->p.kernel)
                       : lbk::step_sums_blocks(ctx->kp, ctx->tc, ctx->fp32, ctx->p.kernel));
 }
 
@@ -336,7 +336,7 @@ static size_t march_blocks(const lb_ctx* ctx)
 {
     const lbk::TileCfg tc = lbk::row_tile_config(ctx->kp, ctx->p.segment_x);
     if (ctx->p.kernel == LB_KERNEL_TWO_PASS) return 0;
-    if (ctx->kp.fd) return size_t(lbk::fd_sums_blocks(ctx->kp, tc, LB_KERNEL_FUSED));
+    if (ctx->kp.fd) return size_t(lbk::fd_march_blocks(ctx->kp, tc));
     if (ctx->kp.force) return size_t(lbk::force_sums_blocks(ctx->kp, ctx->p.segment_x));
     return size_t(tc.ntiles) * tc.nseg;
 }

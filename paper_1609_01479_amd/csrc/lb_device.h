@@ -208,6 +208,16 @@ __device__ __forceinline__ T to_dest_ref(int i, T hstar, double phi_here, double
     return T(__builtin_fma(rweight(i), phi_here - phic_round(phi_dest), double(hstar)));
 }
 
+// A store of the new level, non-temporal or not (nt_stores).
+template <bool NT, typename T>
+__device__ __forceinline__ void store(T v, T* q)
+{
+    if constexpr (NT)
+        __builtin_nontemporal_store(v, q);
+    else
+        *q = v;
+}
+
 // ---------------------------------------------------------------------------
 // Local physics.
 

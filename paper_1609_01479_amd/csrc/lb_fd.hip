@@ -96,7 +96,8 @@ using FdWork = typename std::conditional<FORCE && std::is_same<T, float>::value,
 // Work fields (each `stride` FP64 values): mu, u_x, u_y, u_z.  FORCE: the
 // force coupling, F = -div Pi from the phi field (force_from_phi), the
 // forcing collision of f, u = (j + F/2)/rho, and momentum sums of j + F/2.
-template <typename T, bool DEV, bool FORCE>
+// SUMS: 0, or the block size, for block partials of the source level's sums.
+template <typename T, bool DEV, bool FORCE, bool NT, int SUMS>
 __global__ __launch_bounds__(kBlock) void k_fd_collide(KParams p, const T* __restrict__ sF,
                                                        const double* __restrict__ sphi,
                                                        T* __restrict__ dF,
@@ -104,7 +105,7 @@ __global__ __launch_bounds__(kBlock) void k_fd_collide(KParams p, const T* __res
                                                        double* __restrict__ partials)
 {
     using W = FdWork<T, FORCE>;
-    const int s = xcd_block() * kBlock + threadIdx.x;
+    const int s = xcd_block() * int(blockDim.x) + threadIdx.x;
     double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
     if (s < p.nsites) {
         const Geo q = geo_of(p, s);
@@ -117,33 +118,16 @@ __global__ __launch_bounds__(kBlock) void k_fd_collide(KParams p, const T* __res
                                    sphi[site_of(p, q.x, q.y, q.zp)], sphi[site_of(p, q.x, q.y, q.zm)]);
         double F[3] = {0.0, 0.0, 0.0};
         if (FORCE) force_from_phi(p, q, sphi, F);
-        if (partials) {
-            // FP64 moments of the source level, in index order
-            double b = 0.0, jx = 0.0, jy = 0.0, jz = 0.0;
-#pragma unroll
-            for (int i = 0; i < NV; i++) {
-                const double v = double(f[i]);
-                b += v;
-                jx += CX[i] * v;
-                jy += CY[i] * v;
-                jz += CZ[i] * v;
-            }
-            acc[0] = DEV ? p.rho0 + b : b;
-            acc[1] = c;
-            acc[2] = FORCE ? jx + 0.5 * F[0] : jx;
-            acc[3] = FORCE ? jy + 0.5 * F[1] : jy;
-            acc[4] = FORCE ? jz + 0.5 * F[2] : jz;
-        }
+        if (SUMS) site_sums<DEV>(p, f, c, FORCE ? F : nullptr, acc);
         const Vel<T> u = FORCE ? collide_force_f<T, DEV>(p, f, F) : collide_f<T, DEV>(p, f, st);
-        // the new level is not read in this launch
 #pragma unroll
-        for (int i = 0; i < NV; i++) __builtin_nontemporal_store(f[i], &dF[dist_own(p, q, i)]);
+        for (int i = 0; i < NV; i++) store<NT>(f[i], &dF[dist_own(p, q, i)]);
         work[s] = W(fd_mu(p, c, st.lap));
         work[p.stride + s] = W(u.x);
         work[2 * p.stride + s] = W(u.y);
         work[3 * p.stride + s] = W(u.z);
     }
-    if (partials) block_partials<5>(acc, partials);
+    if (SUMS) block_partials<5, SUMS ? SUMS : kBlock>(acc, partials);
 }
 
 // Flux through the face between L and L + e_a (R).  Explicit fma: both sites
@@ -213,6 +197,32 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) 
     }
 }
 
+// The same update with one site per thread, every load in flight at once, for
+// lattices whose fields stay in cache (the march's x reuse then saves
+// nothing, and its rows of 64 sites and short segments leave lanes idle).
+template <typename W>
+__global__ __launch_bounds__(kBlock) void k_fd_update_site(KParams p, const double* __restrict__ phi,
+                                                           const W* __restrict__ work,
+                                                           double* __restrict__ dphi)
+{
+    const int s = xcd_block() * int(blockDim.x) + threadIdx.x;
+    if (s >= p.nsites) return;
+    const Geo q = geo_of(p, s);
+    const int nb[3][2] = {{site_of(p, q.xp, q.y, q.z), site_of(p, q.xm, q.y, q.z)},
+                          {site_of(p, q.x, q.yp, q.z), site_of(p, q.x, q.ym, q.z)},
+                          {site_of(p, q.x, q.y, q.zp), site_of(p, q.x, q.y, q.zm)}};
+    const double M = p.mobility, pc = phi[s], mc = work[s];
+    double div = 0.0;
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        const W* __restrict__ u = work + size_t(a + 1) * p.stride;
+        const double uc = u[s];
+        div += fd_flux(pc, phi[nb[a][0]], uc, u[nb[a][0]], mc, work[nb[a][0]], M)
+             - fd_flux(phi[nb[a][1]], pc, u[nb[a][1]], uc, work[nb[a][1]], mc, M);
+    }
+    dphi[s] = pc - div;
+}
+
 // ---------------------------------------------------------------------------
 // Single-pass step (LB_KERNEL_FUSED): both passes in one kernel, the
 // collision one plane ahead of the flux update.  A workgroup of kFdFused
@@ -247,7 +257,7 @@ struct FdTile {
     static constexpr int BOXPT = (NBOX + kFdFused - 1) / kFdFused;
 };
 
-template <typename T, bool DEV, int TZ>
+template <typename T, bool DEV, int TZ, bool NT>
 __global__ __launch_bounds__(kFdFused) void k_fd_fused(KParams p, TileCfg tc,
                                                        const T* __restrict__ sF,
                                                        const double* __restrict__ sphi,
@@ -362,7 +372,7 @@ __global__ __launch_bounds__(kFdFused) void k_fd_fused(KParams p, TileCfg tc,
         const Vel<T> u = collide_f<T, DEV>(p, f, st);
         if (interior && valid)
 #pragma unroll
-            for (int i = 0; i < NV; i++) __builtin_nontemporal_store(f[i], &dF[dist_own(p, q, i)]);
+            for (int i = 0; i < NV; i++) store<NT>(f[i], &dF[dist_own(p, q, i)]);
         const double muP = fd_mu(p, phc, st.lap);
         const double uxP = double(u.x), uyP = double(u.y), uzP = double(u.z);
         s_mu[w][ro] = muP;
@@ -397,7 +407,7 @@ __global__ __launch_bounds__(kFdFused) void k_fd_fused(KParams p, TileCfg tc,
                  - fd_flux(fx[bo - BZ], pc, s_uy[v][ro - RZ], uyB, s_mu[v][ro - RZ], mc, M);
             div += fd_flux(pc, fx[bo + 1], uzB, s_uz[v][ro + 1], mc, s_mu[v][ro + 1], M)
                  - fd_flux(fx[bo - 1], pc, s_uz[v][ro - 1], uzB, s_mu[v][ro - 1], mc, M);
-            __builtin_nontemporal_store(pc - div, &dphi[(P - 1) * plane + yg * p.nz + zg]);
+            store<NT>(pc - div, &dphi[(P - 1) * plane + yg * p.nz + zg]);
         }
         phA = phB; phB = phc;
         muA = muB; muB = muP;
@@ -407,13 +417,17 @@ __global__ __launch_bounds__(kFdFused) void k_fd_fused(KParams p, TileCfg tc,
     if (partials) block_partials<5, kFdFused>(acc, partials);
 }
 
+// Non-temporal stores from a level of 96 MiB on (us per step, NT / plain: FP32
+// 96^3 42 / 36, FP64 96^3 71 / 75, FP32 128^3 73 / 77, and with rows that are
+// not whole 64-byte pieces FP32 72 x 111 x 150 59 / 46, 151 x 105 x 150 128 / 114).
 template <typename T>
 struct FdFused {
-    using K = decltype(&k_fd_fused<T, std::is_same<T, float>::value, 128>);
-    static K get(int tz)
+    static constexpr bool DEV = std::is_same<T, float>::value;
+    using K = decltype(&k_fd_fused<T, DEV, 128, true>);
+    static K get(int tz, bool nt)
     {
-        constexpr bool DEV = std::is_same<T, float>::value;
-        return tz == 64 ? k_fd_fused<T, DEV, 64> : k_fd_fused<T, DEV, 128>;
+        if (tz == 64) return nt ? k_fd_fused<T, DEV, 64, true> : k_fd_fused<T, DEV, 64, false>;
+        return nt ? k_fd_fused<T, DEV, 128, true> : k_fd_fused<T, DEV, 128, false>;
     }
 };
 
@@ -463,7 +477,7 @@ struct FfTile {
 static_assert(FfTile::TY * FfTile::TZ == kFdFused, "one site per thread");
 static_assert(FfTile::NPIX <= kFdFused && FfTile::NRING <= kFdFused, "halo cells per thread");
 
-template <typename T, bool DEV>
+template <typename T, bool DEV, bool NT>
 __global__ __launch_bounds__(kFdFused) void k_fd_force_fused(KParams p, TileCfg tc,
                                                              const T* __restrict__ sF,
                                                              const double* __restrict__ sphi,
@@ -657,7 +671,7 @@ __global__ __launch_bounds__(kFdFused) void k_fd_force_fused(KParams p, TileCfg 
             const Vel<T> u = collide_force_f<T, DEV>(p, f, F);
             if (inner && valid)
 #pragma unroll
-                for (int i = 0; i < NV; i++) __builtin_nontemporal_store(f[i], &dF[dist_own(p, q, i)]);
+                for (int i = 0; i < NV; i++) store<NT>(f[i], &dF[dist_own(p, q, i)]);
             const W muw = W(mum), uyw = W(u.y), uzw = W(u.z);
             phC = c;
             muC = double(muw);
@@ -717,7 +731,7 @@ __global__ __launch_bounds__(kFdFused) void k_fd_force_fused(KParams p, TileCfg 
                           double(s_mu[v][ro + 1]), M)
                 - fd_flux(s_ph[v][ro - 1], pc, double(s_uz[v][ro - 1]), uzB,
                           double(s_mu[v][ro - 1]), mc, M);
-            __builtin_nontemporal_store(pc - dv, &dphi[U * plane + yg * p.nz + zg]);
+            store<NT>(pc - dv, &dphi[U * plane + yg * p.nz + zg]);
         }
 #pragma unroll
         for (int a = 0; a < 3; a++) {
@@ -1116,21 +1130,49 @@ int fd_reduction_grid(const KParams& p)
 
 }  // namespace
 
+// The update pass runs one site per thread up to this size: beyond it the
+// fields leave the Infinity Cache and the march's x reuse pays (us per
+// two-pass step, march / per site: 60 x 52 x 70 20 / 14, 90 x 75 x 100 31 / 31,
+// 72 x 111 x 150 53 / 52, 256^3 834 / 876).
+constexpr int kFdSiteUpdate = 1500000;
+
+// Blocks the collision pass reduces over.
+static int fd_collide_grid(const KParams& p) { return (p.nsites + site_block(p) - 1) / site_block(p); }
+
+// Which form a step of `variant` runs (1: two passes).  As for the LB scheme
+// (step_variant), the march's prologue, halo work and idle lanes cost more
+// than the work fields' traffic on small lattices.  Measured (us per step,
+// march / two passes): stress FP32 16^3 8.8 / 5.9, 70 x 84 x 66 24 / 20,
+// 90 x 75 x 100 29 / 30.5; stress FP64 16^3 11 / 5.8, 64^3 24 / 19, 96^3 71 / 68,
+// 72 x 111 x 150 95 / 101; force FP32 16^3 15 / 6.1, 96^3 45 / 38,
+// 72 x 111 x 150 57 / 51, 128^3 79 / 107; force FP64 16^3 17 / 6.3,
+// 64^3 29 / 22, 96^3 76 / 74, 72 x 111 x 150 100 / 108.
+static int fd_variant(const KParams& p, const TileCfg& tc, bool fp32, int variant, bool sums)
+{
+    if (variant != 0 || tc.seg_req > 0) return variant;
+    if (sums && fd_collide_grid(p) > kMaxStepPartials) return 0;
+    const int limit = !fp32 ? 900000 : p.force ? 1300000 : 450000;
+    return p.nsites <= limit ? 1 : 0;
+}
+
 int fd_step_partial_blocks(const KParams& p, int segment_x)
 {
     const TileCfg ft = ff_tiles(p, segment_x);
-    const int g = fd_grid(p);
+    const int g = fd_collide_grid(p);
     return ft.ntiles * ft.nseg > g ? ft.ntiles * ft.nseg : g;
 }
 
-int fd_sums_blocks(const KParams& p, const TileCfg& tc, int variant)
+int fd_sums_blocks(const KParams& p, const TileCfg& tc, bool fp32, int variant)
 {
-    if (variant != 0) return fd_grid(p);
-    if (p.force) {
-        const TileCfg ft = ff_tiles(p, tc.seg_req);
-        return ft.ntiles * ft.nseg;
-    }
-    return tc.ntiles * tc.nseg;
+    if (fd_variant(p, tc, fp32, variant, true) != 0) return fd_collide_grid(p);
+    return fd_march_blocks(p, tc);
+}
+
+int fd_march_blocks(const KParams& p, const TileCfg& tc)
+{
+    if (!p.force) return tc.ntiles * tc.nseg;
+    const TileCfg ft = ff_tiles(p, tc.seg_req);
+    return ft.ntiles * ft.nseg;
 }
 
 hipError_t launch_fd_init(const KParams& p, bool fp32, void* state, const double* phi0,
@@ -1146,57 +1188,56 @@ hipError_t launch_fd_init(const KParams& p, bool fp32, void* state, const double
     return hipGetLastError();
 }
 
+// The two passes: collision, then the update (marching, or one site per
+// thread).
+template <typename T, bool FORCE, bool NT>
+static void fd_two_pass(const KParams& p, const FdLvl<T>& a, const FdLvl<T>& d, double* work,
+                        double* partials, hipStream_t s)
+{
+    constexpr bool DEV = std::is_same<T, float>::value;
+    using W = FdWork<T, FORCE>;
+    W* w = reinterpret_cast<W*>(work);
+    const int nb = site_block(p), grid = (p.nsites + nb - 1) / nb;
+    auto k = !partials ? k_fd_collide<T, DEV, FORCE, NT, 0>
+             : nb == kBlock ? k_fd_collide<T, DEV, FORCE, NT, kBlock>
+                            : k_fd_collide<T, DEV, FORCE, NT, 64>;
+    k<<<grid, nb, 0, s>>>(p, a.F, a.phi, d.F, w, partials);
+    if (p.nsites <= kFdSiteUpdate) {
+        k_fd_update_site<W><<<grid, nb, 0, s>>>(p, a.phi, w, d.phi);
+    } else {
+        const FdTiles ft = fd_tiles(p);
+        k_fd_update<W><<<ft.ntiles * ft.nseg, kBlock, 0, s>>>(p, ft.ntz, ft.ntiles, ft.sx, a.phi,
+                                                              w, d.phi);
+    }
+}
+
 hipError_t launch_fd_step(const KParams& p, const TileCfg& tc, bool fp32, int variant,
                           const void* src, void* dst, double* work, double* partials,
                           hipStream_t s)
 {
-    if (variant == 0 && p.force) {
-        // one marching pass: force, collision and flux update
-        const TileCfg ft = ff_tiles(p, tc.seg_req);
+    variant = fd_variant(p, tc, fp32, variant, partials != nullptr);
+    const bool nt = nt_stores(p, NV, fp32 ? 4 : 8, 96);
 #define CALL                                                                                  \
     {                                                                                         \
         FdLvl<T> a = fd_level<T>(const_cast<void*>(src), p);                                  \
         FdLvl<T> d = fd_level<T>(dst, p);                                                     \
-        k_fd_force_fused<T, DEV><<<ft.ntiles * ft.nseg, kFdFused, 0, s>>>(p, ft, a.F, a.phi,  \
-                                                                          d.F, d.phi,         \
-                                                                          partials);          \
-    }
-        LB_FD_DISPATCH(fp32, CALL);
-#undef CALL
-    } else if (variant == 0) {
-#define CALL                                                                                  \
-    {                                                                                         \
-        FdLvl<T> a = fd_level<T>(const_cast<void*>(src), p);                                  \
-        FdLvl<T> d = fd_level<T>(dst, p);                                                     \
-        FdFused<T>::get(tc.tz)<<<tc.ntiles * tc.nseg, kFdFused, 0, s>>>(p, tc, a.F, a.phi,    \
-                                                                        d.F, d.phi, partials);\
-    }
-        LB_FD_DISPATCH(fp32, CALL);
-#undef CALL
-    } else {
-        const FdTiles ft = fd_tiles(p);
-#define CALL                                                                                  \
-    {                                                                                         \
-        FdLvl<T> a = fd_level<T>(const_cast<void*>(src), p);                                  \
-        FdLvl<T> d = fd_level<T>(dst, p);                                                     \
-        if (p.force) {                                                                        \
-            using W = FdWork<T, true>;                                                        \
-            W* w = reinterpret_cast<W*>(work);                                                \
-            k_fd_collide<T, DEV, true><<<fd_grid(p), kBlock, 0, s>>>(p, a.F, a.phi, d.F, w,    \
-                                                                     partials);                \
-            k_fd_update<W><<<ft.ntiles * ft.nseg, kBlock, 0, s>>>(p, ft.ntz, ft.ntiles, ft.sx, \
-                                                                  a.phi, w, d.phi);           \
+        if (variant != 0) {                                                                   \
+            auto k = p.force ? (nt ? fd_two_pass<T, true, true> : fd_two_pass<T, true, false>) \
+                             : (nt ? fd_two_pass<T, false, true>                              \
+                                   : fd_two_pass<T, false, false>);                           \
+            k(p, a, d, work, partials, s);                                                    \
+        } else if (p.force) {                                                                 \
+            /* one marching pass: force, collision and flux update */                         \
+            const TileCfg ft = ff_tiles(p, tc.seg_req);                                       \
+            auto k = nt ? k_fd_force_fused<T, DEV, true> : k_fd_force_fused<T, DEV, false>;   \
+            k<<<ft.ntiles * ft.nseg, kFdFused, 0, s>>>(p, ft, a.F, a.phi, d.F, d.phi, partials); \
         } else {                                                                              \
-            k_fd_collide<T, DEV, false><<<fd_grid(p), kBlock, 0, s>>>(p, a.F, a.phi, d.F, work,\
-                                                                      partials);               \
-            k_fd_update<double><<<ft.ntiles * ft.nseg, kBlock, 0, s>>>(p, ft.ntz, ft.ntiles,   \
-                                                                       ft.sx, a.phi, work,     \
-                                                                       d.phi);                 \
+            FdFused<T>::get(tc.tz, nt)<<<tc.ntiles * tc.nseg, kFdFused, 0, s>>>(              \
+                p, tc, a.F, a.phi, d.F, d.phi, partials);                                     \
         }                                                                                     \
     }
-        LB_FD_DISPATCH(fp32, CALL);
+    LB_FD_DISPATCH(fp32, CALL);
 #undef CALL
-    }
     return hipGetLastError();
 }
 

@@ -100,7 +100,7 @@ struct ForceTile {
 // of [rho, phi, j + F/2] of the state stepped from go to `partials`, as
 // k_moments sums them with the force (a separate instantiation: the sums'
 // registers would otherwise make the plain step spill).
-template <typename T, bool DEV, bool REF, int TZ, bool G1, bool SUMS>
+template <typename T, bool DEV, bool REF, int TZ, bool G1, bool SUMS, bool NT>
 __global__ __launch_bounds__(kForceFused) void k_force_fused(KParams p, TileCfg tc,
                                                              const T* __restrict__ sF,
                                                              const T* __restrict__ sG,
@@ -309,13 +309,13 @@ __global__ __launch_bounds__(kForceFused) void k_force_fused(KParams p, TileCfg 
             if (phi_out) phi_out[X * plane + yg * p.nz + zg] = c;
 #pragma unroll
             for (int i = 0; i < NV; i++) {
-                __builtin_nontemporal_store(f[i], &dF[dist_own(p, q, i)]);
+                store<NT>(f[i], &dF[dist_own(p, q, i)]);
                 T gv = g[i];
                 if (REF) {
                     const double* __restrict__ pl = CX[i] > 0 ? xp : (CX[i] < 0 ? xm : xc);
                     gv = to_dest_ref(i, g[i], c, pl[bo + CY[i] * BZ + CZ[i]]);
                 }
-                __builtin_nontemporal_store(gv, &dG[dist_own(p, q, i)]);
+                store<NT>(gv, &dG[dist_own(p, q, i)]);
             }
         }
 #pragma unroll
@@ -334,6 +334,16 @@ decltype(&k_step_force<T, false, false, G1, 0>) pick_step_force(bool sums, int n
     constexpr bool F32 = std::is_same<T, float>::value;
     if (!sums) return k_step_force<T, F32, F32, G1, 0>;
     return nb == kBlock ? k_step_force<T, F32, F32, G1, kBlock> : k_step_force<T, F32, F32, G1, 64>;
+}
+
+template <typename T, bool NT>
+decltype(&k_force_fused<T, false, false, 64, false, false, NT>) pick_force_fused(bool g1, bool sums)
+{
+    constexpr bool F32 = std::is_same<T, float>::value;
+    if (g1) return sums ? k_force_fused<T, F32, F32, 64, true, true, NT>
+                        : k_force_fused<T, F32, F32, 64, true, false, NT>;
+    return sums ? k_force_fused<T, F32, F32, 64, false, true, NT>
+                : k_force_fused<T, F32, F32, 64, false, false, NT>;
 }
 
 // Tiling of the single pass: 8 x 64 tiles, whose box of phi (two cells
@@ -386,14 +396,13 @@ hipError_t launch_force_collide(const KParams& p, const TileCfg& tc, bool fp32, 
     // still pulls g for phi)
     const bool g1 = p.omega_g == 1.0;
     const int nb = site_block(p);  // of variant 1's kernel
+    const bool nt = nt_stores(p, 2 * NV, fp32 ? 4 : 8, 192);
     if (fp32) {
         Lvl<float> a = level<float>(const_cast<void*>(src), p, true);
         Lvl<float> d = level<float>(dst, p, true);
         if (variant == 0) {
-            auto k = g1 ? (partials ? k_force_fused<float, true, true, 64, true, true>
-                                    : k_force_fused<float, true, true, 64, true, false>)
-                        : (partials ? k_force_fused<float, true, true, 64, false, true>
-                                    : k_force_fused<float, true, true, 64, false, false>);
+            auto k = nt ? pick_force_fused<float, true>(g1, partials)
+                        : pick_force_fused<float, false>(g1, partials);
             k<<<nft, kForceFused, 0, s>>>(p, ft, a.F, a.G, a.phic, d.phic, phi, d.F, d.G, partials);
         } else {
             auto k = g1 ? pick_step_force<float, true>(partials, nb)
@@ -404,10 +413,8 @@ hipError_t launch_force_collide(const KParams& p, const TileCfg& tc, bool fp32, 
         Lvl<double> a = level<double>(const_cast<void*>(src), p, false);
         Lvl<double> d = level<double>(dst, p, false);
         if (variant == 0) {
-            auto k = g1 ? (partials ? k_force_fused<double, false, false, 64, true, true>
-                                    : k_force_fused<double, false, false, 64, true, false>)
-                        : (partials ? k_force_fused<double, false, false, 64, false, true>
-                                    : k_force_fused<double, false, false, 64, false, false>);
+            auto k = nt ? pick_force_fused<double, true>(g1, partials)
+                        : pick_force_fused<double, false>(g1, partials);
             k<<<nft, kForceFused, 0, s>>>(p, ft, a.F, a.G, nullptr, nullptr, phi, d.F, d.G,
                                           partials);
         } else {

@@ -72,6 +72,15 @@ void set_layout(KParams& k, int layout, int aosoa_len);
 // 16^3 7.1 / 5.8, 32^3 8.3 / 7.4, 40^3 10.5 / 10.4).
 inline int site_block(const KParams& p) { return p.nsites <= 65536 ? 64 : 256; }
 
+// Whether a step's stores of a level of ncomp components are non-temporal: a
+// component's rows are whole 64-byte pieces and the level is larger than `mb`
+// MiB, about what the 256 MB Infinity Cache carries over to the next step (the
+// reasons and figures are at stc() in lb_step.h and FdFused in lb_fd.hip).
+inline bool nt_stores(const KParams& p, int ncomp, size_t elem, int mb)
+{
+    return p.cs * elem % 64 == 0 && size_t(ncomp) * p.nsites * elem > (size_t(mb) << 20);
+}
+
 // All launchers enqueue on `s` and return hipGetLastError().
 // `fp32` selects the FP32 deviation-storage instantiation; otherwise FP64.
 // A time level (`state`) is an F region and a G region of 19*stride elements
@@ -180,7 +189,9 @@ hipError_t launch_adj_export(const KParams& p, bool fp32, const void* adj, doubl
 // source level's sums there: 5 * fd_sums_blocks doubles, the number of blocks
 // of `variant` (at most max(tc.ntiles * tc.nseg, fd_step_partial_blocks)).
 int fd_step_partial_blocks(const KParams& p, int segment_x);
-int fd_sums_blocks(const KParams& p, const TileCfg& tc, int variant);
+int fd_sums_blocks(const KParams& p, const TileCfg& tc, bool fp32, int variant);
+// ... and that of its marching pass.
+int fd_march_blocks(const KParams& p, const TileCfg& tc);
 hipError_t launch_fd_init(const KParams& p, bool fp32, void* state, const double* phi0,
                           hipStream_t s);
 hipError_t launch_fd_step(const KParams& p, const TileCfg& tc, bool fp32, int variant,

@@ -236,21 +236,19 @@ void set_layout(KParams& k, int layout, int aosoa_len)
 constexpr int kCUs = 256;
 constexpr int kFused = 512;  // columns of a marching kernel's tile
 
-// Whether the LB step marches over flat tiles (lb_step.h) or over row tiles tz
-// wide.  Flat tiles need a plane of at least one tile, and a halo of at most
-// one cell per thread: nz sites before and after a tile of whole rows, and in
-// FP32 mode 4 more for any other.  Measured (us per step, rows / flat): FP32
-// 128^3 132 / 130, 192^3 461 / 451, 100 x 120 x 240 207 / 198, 151 x 105 x 160
-// 198 / 168, so wherever they can; FP64 192^3 831 / 843, 256^3 1831 / 1905
-// (flat tiles re-read more through L2), 100 x 120 x 240 340 / 346, but
-// 96^3 119 / 111, 151 x 105 x 150 409 / 354: where row tiles leave more than
-// a tenth of their lanes idle along z.
-static bool flat_tiles(const KParams& p, bool fp32, int tz)
+// Whether the LB step can march over flat tiles (lb_step.h): a plane of at
+// least one tile, and a halo of at most one cell per thread -- nz sites before
+// and after a tile of whole rows, and in FP32 mode 4 more for any other.
+static bool flat_fits(const KParams& p, bool fp32)
 {
     if (p.fd || (long long)p.ny * p.nz < kFused) return false;
-    const int halo = 2 * p.nz + (fp32 && kFused % p.nz ? 4 : 0);
-    if (halo > kFused) return false;
-    return fp32 || 10LL * p.nz < 9LL * tz * ((p.nz + tz - 1) / tz);
+    return 2 * p.nz + (fp32 && kFused % p.nz ? 4 : 0) <= kFused;
+}
+
+// rounds * (planes + 2) of a tiling: what its march takes, in planes
+static long long march_cost(const TileCfg& tc)
+{
+    return (long long)((tc.ntiles * (long long)tc.nseg + kCUs - 1) / kCUs) * (tc.sx + 2);
 }
 
 static TileCfg with_segments(const KParams& p, TileCfg tc, int segment_x)
@@ -293,14 +291,28 @@ TileCfg row_tile_config(const KParams& p, int segment_x)
     return with_segments(p, tc, segment_x);
 }
 
+// Flat tiles or row tiles.  Measured (us per step, rows / flat): FP32 128^3
+// 132 / 130, 192^3 461 / 451, 100 x 120 x 240 207 / 198, 151 x 105 x 160 198 / 168,
+// but 24^3 9.2 / 12.4, 40^3 9.8 / 12.7 (short segments, whose prologue the
+// pipelined march of flat tiles lengthens): flat where they march fewer planes,
+// or as many in segments of 8 or more.  FP64 192^3 831 / 843, 256^3 1831 / 1905
+// (flat tiles re-read more through L2), 100 x 120 x 240 340 / 346, but 96^3
+// 119 / 111, 151 x 105 x 150 409 / 354: flat where row tiles leave more than a
+// tenth of their lanes idle along z.
 TileCfg tile_config(const KParams& p, int segment_x, bool fp32)
 {
-    TileCfg tc = row_tile_config(p, segment_x);
-    if (!flat_tiles(p, fp32, tc.tz)) return tc;
-    tc.tz = 0;
-    tc.nty = 1;
-    tc.ntz = (p.ny * p.nz + kFused - 1) / kFused;
-    return with_segments(p, tc, segment_x);
+    const TileCfg rows = row_tile_config(p, segment_x);
+    if (!flat_fits(p, fp32)) return rows;
+    TileCfg flat = rows;
+    flat.tz = 0;
+    flat.nty = 1;
+    flat.ntz = (p.ny * p.nz + kFused - 1) / kFused;
+    flat = with_segments(p, flat, segment_x);
+    if (fp32) {
+        const long long r = march_cost(rows), f = march_cost(flat);
+        return f < r || (f == r && flat.sx >= 8) ? flat : rows;
+    }
+    return 10LL * p.nz < 9LL * rows.tz * ((p.nz + rows.tz - 1) / rows.tz) ? flat : rows;
 }
 
 // Where the march is short, its serial prologue and the idle CUs cost more
@@ -314,9 +326,10 @@ TileCfg tile_config(const KParams& p, int segment_x, bool fp32)
 //     128^3 248 / 255, 192^3 832 / 861
 //   stress, FP64, other tau_g (608 / 784 B): 16^3 12.8 / 6.1, 64^3 33.8 / 31.9,
 //     90 x 75 x 100 101 / 100, 96^3 112 / 126
-//   force, FP32: 16^3 19 / 8.6, 64^3 27 / 21, 96^3 84 / 63, 128^3 155 / 168
-//   force, FP64, tau_g = 1: 64^3 44 / 27, 128^3 276 / 271, 192^3 937 / 909,
-//     256^3 1999 / 2107; other tau_g: 96^3 156 / 126, 128^3 299 / 319
+//   force, FP32: 16^3 19 / 7.7, 64^3 25 / 21, 96^3 78 / 69, 72 x 111 x 150
+//     110 / 111, 128^3 161 / 171, 151 x 105 x 150 219 / 226
+//   force, FP64, tau_g = 1: 64^3 43 / 27, 128^3 290 / 275, 192^3 942 / 913,
+//     256^3 1999 / 2107; other tau_g: 96^3 155 / 134, 128^3 299 / 319
 // With sums, lattices whose collision pass cannot reduce them (a third pass)
 // march.
 int step_variant(const KParams& p, const TileCfg& tc, bool fp32, int variant, bool sums)
@@ -326,7 +339,7 @@ int step_variant(const KParams& p, const TileCfg& tc, bool fp32, int variant, bo
     if (variant != 0 || p.xh || tc.seg_req > 0) return variant;
     if (sums && !collide_sums(p)) return 0;
     const bool g1 = !fp32 && p.omega_g == 1.0;
-    const int limit = p.force ? (g1 ? 7000000 : 1500000)
+    const int limit = p.force ? (g1 ? 7100000 : fp32 ? 1100000 : 1500000)
                               : (g1 ? 2000000 : fp32 ? 700000 : 300000);
     return p.nsites <= limit ? 1 : 0;
 }

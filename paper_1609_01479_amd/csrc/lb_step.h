@@ -607,10 +607,7 @@ hipError_t launch_step_t(const KParams& p, const TileCfg& tc, int variant, const
         k<<<(p.nsites + nb - 1) / nb, nb, 0, s>>>(p, a.F, a.G, a.phic, phi64, d.F, d.G, partials);
     } else {
         const bool small = size_t(NV) * p.stride * sizeof(T) < (size_t(1) << 32);
-        // (see stc)
-        const size_t level = size_t(2 * NV) * p.nsites * sizeof(T);
-        const bool nt = p.cs * sizeof(T) % 64 == 0 && level > (size_t(192) << 20);
-        auto k = Fused<T>::get(small, tc.tz, variant == 0, g1, nt);
+        auto k = Fused<T>::get(small, tc.tz, variant == 0, g1, nt_stores(p, 2 * NV, sizeof(T), 192));
         k<<<tc.ntiles * tc.nseg, kFused, 0, s>>>(p, tc, a.F, a.G, a.phic, d.F, d.G, d.phic,
                                                  phi_src_out, partials);
     }

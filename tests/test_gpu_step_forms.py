@@ -16,9 +16,9 @@ pytestmark = pytest.mark.gpu
 # more (last tile shifted back), rows longer than any halo allows (row tiles),
 # the longest flat rows of each precision, whole-row tiles, rows of 1 and 2
 # sites, extents of 1 and 2, tiles that start and end anywhere in a row
-MARCH = [((3, 8, 64), 3), ((4, 27, 19), 2), ((2, 9, 64), 1), ((1, 3, 254), 1), ((3, 3, 255), 2),
-         ((2, 5, 256), 2), ((2, 3, 257), 1), ((3, 513, 1), 3), ((2, 300, 2), 1), ((5, 11, 100), 4),
-         ((2, 13, 150), 2), ((1, 7, 74), 1), ((4, 2, 256), 4), ((3, 6, 96), 2)]
+MARCH = [((8, 8, 64), 8), ((9, 27, 19), 8), ((2, 9, 64), 1), ((8, 3, 254), 8), ((8, 3, 255), 8),
+         ((9, 5, 256), 9), ((2, 3, 257), 1), ((8, 513, 1), 8), ((8, 300, 2), 8), ((9, 11, 100), 8),
+         ((8, 13, 150), 8), ((8, 7, 74), 8), ((8, 2, 256), 8), ((9, 6, 96), 9), ((3, 5, 100), 2)]
 
 
 @pytest.mark.parametrize("tau_g", [1.0, 1.3])
@@ -82,11 +82,11 @@ def test_fp64_forms_match_the_oracle(shape, seg, tau_g):
                                     dict(layout="aosoa", aosoa_len=4)])
 @pytest.mark.parametrize("prec", ["fp64", "fp32_dev"])
 def test_flat_tiles_in_every_layout(prec, layout):
-    shape = (3, 9, 100)
+    shape = (9, 9, 100)
     phi0 = lbinputs.spinodal_phi0(shape, seed=3, amp=0.3)
     out = []
     for lay in ({}, layout):
-        lb = make_lb(shape, precision=prec, tau_f=0.8, tau_g=1.3, segment_x=2, **lay)
+        lb = make_lb(shape, precision=prec, tau_f=0.8, tau_g=1.3, segment_x=8, **lay)
         lb.init_phi(phi0)
         lb.step(4)
         out.append(gpu_state(lb))
@@ -102,3 +102,27 @@ def test_noalloc_still_refuses_what_row_tiles_exceed():
     for kw in (dict(), dict(coupling="force")):
         with pytest.raises(LbError, match="partial blocks"):
             make_lb((1, 60000, 1), **kw).step_sums_noalloc(1, out)
+
+
+@pytest.mark.parametrize("coupling,order_param", [("force", "lb"), ("stress", "fd"), ("force", "fd")])
+@pytest.mark.parametrize("prec", ["fp64", "fp32_dev"])
+@pytest.mark.parametrize("shape,seg", [((1, 1, 1), 1), ((5, 9, 70), 3), ((4, 6, 64), 4),
+                                       ((33, 40, 50), 7), ((3, 5, 131), 2), ((116, 116, 116), 0)])
+def test_other_schemes_forms_agree_bit_for_bit(shape, seg, prec, coupling, order_param):
+    """March and two passes of the other schemes: blocks of one wave and of
+    four, rows that are whole 64-byte pieces and rows that are not, and (at
+    116^3) the update pass that marches."""
+    print(f"[forms] {shape} seg {seg} {prec} {coupling} {order_param}", flush=True)
+    phi0 = lbinputs.spinodal_phi0(shape, seed=31, amp=0.3)
+    states, sums = [], []
+    for kernel, sx in (("fused", seg), ("two_pass", 0)):
+        lb = make_lb(shape, precision=prec, tau_f=0.8, coupling=coupling, order_param=order_param,
+                     kernel=kernel, segment_x=sx)
+        lb.init_phi(phi0)
+        lb.step(2)
+        sums.append(lb.step_sums(3).cpu().numpy())
+        states.append([t for t in lb.export_dist() + lb.moments() if t is not None])
+    for a, b in zip(*states):
+        assert torch.equal(a, b)
+    n = float(np.prod(shape))
+    assert np.abs(sums[0] - sums[1]).max() <= n * n * 2.3e-16

@@ -296,6 +296,23 @@ lb_status lb_step_from(lb_ctx *ctx, const void *src_dev, void *dst_dev);
  * beyond lb_step_from's (a project extension for the reverse mode). */
 lb_status lb_step_from_phi(lb_ctx *ctx, const void *src_dev, void *dst_dev, double *phi_dev);
 
+/* nsteps >= 0 timesteps through the caller's levels in one call: from src_dev
+ * to levels_dev[0], from there to levels_dev[1], and so on (host array of
+ * nsteps device pointers), each as lb_step_from.  phis_dev (host array of
+ * nsteps device pointers, LB_OP_LB only; NULL, or NULL entries, for none):
+ * phis_dev[t] receives phi of the level that step t leaves, as
+ * lb_step_from_phi.  Consecutive levels must differ; a buffer may come again
+ * later (two scratch levels in turn).  Everything is checked before the first
+ * launch.  Passage: as lb_step_from. */
+lb_status lb_step_chain(lb_ctx *ctx, const void *src_dev, void *const *levels_dev,
+                        double *const *phis_dev, int32_t nsteps);
+
+/* phi of the caller's time level (device, N FP64 values in dense (x, y, z)
+ * order, 256-byte aligned), without touching the context's current level.
+ * LB_ESTATE on a shard.  Passage: Sec. 3.2.3, Fig. 2 (copyFromTarget); the
+ * level from the caller is a project extension, as in lb_step_from. */
+lb_status lb_level_phi(lb_ctx *ctx, const void *level_dev, double *phi_dev);
+
 /* Moments of the current (post-propagation) state, as dense FP64 device
  * arrays: rho_dev (N), u_dev (3N: x, y, z planes), phi_dev (N).  Any pointer
  * may be NULL to skip that output.  u = j/rho; with LB_COUPLING_FORCE
@@ -381,6 +398,15 @@ lb_status lb_adjoint_step(lb_ctx *ctx, const void *state_t_dev, double *dtheta3_
  * LB_OP_LB only (LB_EINVAL otherwise: LB_OP_FD holds phi in the level). */
 lb_status lb_adjoint_step_phi(lb_ctx *ctx, const void *state_t_dev, const double *phi_t_dev,
                               double *dtheta3_dev);
+
+/* nsteps >= 0 reverse steps in one call, in the order they are taken: at
+ * levels_dev[0], then levels_dev[1], ... (host array of nsteps device
+ * pointers; for a rollout the later level comes first).  phis_dev (host array,
+ * LB_OP_LB only; NULL, or NULL entries, for none): phi of each level, as for
+ * lb_adjoint_step_phi.  dtheta3_dev as for lb_adjoint_step.  Everything is
+ * checked before the first launch. */
+lb_status lb_adjoint_chain(lb_ctx *ctx, const void *const *levels_dev,
+                           const double *const *phis_dev, int32_t nsteps, double *dtheta3_dev);
 
 /* dL/dphi0 (FP64, N) of the initial state built by lb_init_phi, from the
  * current lambda_0. */

@@ -423,6 +423,46 @@ lb_status lb_step_from_phi(lb_ctx* ctx, const void* src_dev, void* dst_dev, doub
     return e == hipSuccess ? LB_OK : hip_fail(e, "lb_step_from_phi");
 }
 
+lb_status lb_step_chain(lb_ctx* ctx, const void* src_dev, void* const* levels_dev,
+                        double* const* phis_dev, int32_t nsteps)
+{
+    if (!ctx || !src_dev) return fail(LB_EINVAL, "ctx and src_dev are required");
+    if (nsteps < 0) return fail(LB_EINVAL, "nsteps must be >= 0 (got %d)", nsteps);
+    if (nsteps > 0 && !levels_dev) return fail(LB_EINVAL, "levels_dev is required");
+    if (ctx->kp.xh && nsteps > 1)
+        return fail(LB_EINVAL, "an x-slab shard advances one step per call; got nsteps = %d", nsteps);
+    if (!aligned(src_dev)) return fail(LB_EALIGN, "src_dev is not 256-byte aligned");
+    for (int32_t t = 0; t < nsteps; t++) {
+        const void* src = t ? levels_dev[t - 1] : src_dev;
+        if (!levels_dev[t]) return fail(LB_EINVAL, "levels_dev[%d] is NULL", t);
+        if (levels_dev[t] == src) return fail(LB_EINVAL, "levels_dev[%d] is the level it steps from", t);
+        if (!aligned(levels_dev[t])) return fail(LB_EALIGN, "levels_dev[%d] is not 256-byte aligned", t);
+        const double* phi = phis_dev ? phis_dev[t] : nullptr;
+        if (!phi) continue;
+        if (ctx->kp.xh) return fail(LB_ESTATE, "phi of a level is not available on a shard");
+        if (ctx->kp.fd) return fail(LB_EINVAL, "phis_dev is for LB_OP_LB");
+        if (!aligned(phi)) return fail(LB_EALIGN, "phis_dev[%d] is not 256-byte aligned", t);
+    }
+    for (int32_t t = 0; t < nsteps; t++) {
+        hipError_t e = one_step(ctx, t ? levels_dev[t - 1] : src_dev, levels_dev[t], nullptr,
+                                phis_dev ? phis_dev[t] : nullptr);
+        if (e != hipSuccess) return hip_fail(e, "lb_step_chain");
+    }
+    return LB_OK;
+}
+
+lb_status lb_level_phi(lb_ctx* ctx, const void* level_dev, double* phi_dev)
+{
+    if (!ctx || !level_dev || !phi_dev) return fail(LB_EINVAL, "ctx, level_dev and phi_dev are required");
+    if (ctx->kp.xh) return fail(LB_ESTATE, "lb_level_phi is not available on a shard");
+    if (!aligned(level_dev) || !aligned(phi_dev))
+        return fail(LB_EALIGN, "level_dev and phi_dev must be 256-byte aligned");
+    hipError_t e = ctx->kp.fd
+                       ? lbk::launch_fd_phi(ctx->kp, ctx->fp32, level_dev, phi_dev, ctx->stream)
+                       : lbk::launch_phi(ctx->kp, ctx->fp32, level_dev, phi_dev, ctx->stream);
+    return e == hipSuccess ? LB_OK : hip_fail(e, "lb_level_phi");
+}
+
 // Moments of the current level, and block partials of its sums in scratch.
 static hipError_t moments(lb_ctx* ctx, double* rho, double* u, double* phi, int* nb)
 {
@@ -551,6 +591,26 @@ static lb_status adjoint_step(lb_ctx* ctx, const void* state_t_dev, const double
                                           ctx->b.adj_scratch, part, dtheta3_dev, ctx->stream);
     if (e != hipSuccess) return hip_fail(e, "lb_adjoint_step");
     ctx->adj_cur = 1 - ctx->adj_cur;
+    return LB_OK;
+}
+
+lb_status lb_adjoint_chain(lb_ctx* ctx, const void* const* levels_dev,
+                           const double* const* phis_dev, int32_t nsteps, double* dtheta3_dev)
+{
+    if (!ctx) return fail(LB_EINVAL, "ctx is NULL");
+    if (nsteps < 0) return fail(LB_EINVAL, "nsteps must be >= 0 (got %d)", nsteps);
+    if (nsteps > 0 && !levels_dev) return fail(LB_EINVAL, "levels_dev is required");
+    for (int32_t t = 0; t < nsteps; t++) {
+        if (!levels_dev[t]) return fail(LB_EINVAL, "levels_dev[%d] is NULL", t);
+        if (!aligned(levels_dev[t])) return fail(LB_EALIGN, "levels_dev[%d] is not 256-byte aligned", t);
+        if (!phis_dev || !phis_dev[t]) continue;
+        if (ctx->kp.fd) return fail(LB_EINVAL, "phis_dev is for LB_OP_LB");
+        if (!aligned(phis_dev[t])) return fail(LB_EALIGN, "phis_dev[%d] is not 256-byte aligned", t);
+    }
+    for (int32_t t = 0; t < nsteps; t++) {
+        lb_status st = adjoint_step(ctx, levels_dev[t], phis_dev ? phis_dev[t] : nullptr, dtheta3_dev);
+        if (st != LB_OK) return st;
+    }
     return LB_OK;
 }
 

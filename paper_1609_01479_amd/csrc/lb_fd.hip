@@ -746,6 +746,13 @@ __global__ __launch_bounds__(kFdFused) void k_fd_force_fused(KParams p, TileCfg 
     if (partials) block_partials<5, kFdFused>(acc, partials);
 }
 
+__global__ __launch_bounds__(kBlock) void k_fd_phi(int n, const double* __restrict__ src,
+                                                   double* __restrict__ phi)
+{
+    const int s = blockIdx.x * kBlock + threadIdx.x;
+    if (s < n) phi[s] = src[s];
+}
+
 // Dense FP64 moments and block partials of [rho, phi, jx, jy, jz]
 // (grid-stride); u = j/rho, or with FORCE (j + F/2)/rho and sums of j + F/2.
 template <typename T, bool DEV, bool FORCE>
@@ -1279,6 +1286,14 @@ hipError_t launch_fd_adj_step(const KParams& p, bool fp32, const void* state, do
         if (e != hipSuccess) return e;
     }
     return launch_adj_stencil(p, fp32, adj_scratch, adj_prev, partials, partials2, nb, dtheta, s);
+}
+
+hipError_t launch_fd_phi(const KParams& p, bool fp32, const void* state, double* phi, hipStream_t s)
+{
+    void* st = const_cast<void*>(state);
+    const double* src = fp32 ? fd_level<float>(st, p).phi : fd_level<double>(st, p).phi;
+    k_fd_phi<<<fd_grid(p), kBlock, 0, s>>>(p.nsites, src, phi);
+    return hipGetLastError();
 }
 
 hipError_t launch_fd_moments(const KParams& p, bool fp32, const void* state, double* rho,

@@ -204,6 +204,8 @@ hipError_t launch_fd_step(const KParams& p, const TileCfg& tc, bool fp32, int va
 hipError_t launch_fd_adj_step(const KParams& p, bool fp32, const void* state, double* work,
                               const void* adj_next, void* adj_prev, void* adj_scratch,
                               double* partials, double* dtheta, hipStream_t s);
+// phi of the level `state` (a copy of its phi field)
+hipError_t launch_fd_phi(const KParams& p, bool fp32, const void* state, double* phi, hipStream_t s);
 hipError_t launch_fd_moments(const KParams& p, bool fp32, const void* state, double* rho,
                              double* u, double* phi, double* partials, int* nblocks_out,
                              hipStream_t s);

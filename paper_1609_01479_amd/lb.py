@@ -39,6 +39,12 @@ def _ptr(t: torch.Tensor | None):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
 
+def _ptrs(tensors):
+    """Host array of the device pointers of `tensors` (None: NULL)."""
+    return (ctypes.c_void_p * len(tensors))(*[None if t is None else t.data_ptr()
+                                              for t in tensors])
+
+
 class LB:
     """One D3Q19 binary-fluid lattice on one GPU.
 
@@ -221,6 +227,34 @@ class LB:
             self._check_phi(phi_out)
             self._call("lb_step_from_phi", _ptr(src), _ptr(dst), _ptr(phi_out))
 
+    def _check_level(self, t: torch.Tensor) -> None:
+        if t.numel() * t.element_size() != self.sizes.state_bytes:
+            raise ValueError("state buffer has the wrong size")
+
+    def step_chain(self, src: torch.Tensor, levels, phis=None) -> None:
+        """len(levels) steps in one call: from `src` into levels[0], from there
+        into levels[1], and so on (caller buffers; two scratch levels may take
+        turns).  phis (LB order parameter): for each step None or the FP64
+        tensor that receives phi of the level it leaves (lb_step_chain)."""
+        self._check_level(src)
+        for t in levels:
+            self._check_level(t)
+        if phis is not None:
+            if len(phis) != len(levels):
+                raise ValueError("phis must have one entry per level")
+            for t in phis:
+                if t is not None:
+                    self._check_phi(t)
+        self._call("lb_step_chain", _ptr(src), _ptrs(levels),
+                   None if phis is None else _ptrs(phis), ctypes.c_int32(len(levels)))
+
+    def level_phi(self, level: torch.Tensor) -> torch.Tensor:
+        """phi of the time level in `level` (a caller buffer)."""
+        self._check_level(level)
+        out = self._out(*self.shape)
+        self._call("lb_level_phi", _ptr(level), _ptr(out))
+        return out
+
     def _check_phi(self, t: torch.Tensor) -> None:
         if (t.dtype != torch.float64 or not t.is_contiguous() or t.numel() != self.nsites
                 or t.device != self.device):
@@ -293,6 +327,21 @@ class LB:
             self._call("lb_adjoint_step_phi", _ptr(state_t), _ptr(phi), _ptr(dtheta))
         else:
             self._call("lb_adjoint_step", _ptr(state_t), _ptr(dtheta))
+
+    def adjoint_chain(self, levels, dtheta: torch.Tensor | None = None, phis=None) -> None:
+        """len(levels) reverse steps in one call, at levels[0] first (for a
+        rollout the latest level); phis: for each None or phi of the level
+        (lb_adjoint_chain)."""
+        for t in levels:
+            self._check_level(t)
+        if phis is not None:
+            if len(phis) != len(levels):
+                raise ValueError("phis must have one entry per level")
+            for t in phis:
+                if t is not None:
+                    self._check_phi(t)
+        self._call("lb_adjoint_chain", _ptrs(levels), None if phis is None else _ptrs(phis),
+                   ctypes.c_int32(len(levels)), _ptr(dtheta))
 
     def adjoint_dist(self):
         """(dL/df, dL/dg) of the current adjoint level as FP64 (19, nx, ny, nz)

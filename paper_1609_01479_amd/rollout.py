@@ -5,9 +5,10 @@ backward(dL/dphi_T) returns dL/dphi0 and dL/d(A, B, kappa) from the
 hand-written adjoint kernels (lb_adjoint_step), with checkpointing and
 recomputation: the forward keeps the state every k steps (k = ceil(sqrt(T))
 by default); the backward takes each checkpoint in reverse order,
-recomputes the k - 1 later states of its segment with lb_step_from (each
+recomputes the k - 1 later states of its segment (lb_step_chain: each
 written once, straight into its segment buffer), and walks the adjoint back
-through them.  Memory: ceil(T/k) + max(k - 1, 2) states instead of T (the
+through them (lb_adjoint_chain).  A segment is one native call each way: step
+by step from Python, a small lattice's rollout waited for the host.  Memory: ceil(T/k) + max(k - 1, 2) states instead of T (the
 checkpoints, and the segment buffers or the forward's two scratch levels),
 plus, for the LB order parameter, FP64 phi fields (8 bytes per site each) that hand phi of
 each level to its reverse step, so that none runs a phi pass: k - 1 for the
@@ -17,8 +18,7 @@ step that produces it, so a small k costs no copies.  interval="auto" sizes k
 to the device's memory: on a 288 GB MI355X the 128^3 FP32-storage rollout of
 1000 steps keeps every second state instead of every 32nd.
 
-All state copies are lossless (lb_get_state / lb_set_state), and the forward
-step is deterministic, so the recomputed states are bit-identical to the
+The forward step is deterministic, so the recomputed states are bit-identical to the
 forward's.
 """
 from __future__ import annotations
@@ -63,7 +63,12 @@ class _Rollout(torch.autograd.Function):
     @staticmethod
     def forward(ctx, phi0, A, B, kappa, cfg):
         T = int(cfg["nsteps"])
-        lb = LB(phi0.shape, A=float(A), B=float(B), kappa=float(kappa),
+        # one read-back for the parameters that are on the device
+        theta = [v.detach() for v in (A, B, kappa)]
+        if all(v.is_cuda and v.device == theta[0].device for v in theta):
+            theta = torch.stack([v.reshape(()).to(torch.float64) for v in theta]).tolist()
+        a, b, kap = (float(v) for v in theta)
+        lb = LB(phi0.shape, A=a, B=b, kappa=kap,
                 gamma=cfg.get("gamma", 0.5), tau_f=cfg.get("tau_f", 1.0),
                 tau_g=cfg.get("tau_g", 1.0), rho0=cfg.get("rho0", 1.0),
                 precision=cfg.get("precision", "fp64"), adjoint=True, device=phi0.device,
@@ -85,40 +90,36 @@ class _Rollout(torch.autograd.Function):
         else:
             k = int(interval or default_interval(T))
         lb.init_phi(phi0.detach())
-        # each step writes a caller buffer (lb_step_from): a segment's last
-        # step straight into the next checkpoint, its others into two scratch
-        # levels, so the checkpoints cost no copies; the rollout's final
-        # step goes to a scratch level that becomes the context's, which
-        # phi() reads.  The last step of each segment also stores phi of the
-        # level it leaves (lb_step_from_phi), which that level's reverse step
-        # needs and no recomputation forms.
-        ckpts = [lb.get_state()]
+        # the steps write caller buffers, each segment in one call
+        # (lb_step_chain): a segment's last step straight into the next
+        # checkpoint, its others into two scratch levels, so the checkpoints
+        # cost no copies.  The context's own two levels are the first
+        # checkpoint (where lb_init_phi put the initial state) and one of the
+        # scratch levels.  The last step of each segment also stores phi of
+        # the level it leaves, which that level's reverse step needs and no
+        # recomputation forms.
+        ckpts = [lb.state_buf[0]]
         ends = []
-        work = [lb.new_state(), lb.new_state()] if T > 0 else []
-        t = 0
-        while t < T:
-            n = min(k, T - t)
-            src = ckpts[-1]
-            for j in range(n):
-                ph = None
-                if j == n - 1 and phi_b:
-                    ph = torch.empty(lb.shape, dtype=torch.float64, device=lb.device)
-                    ends.append(ph)
-                if t + j == T - 1:
-                    dst = work[1] if src is work[0] else work[0]
-                elif j == n - 1:
-                    dst = lb.new_state()
-                else:
-                    dst = work[j & 1]
-                lb.step_from(src, dst, phi_out=ph)
-                src = dst
-            if t + n < T:
-                ckpts.append(src)
-            t += n
-        if T > 0:
-            lb.set_state(src)
+        work = [lb.state_buf[1], lb.new_state() if T > 1 else None]
+        dev, nbytes = lb.device, int(lb.sizes.state_bytes)
+        src = ckpts[0]
+        with torch.cuda.device(dev), torch.cuda.stream(lb.stream):
+            for t in range(0, T, k):
+                n = min(k, T - t)
+                src = ckpts[-1]
+                levels = [work[j & 1] for j in range(n)]
+                if t + n < T:
+                    levels[-1] = torch.empty(nbytes, dtype=torch.uint8, device=dev)
+                    ckpts.append(levels[-1])
+                phis = None
+                if phi_b:
+                    phis = [None] * n
+                    phis[-1] = torch.empty(lb.shape, dtype=torch.float64, device=dev)
+                    ends.append(phis[-1])
+                lb.step_chain(src, levels, phis)
+                src = levels[-1]
+        phiT = lb.level_phi(src)
         del work
-        phiT = lb.phi()
         ctx.lb = lb
         ctx.ckpts = ckpts
         ctx.ends = ends
@@ -130,31 +131,27 @@ class _Rollout(torch.autograd.Function):
     @staticmethod
     def backward(ctx, gphi):
         lb, ckpts, ends, T, k = ctx.lb, ctx.ckpts, ctx.ends, ctx.T, ctx.k
-        dtheta = torch.zeros(3, dtype=torch.float64, device=lb.device)
+        dev, nbytes = lb.device, int(lb.sizes.state_bytes)
         lb.adjoint_seed(gphi.detach())
-        # segment buffers: the checkpoint itself is the segment's first state;
-        # the others are recomputed in place by one step each (no copies)
-        seg = [None] + [lb.new_state() for _ in range(min(k, T) - 1)]
-        # LB order parameter: the recomputing steps also store phi of each
-        # level they start from, and the forward stored phi of each segment's
-        # last level, so no reverse step runs a phi pass (the
-        # finite-difference level holds phi)
-        phis = None
-        if not lb.fd:
-            phis = [torch.empty(lb.shape, dtype=torch.float64, device=lb.device)
-                    for _ in range(min(k, T) - 1)]
+        with torch.cuda.device(dev), torch.cuda.stream(lb.stream):
+            dtheta = torch.zeros(3, dtype=torch.float64, device=dev)
+            # segment buffers: the checkpoint itself is the segment's first
+            # state; the others are recomputed in place (no copies)
+            m = min(k, T) - 1
+            seg = [torch.empty(nbytes, dtype=torch.uint8, device=dev) for _ in range(m)]
+            # LB order parameter: the recomputing steps also store phi of each
+            # level they start from, and the forward stored phi of each
+            # segment's last level, so no reverse step runs a phi pass (the
+            # finite-difference level holds phi)
+            phis = None
+            if not lb.fd:
+                phis = [torch.empty(lb.shape, dtype=torch.float64, device=dev) for _ in range(m)]
         for si in reversed(range(len(ckpts) if T > 0 else 0)):
-            t0 = si * k
-            t1 = min(T, t0 + k)
-            seg[0] = ckpts[si]
-            for j in range(1, t1 - t0):
-                lb.step_from(seg[j - 1], seg[j], phi_out=phis[j - 1] if phis else None)
-            for t in reversed(range(t0, t1)):
-                if t + 1 < t1:
-                    phi = phis[t - t0] if phis else None
-                else:
-                    phi = ends[si] if ends else None
-                lb.adjoint_step(seg[t - t0], dtheta, phi=phi)
+            n = min(T - si * k, k)
+            lb.step_chain(ckpts[si], seg[:n - 1], phis[:n - 1] if phis else None)
+            levels = [ckpts[si]] + seg[:n - 1]
+            lb.adjoint_chain(levels[::-1], dtheta,
+                             None if phis is None else [ends[si]] + phis[:n - 1][::-1])
         dphi0 = lb.adjoint_phi0()
         ctx.lb = None
         ctx.ckpts = None
@@ -177,9 +174,7 @@ def rollout(phi0: torch.Tensor, A, B, kappa, nsteps: int, *, interval: int | str
     few recomputed steps.  The gradients do not depend on k (the recomputed
     states are bit-identical).  info (a dict, optional) receives "interval",
     the k used."""
-    dev = phi0.device
-    as_t = lambda v: v if torch.is_tensor(v) else torch.tensor(float(v), dtype=torch.float64,  # noqa: E731
-                                                               device=dev)
+    as_t = lambda v: v if torch.is_tensor(v) else torch.tensor(float(v), dtype=torch.float64)  # noqa: E731
     cfg = dict(nsteps=nsteps, interval=interval, memory_budget=memory_budget, gamma=gamma,
                tau_f=tau_f, tau_g=tau_g, rho0=rho0, precision=precision,
                order_param=order_param, coupling=coupling)

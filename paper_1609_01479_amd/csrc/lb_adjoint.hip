@@ -74,7 +74,7 @@ __device__ __forceinline__ T opaque_copy(T v)
 // transposed local collision Jacobian at x with the forward locals recomputed
 // from the saved state; writes lf, lg of the previous level, the stencil
 // cotangents, and block partials of d/d(A, B, kappa).
-template <typename T, typename AR, bool DEV, bool G1>
+template <typename T, typename AR, bool DEV, bool G1, int NB>
 __device__ __forceinline__ void adj_local_body(const KParams& p, const T* __restrict__ F,
                                                const double* __restrict__ phi,
                                                const T* __restrict__ an, T* __restrict__ ap,
@@ -82,7 +82,7 @@ __device__ __forceinline__ void adj_local_body(const KParams& p, const T* __rest
 {
     double dth[3] = {0.0, 0.0, 0.0};
     const unsigned S = p.stride;
-    for (XcdSweep w = xcd_sweep(p.nsites, kBlock); w.s < w.end; w.s += w.stride) {
+    for (XcdSweep w = xcd_sweep(p.nsites, NB); w.s < w.end; w.s += w.stride) {
         const int s = w.s;
         const Geo q = geo_of(p, s);
         T lfr[NV], lgr[NV], lpr[NV], f[NV];
@@ -189,7 +189,7 @@ __device__ __forceinline__ void adj_local_body(const KParams& p, const T* __rest
         dth[1] += 4.5 * (dtrs * 0.75 * dph * dph * dph * dph + p.gamma * dph * dph * dph * dtrt);
         dth[2] += 4.5 * (dtrs * (-dph * st.lap - 0.5 * g2) + double(gsg) - p.gamma * st.lap * dtrt);
     }
-    block_partials<3>(dth, partials);
+    block_partials<3, NB>(dth, partials);
 }
 
 // FP32 storage with FP64 arithmetic: the transposed collision sums 19
@@ -204,22 +204,22 @@ __device__ __forceinline__ void adj_local_body(const KParams& p, const T* __rest
 // waves made the compiler serialise the loads: 2.2x slower).  The FP32
 // kernel runs 3-5% faster this way; the FP64 ones gain nothing but are kept
 // at the budget that needs no AGPRs.
-template <bool G1>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_adj_local_f32(
+template <bool G1, int NB>
+__global__ __launch_bounds__(NB) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_adj_local_f32(
     KParams p, const float* __restrict__ F, const double* __restrict__ phi,
     const float* __restrict__ an, float* __restrict__ ap, float* __restrict__ sc,
     double* __restrict__ partials)
 {
-    adj_local_body<float, double, true, G1>(p, F, phi, an, ap, sc, partials);
+    adj_local_body<float, double, true, G1, NB>(p, F, phi, an, ap, sc, partials);
 }
 
-template <bool G1>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_adj_local_f64(
+template <bool G1, int NB>
+__global__ __launch_bounds__(NB) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_adj_local_f64(
     KParams p, const double* __restrict__ F, const double* __restrict__ phi,
     const double* __restrict__ an, double* __restrict__ ap, double* __restrict__ sc,
     double* __restrict__ partials)
 {
-    adj_local_body<double, double, false, G1>(p, F, phi, an, ap, sc, partials);
+    adj_local_body<double, double, false, G1, NB>(p, F, phi, an, ap, sc, partials);
 }
 
 // Force coupling (u = (j + F/2)/rho in both equilibria, f^eq = w rho (1 +
@@ -237,7 +237,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 // through Pi at the face neighbours: k_adj_force_pi.
 // F_IN: F comes from k_adj_force_f in the dL/dF slots of sc (read at the own
 // site before they are overwritten), instead of being formed here.
-template <typename T, typename AR, bool DEV, bool F_IN, bool G1>
+template <typename T, typename AR, bool DEV, bool F_IN, bool G1, int NB>
 __device__ __forceinline__ void adj_local_force_body(const KParams& p, const T* __restrict__ F,
                                                      const double* __restrict__ phi,
                                                      const T* __restrict__ an, T* __restrict__ ap,
@@ -249,7 +249,7 @@ __device__ __forceinline__ void adj_local_force_body(const KParams& p, const T* 
     const AR A = AR(p.A), B = AR(p.B), kap = AR(p.kappa), gam = AR(p.gamma);
     const AR omf = AR(p.omega_f), omg = AR(p.omega_g), pref = AR(1) - AR(0.5) * omf;
     const AR h = AR(4.5), third = AR(1.0 / 3.0);
-    for (XcdSweep w = xcd_sweep(p.nsites, kBlock); w.s < w.end; w.s += w.stride) {
+    for (XcdSweep w = xcd_sweep(p.nsites, NB); w.s < w.end; w.s += w.stride) {
         const int s = w.s;
         const Geo q = geo_of(p, s);
         T lfr[NV], lgr[NV], lpr[NV], f[NV];
@@ -369,25 +369,25 @@ __device__ __forceinline__ void adj_local_force_body(const KParams& p, const T* 
         dth[1] += 4.5 * p.gamma * dph * dph * dph * dtrt;
         dth[2] += -4.5 * p.gamma * st.lap * dtrt;
     }
-    block_partials<3>(dth, partials);
+    block_partials<3, NB>(dth, partials);
 }
 
-template <bool G1>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_adj_local_force_f32(
+template <bool G1, int NB>
+__global__ __launch_bounds__(NB) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_adj_local_force_f32(
     KParams p, const float* __restrict__ F, const double* __restrict__ phi,
     const float* __restrict__ an, float* __restrict__ ap, float* __restrict__ sc,
     double* __restrict__ partials)
 {
-    adj_local_force_body<float, double, true, false, G1>(p, F, phi, an, ap, sc, partials);
+    adj_local_force_body<float, double, true, false, G1, NB>(p, F, phi, an, ap, sc, partials);
 }
 
-template <bool G1>
-__global__ __launch_bounds__(kBlock) void k_adj_local_force_f64(
+template <bool G1, int NB>
+__global__ __launch_bounds__(NB) void k_adj_local_force_f64(
     KParams p, const double* __restrict__ F, const double* __restrict__ phi,
     const double* __restrict__ an, double* __restrict__ ap, double* __restrict__ sc,
     double* __restrict__ partials)
 {
-    adj_local_force_body<double, double, false, true, G1>(p, F, phi, an, ap, sc, partials);
+    adj_local_force_body<double, double, false, true, G1, NB>(p, F, phi, an, ap, sc, partials);
 }
 
 // F = -div Pi of the phi field (T-rounded, as the forward uses it) into the
@@ -399,7 +399,7 @@ template <typename T>
 __global__ __launch_bounds__(kBlock) void k_adj_force_f(KParams p, const double* __restrict__ phi,
                                                         T* __restrict__ sc)
 {
-    const int s = xcd_block() * kBlock + threadIdx.x;
+    const int s = xcd_block() * int(blockDim.x) + threadIdx.x;
     if (s >= p.nsites) return;
     double Fd[3];
     force_from_phi(p, geo_of(p, s), phi, Fd);
@@ -417,8 +417,8 @@ __global__ __launch_bounds__(kBlock) void k_adj_force_f(KParams p, const double*
 //   c += -kappa phi trL,
 // and d/d(A, B, kappa) += trL (phi^2/2, 3 phi^4/4, -phi lap - |grad|^2/2)
 // + (0, 0, grad.L.grad).  Each site updates only its own cotangents.
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_adj_force_pi(KParams p, const double* __restrict__ phi,
+template <typename T, int NB>
+__global__ __launch_bounds__(NB) void k_adj_force_pi(KParams p, const double* __restrict__ phi,
                                                          T* __restrict__ sc,
                                                          double* __restrict__ partials)
 {
@@ -426,7 +426,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_force_pi(KParams p, const double
     const unsigned S = p.stride;
     const T* __restrict__ lF[3] = {sc + 5 * size_t(S), sc + 6 * size_t(S), sc + 7 * size_t(S)};
     const T A = T(p.A), B = T(p.B), kap = T(p.kappa);
-    for (XcdSweep w = xcd_sweep(p.nsites, kBlock); w.s < w.end; w.s += w.stride) {
+    for (XcdSweep w = xcd_sweep(p.nsites, NB); w.s < w.end; w.s += w.stride) {
         const int s = w.s;
         const Geo q = geo_of(p, s);
         const int nb[3][2] = {{site_of(p, q.xp, q.y, q.z), site_of(p, q.xm, q.y, q.z)},
@@ -461,7 +461,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_force_pi(KParams p, const double
         dth[1] += dtr * 0.75 * dph * dph * dph * dph;
         dth[2] += dtr * (-dph * st.lap - 0.5 * g2) + gLg;
     }
-    block_partials<3>(dth, partials);
+    block_partials<3, NB>(dth, partials);
 }
 
 // lp(x) = a(x) - sum_a D_a b_a (x) + lap c (x).  With dtheta, workgroups
@@ -488,14 +488,14 @@ __device__ __forceinline__ void adj_stencil_site(const KParams& p, int s, const 
     ap[2 * NV * S + s] = a[s] - divb + lapc;
 }
 
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_adj_stencil(KParams p, const T* __restrict__ sc,
+template <typename T, int NB>
+__global__ __launch_bounds__(NB) void k_adj_stencil(KParams p, const T* __restrict__ sc,
                                                         T* __restrict__ ap,
                                                         const double* __restrict__ partials,
                                                         const double* __restrict__ partials2,
                                                         int nparts, double* __restrict__ dtheta)
 {
-    const int s = xcd_block() * kBlock + threadIdx.x;
+    const int s = xcd_block() * NB + threadIdx.x;
     if (s < p.nsites) adj_stencil_site<T>(p, s, sc, ap);
     if (!dtheta) return;
     // workgroup k < 3 adds component k (one workgroup does all three on a
@@ -503,10 +503,10 @@ __global__ __launch_bounds__(kBlock) void k_adj_stencil(KParams p, const T* __re
     const int k0 = gridDim.x >= 3 ? int(blockIdx.x) : 0;
     const int nk = gridDim.x >= 3 ? 1 : 3;
     if (int(blockIdx.x) != k0 || k0 >= 3) return;
-    reduce_partials_block(partials + size_t(k0) * nparts, nparts, nk, dtheta + k0, true);
+    reduce_partials_block<NB>(partials + size_t(k0) * nparts, nparts, nk, dtheta + k0, true);
     if (partials2) {
         __syncthreads();
-        reduce_partials_block(partials2 + size_t(k0) * nparts, nparts, nk, dtheta + k0, true);
+        reduce_partials_block<NB>(partials2 + size_t(k0) * nparts, nparts, nk, dtheta + k0, true);
     }
 }
 
@@ -549,12 +549,6 @@ int grid_for(const KParams& p) { return (p.nsites + kBlock - 1) / kBlock; }
 // tau_g = 1: the levels' lg is identically zero (see the top of this file)
 bool g_free(const KParams& p) { return p.omega_g == 1.0; }
 
-int reduction_grid(const KParams& p)
-{
-    const int g = grid_for(p);
-    return g < kMaxPartialBlocks ? g : kMaxPartialBlocks;
-}
-
 }  // namespace
 
 hipError_t launch_adj_seed(const KParams& p, bool fp32, void* adj, void* other, const double* dphi,
@@ -570,6 +564,40 @@ hipError_t launch_adj_seed(const KParams& p, bool fp32, void* adj, void* other, 
     return hipGetLastError();
 }
 
+// The launches of one reverse step with blocks of NB threads.
+namespace {
+
+template <int NB>
+hipError_t adj_step(const KParams& p, bool fp32, const void* state, const double* phi,
+                    const void* adj_next, void* adj_prev, void* adj_scratch, double* partials,
+                    double* partials2, int nb, hipStream_t s)
+{
+    const bool g1 = g_free(p);
+    if (fp32) {
+        const float* F = static_cast<const float*>(state);
+        const float* an = static_cast<const float*>(adj_next);
+        float* ap = static_cast<float*>(adj_prev);
+        float* sc = static_cast<float*>(adj_scratch);
+        auto k = p.force ? (g1 ? k_adj_local_force_f32<true, NB> : k_adj_local_force_f32<false, NB>)
+                         : (g1 ? k_adj_local_f32<true, NB> : k_adj_local_f32<false, NB>);
+        k<<<nb, NB, 0, s>>>(p, F, phi, an, ap, sc, partials);
+    } else {
+        const double* F = static_cast<const double*>(state);
+        const double* an = static_cast<const double*>(adj_next);
+        double* ap = static_cast<double*>(adj_prev);
+        double* sc = static_cast<double*>(adj_scratch);
+        if (p.force) k_adj_force_f<double><<<(p.nsites + NB - 1) / NB, NB, 0, s>>>(p, phi, sc);
+        auto k = p.force ? (g1 ? k_adj_local_force_f64<true, NB> : k_adj_local_force_f64<false, NB>)
+                         : (g1 ? k_adj_local_f64<true, NB> : k_adj_local_f64<false, NB>);
+        k<<<nb, NB, 0, s>>>(p, F, phi, an, ap, sc, partials);
+    }
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !p.force) return e;
+    return launch_adj_force_pi(p, fp32, phi, adj_scratch, partials2, nb, s);
+}
+
+}  // namespace
+
 hipError_t launch_adj_step(const KParams& p, bool fp32, const void* state,
                            const double* phi_given, double* phi,
                            const void* adj_next, void* adj_prev, void* adj_scratch,
@@ -582,51 +610,12 @@ hipError_t launch_adj_step(const KParams& p, bool fp32, const void* state,
         hipError_t e = launch_phi(p, fp32, state, phi, s);
         if (e != hipSuccess) return e;
     }
-    // 1024 workgroups of 256 threads, each thread looping over its sites (a
-    // few resident rounds at the local kernels' 1-3 waves per SIMD; a grid
-    // of exactly one round measured no faster); the parameter reduction (in
-    // the stencil kernel's first workgroups) then reads half the partials of
-    // 2048 workgroups (measured as a launch of its own at 128^3: 9.9 -> 5.5
-    // us, k_adj_local unchanged)
-    constexpr int kAdjBlocks = 1024;
-    const int nb = reduction_grid(p) < kAdjBlocks ? reduction_grid(p) : kAdjBlocks;
+    const int nb = adj_blocks(p);
     // force coupling: the second pass's partials follow the first's
     double* partials2 = p.force ? partials + 3 * kAdjBlocks : nullptr;
-    if (fp32) {
-        const float* F = static_cast<const float*>(state);
-        const float* an = static_cast<const float*>(adj_next);
-        float* ap = static_cast<float*>(adj_prev);
-        float* sc = static_cast<float*>(adj_scratch);
-        if (p.force) {
-            if (g_free(p))
-                k_adj_local_force_f32<true><<<nb, kBlock, 0, s>>>(p, F, phi, an, ap, sc, partials);
-            else
-                k_adj_local_force_f32<false><<<nb, kBlock, 0, s>>>(p, F, phi, an, ap, sc, partials);
-            k_adj_force_pi<float><<<nb, kBlock, 0, s>>>(p, phi, sc, partials2);
-        } else if (g_free(p)) {
-            k_adj_local_f32<true><<<nb, kBlock, 0, s>>>(p, F, phi, an, ap, sc, partials);
-        } else {
-            k_adj_local_f32<false><<<nb, kBlock, 0, s>>>(p, F, phi, an, ap, sc, partials);
-        }
-    } else {
-        const double* F = static_cast<const double*>(state);
-        const double* an = static_cast<const double*>(adj_next);
-        double* ap = static_cast<double*>(adj_prev);
-        double* sc = static_cast<double*>(adj_scratch);
-        if (p.force) {
-            k_adj_force_f<double><<<grid_for(p), kBlock, 0, s>>>(p, phi, sc);
-            if (g_free(p))
-                k_adj_local_force_f64<true><<<nb, kBlock, 0, s>>>(p, F, phi, an, ap, sc, partials);
-            else
-                k_adj_local_force_f64<false><<<nb, kBlock, 0, s>>>(p, F, phi, an, ap, sc, partials);
-            k_adj_force_pi<double><<<nb, kBlock, 0, s>>>(p, phi, sc, partials2);
-        } else if (g_free(p)) {
-            k_adj_local_f64<true><<<nb, kBlock, 0, s>>>(p, F, phi, an, ap, sc, partials);
-        } else {
-            k_adj_local_f64<false><<<nb, kBlock, 0, s>>>(p, F, phi, an, ap, sc, partials);
-        }
-    }
-    const hipError_t e = hipGetLastError();
+    auto step = site_block(p) == 64 ? adj_step<64> : adj_step<kBlock>;
+    const hipError_t e = step(p, fp32, state, phi, adj_next, adj_prev, adj_scratch, partials,
+                              partials2, nb, s);
     if (e != hipSuccess) return e;
     return launch_adj_stencil(p, fp32, adj_scratch, adj_prev, partials, partials2, nb, dtheta, s);
 }
@@ -634,12 +623,14 @@ hipError_t launch_adj_step(const KParams& p, bool fp32, const void* state,
 hipError_t launch_adj_force_pi(const KParams& p, bool fp32, const double* phi, void* adj_scratch,
                                double* partials2, int nblocks, hipStream_t s)
 {
-    if (fp32)
-        k_adj_force_pi<float><<<nblocks, kBlock, 0, s>>>(p, phi, static_cast<float*>(adj_scratch),
-                                                         partials2);
-    else
-        k_adj_force_pi<double><<<nblocks, kBlock, 0, s>>>(p, phi, static_cast<double*>(adj_scratch),
-                                                          partials2);
+    const int nt = site_block(p);
+    if (fp32) {
+        auto k = nt == 64 ? k_adj_force_pi<float, 64> : k_adj_force_pi<float, kBlock>;
+        k<<<nblocks, nt, 0, s>>>(p, phi, static_cast<float*>(adj_scratch), partials2);
+    } else {
+        auto k = nt == 64 ? k_adj_force_pi<double, 64> : k_adj_force_pi<double, kBlock>;
+        k<<<nblocks, nt, 0, s>>>(p, phi, static_cast<double*>(adj_scratch), partials2);
+    }
     return hipGetLastError();
 }
 
@@ -647,14 +638,16 @@ hipError_t launch_adj_stencil(const KParams& p, bool fp32, const void* adj_scrat
                               void* adj_prev, const double* partials, const double* partials2,
                               int nparts, double* dtheta, hipStream_t s)
 {
-    if (fp32)
-        k_adj_stencil<float><<<grid_for(p), kBlock, 0, s>>>(p, static_cast<const float*>(adj_scratch),
-                                                            static_cast<float*>(adj_prev), partials,
-                                                            partials2, nparts, dtheta);
-    else
-        k_adj_stencil<double><<<grid_for(p), kBlock, 0, s>>>(p, static_cast<const double*>(adj_scratch),
-                                                             static_cast<double*>(adj_prev), partials,
-                                                             partials2, nparts, dtheta);
+    const int nt = site_block(p), grid = (p.nsites + nt - 1) / nt;
+    if (fp32) {
+        auto k = nt == 64 ? k_adj_stencil<float, 64> : k_adj_stencil<float, kBlock>;
+        k<<<grid, nt, 0, s>>>(p, static_cast<const float*>(adj_scratch),
+                              static_cast<float*>(adj_prev), partials, partials2, nparts, dtheta);
+    } else {
+        auto k = nt == 64 ? k_adj_stencil<double, 64> : k_adj_stencil<double, kBlock>;
+        k<<<grid, nt, 0, s>>>(p, static_cast<const double*>(adj_scratch),
+                              static_cast<double*>(adj_prev), partials, partials2, nparts, dtheta);
+    }
     return hipGetLastError();
 }
 

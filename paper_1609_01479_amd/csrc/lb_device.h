@@ -604,24 +604,25 @@ __device__ __forceinline__ void lds_barrier()
 // us at 128^3 so, or with the reduction ahead of the collision, where it
 // split the loads in two rounds; 256 without sums).
 // Final reduction of `nblocks` block partials of `ncomp` (at most 5)
-// components, laid out as block_partials writes them, by one workgroup of
-// kBlock threads in a fixed order (strided per-thread sums, a wavefront
-// butterfly, then the four waves pairwise): out[k] = sum, or out[k] += sum.
-// Every thread of the workgroup must call it.
+// components, laid out as block_partials writes them, by one workgroup of NB
+// threads (one wave or four) in a fixed order (strided per-thread sums, a
+// wavefront butterfly, then the four waves pairwise): out[k] = sum, or
+// out[k] += sum.  Every thread of the workgroup must call it.
+template <int NB = kBlock>
 __device__ __forceinline__ void reduce_partials_block(const double* __restrict__ partials,
                                                       int nblocks, int ncomp,
                                                       double* __restrict__ out, bool accumulate)
 {
-    static_assert(kBlock == 256, "four waves");
-    constexpr int KMAX = 5;
-    __shared__ double sm[KMAX][kBlock / 64];
+    static_assert(NB == 64 || NB == 256, "one wave or four");
+    constexpr int KMAX = 5, NW = NB / 64;
+    __shared__ double sm[KMAX][NW];
     double v[KMAX];
 #pragma unroll
     for (int k = 0; k < KMAX; k++) {
         v[k] = 0.0;
         if (k < ncomp)
 #pragma unroll 8
-            for (int j = threadIdx.x; j < nblocks; j += kBlock) v[k] += partials[k * nblocks + j];
+            for (int j = threadIdx.x; j < nblocks; j += NB) v[k] += partials[k * nblocks + j];
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1)
@@ -633,7 +634,8 @@ __device__ __forceinline__ void reduce_partials_block(const double* __restrict__
     __syncthreads();
     if (threadIdx.x < ncomp) {
         const int k = threadIdx.x;
-        const double t = (sm[k][0] + sm[k][1]) + (sm[k][2] + sm[k][3]);
+        const double t = NW == 1 ? sm[k][0]
+                                 : (sm[k][0] + sm[k][1 % NW]) + (sm[k][2 % NW] + sm[k][3 % NW]);
         out[k] = accumulate ? out[k] + t : t;
     }
 }

@@ -844,7 +844,7 @@ __global__ __launch_bounds__(kBlock) void k_fd_adj_prep(KParams p, const T* __re
                                                         const double* __restrict__ phi,
                                                         T* __restrict__ work, T* __restrict__ sc)
 {
-    const int s = xcd_block() * kBlock + threadIdx.x;
+    const int s = xcd_block() * int(blockDim.x) + threadIdx.x;
     if (s >= p.nsites) return;
     const Geo q = geo_of(p, s);
     T f[NV];
@@ -888,8 +888,8 @@ __global__ __launch_bounds__(kBlock) void k_fd_adj_prep(KParams p, const T* __re
 // f^eq): the flux's lambda_u joins the collision's, the total goes to j,
 // rho and F as in the LB scheme's force adjoint (lb_adjoint.hip), and dL/dF
 // is written after the five cotangents for k_adj_force_pi.
-template <typename T, bool FORCE>
-__global__ __launch_bounds__(kBlock) void k_fd_adj_local(KParams p, const double* __restrict__ phi,
+template <typename T, bool FORCE, int NB>
+__global__ __launch_bounds__(NB) void k_fd_adj_local(KParams p, const double* __restrict__ phi,
                                                          const T* __restrict__ work,
                                                          const T* __restrict__ an,
                                                          T* __restrict__ ap, T* __restrict__ sc,
@@ -903,7 +903,7 @@ __global__ __launch_bounds__(kBlock) void k_fd_adj_local(KParams p, const double
     const T A = T(p.A), B = T(p.B), kap = T(p.kappa), M = T(p.mobility);
     const T omf = T(p.omega_f), cf = T(1) - omf;
     const T h = T(4.5), third = T(1.0 / 3.0);
-    for (XcdSweep w = xcd_sweep(p.nsites, kBlock); w.s < w.end; w.s += w.stride) {
+    for (XcdSweep w = xcd_sweep(p.nsites, NB); w.s < w.end; w.s += w.stride) {
         const int s = w.s;
         const Geo q = geo_of(p, s);
         T lf[NV];
@@ -1057,7 +1057,7 @@ __global__ __launch_bounds__(kBlock) void k_fd_adj_local(KParams p, const double
         dth[1] += dph * dph * dph * dlm + 4.5 * dtrs * 0.75 * dph * dph * dph * dph;
         dth[2] += -st.lap * dlm + 4.5 * (dtrs * (-dph * st.lap - 0.5 * g2) + double(gsg));
     }
-    block_partials<3>(dth, partials);
+    block_partials<3, NB>(dth, partials);
 }
 
 int fd_grid(const KParams& p) { return (p.nsites + kBlock - 1) / kBlock; }
@@ -1252,11 +1252,8 @@ hipError_t launch_fd_adj_step(const KParams& p, bool fp32, const void* state, do
                               const void* adj_next, void* adj_prev, void* adj_scratch,
                               double* partials, double* dtheta, hipStream_t s)
 {
-    // rho and u go to `work` in the storage type (FP32 mode: half its
-    // space); one resident round of workgroups (4 per CU), as the LB
-    // scheme's local adjoint kernel
-    constexpr int kAdjBlocks = 1024;
-    const int nb = fd_reduction_grid(p) < kAdjBlocks ? fd_reduction_grid(p) : kAdjBlocks;
+    // rho and u go to `work` in the storage type (FP32 mode: half its space)
+    const int nb = adj_blocks(p), nt = site_block(p), grid = (p.nsites + nt - 1) / nt;
     // force coupling: dL/dF through Pi (launch_adj_force_pi), whose
     // partials follow the local kernel's
     double* partials2 = p.force ? partials + 3 * kAdjBlocks : nullptr;
@@ -1269,13 +1266,13 @@ hipError_t launch_fd_adj_step(const KParams& p, bool fp32, const void* state, do
         const T* an = static_cast<const T*>(adj_next);                                        \
         T* ap = static_cast<T*>(adj_prev);                                                    \
         T* sc = static_cast<T*>(adj_scratch);                                                 \
-        if (p.force) {                                                                        \
-            k_fd_adj_prep<T, DEV, true><<<fd_grid(p), kBlock, 0, s>>>(p, a.F, a.phi, w, sc);  \
-            k_fd_adj_local<T, true><<<nb, kBlock, 0, s>>>(p, a.phi, w, an, ap, sc, partials); \
-        } else {                                                                              \
-            k_fd_adj_prep<T, DEV, false><<<fd_grid(p), kBlock, 0, s>>>(p, a.F, a.phi, w, sc); \
-            k_fd_adj_local<T, false><<<nb, kBlock, 0, s>>>(p, a.phi, w, an, ap, sc, partials);\
-        }                                                                                     \
+        auto prep = p.force ? k_fd_adj_prep<T, DEV, true> : k_fd_adj_prep<T, DEV, false>;     \
+        auto local = p.force ? (nt == 64 ? k_fd_adj_local<T, true, 64>                        \
+                                         : k_fd_adj_local<T, true, kBlock>)                   \
+                             : (nt == 64 ? k_fd_adj_local<T, false, 64>                       \
+                                         : k_fd_adj_local<T, false, kBlock>);                 \
+        prep<<<grid, nt, 0, s>>>(p, a.F, a.phi, w, sc);                                       \
+        local<<<nb, nt, 0, s>>>(p, a.phi, w, an, ap, sc, partials);                           \
     }
     LB_FD_DISPATCH(fp32, CALL);
 #undef CALL

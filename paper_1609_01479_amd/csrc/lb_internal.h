@@ -145,6 +145,18 @@ hipError_t launch_import(const KParams& p, bool fp32, void* state, const double*
                          const double* g, hipStream_t s);
 
 // Reverse mode.
+// Workgroups of the sweeping adjoint kernels: at most 1024 of site_block(p)
+// threads, each thread looping over its sites (a few resident rounds at the
+// local kernels' 1-3 waves per SIMD; a grid of exactly one round measured no
+// faster); the parameter reduction (in the stencil kernel's first workgroups)
+// then reads half the partials of 2048 workgroups (measured as a launch of its
+// own at 128^3: 9.9 -> 5.5 us, k_adj_local unchanged).
+constexpr int kAdjBlocks = 1024;
+inline int adj_blocks(const KParams& p)
+{
+    const int nt = site_block(p), g = (p.nsites + nt - 1) / nt;
+    return g < kAdjBlocks ? g : kAdjBlocks;
+}
 // adj: the level seeded (lf = lg = 0, lp = dphi); other: the second level,
 // whose lg is zeroed too when tau_g = 1 (the steps then never touch lg).
 hipError_t launch_adj_seed(const KParams& p, bool fp32, void* adj, void* other, const double* dphi,

@@ -630,18 +630,8 @@ static lb_status faces(lb_ctx* ctx, void* lo, void* hi, bool pack, const char* n
     if ((lo && !aligned(lo)) || (hi && !aligned(hi)))
         return fail(LB_EALIGN, "%s: face buffers must be 256-byte aligned", name);
     if (lo && lo == hi) return fail(LB_EINVAL, "%s: the two face buffers alias", name);
-    const int nx = ctx->p.nx;
-    void* st = ctx->b.state[ctx->cur];
-    hipError_t e = hipSuccess;
-    // packed: the face sent down (planes 0 and 1, c_x = -1) and the one sent
-    // up (planes nx-1 and nx-2, c_x = +1); unpacked: the lower neighbour's
-    // upward face into planes -1 and -2, the upper one's downward face into
-    // planes nx and nx+1
-    if (lo) e = lbk::launch_face(ctx->kp, ctx->fp32, st, lo, pack ? -1 : +1, pack ? 0 : -1, pack,
-                                 ctx->stream);
-    if (e == hipSuccess && hi)
-        e = lbk::launch_face(ctx->kp, ctx->fp32, st, hi, pack ? +1 : -1, pack ? nx - 1 : nx, pack,
-                             ctx->stream);
+    hipError_t e = lbk::launch_faces(ctx->kp, ctx->fp32, ctx->b.state[ctx->cur], lo, hi, pack,
+                                     ctx->stream);
     return e == hipSuccess ? LB_OK : hip_fail(e, name);
 }
 

@@ -396,7 +396,7 @@ hipError_t launch_force_collide(const KParams& p, const TileCfg& tc, bool fp32, 
     // still pulls g for phi)
     const bool g1 = p.omega_g == 1.0;
     const int nb = site_block(p);  // of variant 1's kernel
-    const bool nt = nt_stores(p, 2 * NV, fp32 ? 4 : 8, 192);
+    const bool nt = nt_stores(p, 2 * NV, fp32 ? 4 : 8, 144);
     if (fp32) {
         Lvl<float> a = level<float>(const_cast<void*>(src), p, true);
         Lvl<float> d = level<float>(dst, p, true);

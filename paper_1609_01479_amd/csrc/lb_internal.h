@@ -226,14 +226,14 @@ hipError_t launch_fd_export(const KParams& p, bool fp32, const void* state, doub
 hipError_t launch_fd_import(const KParams& p, bool fp32, void* state, const double* f,
                             hipStream_t s);
 
-// x-slab shards (lb_halo.hip): bytes of one face buffer, and the copy of a
-// face between `buf` and the level `state` -- pack: boundary plane xb and
-// the plane behind it (xb - s) into buf; unpack: buf into the halo planes
-// xb and xb - s.  s = +1: the face sent up (c_x = +1 populations), s = -1:
-// the face sent down.
+// x-slab shards (lb_halo.hip): bytes of one face buffer, and the copy of the
+// faces between the buffers `lo` and `hi` (either may be null) and the level
+// `state` -- pack: the boundary planes and the planes behind them into the
+// buffers for the lower and the upper neighbour; unpack: theirs into the halo
+// planes.
 size_t face_bytes(const KParams& p, bool fp32);
-hipError_t launch_face(const KParams& p, bool fp32, void* state, void* buf, int s, int xb,
-                       bool pack, hipStream_t st);
+hipError_t launch_faces(const KParams& p, bool fp32, void* state, void* lo, void* hi, bool pack,
+                        hipStream_t st);
 
 // Upper bounds on the block partials (per component) of a moments or adjoint
 // reduction, and of an LB step that reduces in its two-pass collision.

@@ -161,7 +161,8 @@ __device__ __forceinline__ T ldc(const T* __restrict__ base, OffT<SMALL> pl, int
 // for the next step, and the pieces that two components or two tiles share
 // would go to memory in parts, where plain stores let L2 join them (us per
 // step, NT / plain: FP32 151 x 105 x 150, rows of 600 bytes, 228 / 189,
-// 90 x 75 x 100 64 / 47, 96^3 64 / 60, 128^3 131 / 136, 256^3 944 / 983).
+// 90 x 75 x 100 64 / 47, 96^3 64 / 60, 128^3 131 / 136, 256^3 944 / 983; FP64
+// 32 x 128 x 128 68 / 71).
 template <bool SMALL, bool NT, typename T>
 __device__ __forceinline__ void stc(T* __restrict__ base, OffT<SMALL> pl, int i, unsigned compb,
                                     unsigned row, T v)
@@ -607,7 +608,7 @@ hipError_t launch_step_t(const KParams& p, const TileCfg& tc, int variant, const
         k<<<(p.nsites + nb - 1) / nb, nb, 0, s>>>(p, a.F, a.G, a.phic, phi64, d.F, d.G, partials);
     } else {
         const bool small = size_t(NV) * p.stride * sizeof(T) < (size_t(1) << 32);
-        auto k = Fused<T>::get(small, tc.tz, variant == 0, g1, nt_stores(p, 2 * NV, sizeof(T), 192));
+        auto k = Fused<T>::get(small, tc.tz, variant == 0, g1, nt_stores(p, 2 * NV, sizeof(T), 144));
         k<<<tc.ntiles * tc.nseg, kFused, 0, s>>>(p, tc, a.F, a.G, a.phic, d.F, d.G, d.phic,
                                                  phi_src_out, partials);
     }

@@ -126,3 +126,30 @@ def test_other_schemes_forms_agree_bit_for_bit(shape, seg, prec, coupling, order
         assert torch.equal(a, b)
     n = float(np.prod(shape))
     assert np.abs(sums[0] - sums[1]).max() <= n * n * 2.3e-16
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32_dev"])
+@pytest.mark.parametrize("yz", [(1, 1), (5, 9), (128, 128), (129, 128)])
+def test_faces_packed_together_and_one_at_a_time_agree(yz, prec):
+    """Faces below and beyond the size that deals slots to more threads; either
+    buffer may be missing, and then its side is left alone."""
+    shape = (4,) + yz
+    print(f"[faces] {shape} {prec}", flush=True)
+    phi0 = lbinputs.spinodal_phi0((shape[0] + 2,) + yz, seed=5, amp=0.3)
+    lb = make_lb(shape, precision=prec, halo_x=True)
+    lb.init_phi(phi0)
+    lb.step(1)
+    both = [lb.new_face().zero_(), lb.new_face().zero_()]
+    single = [lb.new_face().zero_(), lb.new_face().zero_()]
+    lb.pack_faces(*both)
+    lb.pack_faces(single[0], None)
+    lb.pack_faces(None, single[1])
+    assert torch.equal(both[0], single[0]) and torch.equal(both[1], single[1])
+    assert both[0].any() and both[1].any()
+    start = lb.get_state()
+    lb.unpack_faces(both[1], both[0])
+    want = lb.get_state()
+    lb.set_state(start)
+    lb.unpack_faces(both[1], None)
+    lb.unpack_faces(None, both[0])
+    assert torch.equal(lb.get_state(), want)

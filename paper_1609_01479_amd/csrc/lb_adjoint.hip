@@ -27,7 +27,8 @@
 // An adjoint level stores 39 components of `stride` elements:
 //   lf[19] = dL/df_i(x), lg[19] = the part of dL/dg_i(x) specific to i,
 //   lp = dL/dphi(x), so that dL/dg_i(x) = lg_i(x) + lp(x).
-// adj_scratch holds a (direct dPhi/dphi), b_x, b_y, b_z, c per site.
+// adj_scratch holds a (direct dPhi/dphi), b_x, b_y, b_z, c per site (with the
+// force coupling b comes from k_adj_force_pi alone).
 //
 // With omega_g = 1 (tau_g = 1) the post-collision g is g^eq alone, so the
 // previous level's lg = (1 - omega_g) lambda*_g is identically zero: the seed
@@ -357,9 +358,6 @@ __device__ __forceinline__ void adj_local_force_body(const KParams& p, const T* 
         const AR phi2 = phi_c * phi_c;
         const AR a_dir = t0 + AR(3) * t1u + h * (gam * (A + AR(3) * B * phi2) - third) * trt + h * t2uu;
         sc[0 * S + s] = T(a_dir);
-        sc[1 * S + s] = T(0);
-        sc[2 * S + s] = T(0);
-        sc[3 * S + s] = T(0);
         sc[4 * S + s] = T(-h * kap * gam * trt);
         sc[5 * S + s] = T(lFx);
         sc[6 * S + s] = T(lFy);
@@ -416,7 +414,10 @@ __global__ __launch_bounds__(kBlock) void k_adj_force_f(KParams p, const double*
 //   a += trL (A phi + 3B phi^3 - kappa lap),  b += kappa (2 L grad - trL grad),
 //   c += -kappa phi trL,
 // and d/d(A, B, kappa) += trL (phi^2/2, 3 phi^4/4, -phi lap - |grad|^2/2)
-// + (0, 0, grad.L.grad).  Each site updates only its own cotangents.
+// + (0, 0, grad.L.grad).  Each site updates only its own cotangents: a and c
+// add to the local kernel's, b (which no other term of the force coupling
+// feeds) is written here only -- zeros written by the local kernel and read
+// back here were 24 of the FP32 reverse step's 356 bytes per site.
 template <typename T, int NB>
 __global__ __launch_bounds__(NB) void k_adj_force_pi(KParams p, const double* __restrict__ phi,
                                                          T* __restrict__ sc,
@@ -450,9 +451,9 @@ __global__ __launch_bounds__(NB) void k_adj_force_pi(KParams p, const double* __
         const T Lgz = Lxz * gx + Lyz * gy + Lzz * gz;
         const T ph2 = ph * ph;
         sc[0 * S + s] += trL * (A * ph + T(3) * B * ph2 * ph - kap * lap);
-        sc[1 * S + s] += kap * (T(2) * Lgx - trL * gx);
-        sc[2 * S + s] += kap * (T(2) * Lgy - trL * gy);
-        sc[3 * S + s] += kap * (T(2) * Lgz - trL * gz);
+        sc[1 * S + s] = kap * (T(2) * Lgx - trL * gx);
+        sc[2 * S + s] = kap * (T(2) * Lgy - trL * gy);
+        sc[3 * S + s] = kap * (T(2) * Lgz - trL * gz);
         sc[4 * S + s] += -kap * ph * trL;
         const double dtr = double(trL), dph = st.phi;
         const double g2 = st.gx * st.gx + st.gy * st.gy + st.gz * st.gz;

@@ -887,7 +887,7 @@ __global__ __launch_bounds__(kBlock) void k_fd_adj_prep(KParams p, const T* __re
 // FORCE: u = (j + F/2)/rho and the forcing collision of f (Pi is not in
 // f^eq): the flux's lambda_u joins the collision's, the total goes to j,
 // rho and F as in the LB scheme's force adjoint (lb_adjoint.hip), and dL/dF
-// is written after the five cotangents for k_adj_force_pi.
+// is written after the cotangents for k_adj_force_pi, which forms b.
 template <typename T, bool FORCE, int NB>
 __global__ __launch_bounds__(NB) void k_fd_adj_local(KParams p, const double* __restrict__ phi,
                                                          const T* __restrict__ work,
@@ -989,9 +989,6 @@ __global__ __launch_bounds__(NB) void k_fd_adj_local(KParams p, const double* __
             }
             const T phc = T(pc);
             sc[0 * S + s] = lc + (A + T(3) * B * phc * phc) * lmu + adv;
-            sc[1 * S + s] = T(0);
-            sc[2 * S + s] = T(0);
-            sc[3 * S + s] = T(0);
             sc[4 * S + s] = -kap * lmu;
             sc[5 * S + s] = pref * (T(3) * m1x - T(3) * ux * m0 + T(9) * m2ux) + hr * lux;
             sc[6 * S + s] = pref * (T(3) * m1y - T(3) * uy * m0 + T(9) * m2uy) + hr * luy;

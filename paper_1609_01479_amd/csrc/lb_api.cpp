@@ -463,10 +463,9 @@ lb_status lb_level_phi(lb_ctx* ctx, const void* level_dev, double* phi_dev)
     return e == hipSuccess ? LB_OK : hip_fail(e, "lb_level_phi");
 }
 
-// Moments of the current level, and block partials of its sums in scratch.
-static hipError_t moments(lb_ctx* ctx, double* rho, double* u, double* phi, int* nb)
+// Moments of the current level, and with part block partials of its sums.
+static hipError_t moments(lb_ctx* ctx, double* rho, double* u, double* phi, double* part, int* nb)
 {
-    double* part = static_cast<double*>(ctx->b.scratch);
     if (ctx->kp.fd)
         return lbk::launch_fd_moments(ctx->kp, ctx->fp32, ctx->b.state[ctx->cur], rho, u, phi, part,
                                       nb, ctx->stream);
@@ -477,8 +476,9 @@ static hipError_t moments(lb_ctx* ctx, double* rho, double* u, double* phi, int*
 lb_status lb_moments(lb_ctx* ctx, double* rho_dev, double* u_dev, double* phi_dev)
 {
     if (!ctx) return fail(LB_EINVAL, "ctx is NULL");
+    if (!rho_dev && !u_dev && !phi_dev) return LB_OK;
     int nb = 0;
-    hipError_t e = moments(ctx, rho_dev, u_dev, phi_dev, &nb);
+    hipError_t e = moments(ctx, rho_dev, u_dev, phi_dev, nullptr, &nb);
     return e == hipSuccess ? LB_OK : hip_fail(e, "lb_moments");
 }
 
@@ -487,7 +487,7 @@ lb_status lb_sums(lb_ctx* ctx, double* out5_dev)
     if (!ctx || !out5_dev) return fail(LB_EINVAL, "ctx and out5_dev are required");
     int nb = 0;
     double* part = static_cast<double*>(ctx->b.scratch);
-    hipError_t e = moments(ctx, nullptr, nullptr, nullptr, &nb);
+    hipError_t e = moments(ctx, nullptr, nullptr, nullptr, part, &nb);
     if (e != hipSuccess) return hip_fail(e, "lb_sums (partials)");
     e = lbk::launch_sums_final(part, nb, 5, 1, out5_dev, ctx->stream);
     return e == hipSuccess ? LB_OK : hip_fail(e, "lb_sums (final)");

@@ -130,6 +130,8 @@ hipError_t launch_force_collide(const KParams& p, const TileCfg& tc, bool fp32, 
 int force_sums_blocks(const KParams& p, int seg_req);
 // phi(x) of the post-propagation state held in `state`.
 hipError_t launch_phi(const KParams& p, bool fp32, const void* state, double* phi, hipStream_t s);
+// Moments of the level (outputs may be null) and, if partials is not null, the
+// block partials of its sums, *nblocks_out (at most kMaxPartialBlocks) of 5.
 // work: the FP64 phi field the force coupling needs (`stride` long); unused
 // otherwise.
 hipError_t launch_moments(const KParams& p, bool fp32, const void* state, double* rho, double* u,

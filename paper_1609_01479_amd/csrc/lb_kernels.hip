@@ -6,6 +6,7 @@
 // lb_force.hip (the force coupling) and lb_fd.hip (the finite-difference
 // order parameter).
 #include "lb_device.h"
+#include "lb_sweep.h"
 
 namespace lbk {
 
@@ -40,28 +41,36 @@ __global__ __launch_bounds__(kBlock) void k_init(KParams p, T* __restrict__ F, T
     if (REF) phic[phic_site(p, q.x, q.y, q.z)] = phic_word(ph[s]);
 }
 
-// Dense FP64 moments of the post-propagation state and block partials of
-// [rho, phi, jx, jy, jz] (grid-stride, FP64 accumulation).
-// With fphi (force coupling: phi of this state, all sites) the velocity is
-// (j + F/2)/rho, F = -div Pi of this state, and the momentum sums are those
-// of j + F/2.
-template <typename T, bool DEV, bool REF>
-__global__ __launch_bounds__(kBlock) void k_moments(KParams p, const T* __restrict__ F,
-                                                    const T* __restrict__ G,
-                                                    const unsigned* __restrict__ phic,
-                                                    const double* __restrict__ fphi,
-                                                    double* __restrict__ rho_out,
-                                                    double* __restrict__ u_out,
-                                                    double* __restrict__ phi_out,
-                                                    double* __restrict__ partials)
+// Dense FP64 moments of the post-propagation state and, if partials is not
+// null, block partials of [rho, phi, jx, jy, jz] (FP64 accumulation; the
+// sites of each XCD a contiguous eighth, so the rows and planes that its
+// pulls share are in its L2).
+// With fphi (force coupling: phi of this state, all sites) phi comes from
+// there, without a second pull of g, the velocity is (j + F/2)/rho,
+// F = -div Pi of this state, and the momentum sums are those of j + F/2.
+// Bound by memory: one read of the level, one write of what is asked for.
+// Without partials no block reduces them, and the grid is not cut to their
+// number; phi alone reads g alone (launch_moments).  Force coupling at 192^3
+// FP64: rho, u and phi 732 -> 505 us, the sums 632 -> 463, phi 712 -> 209;
+// stress 470 -> 475 (5.1 TB/s), 361 -> 359, 386 -> 207.
+template <typename T, bool DEV, bool REF, int NB>
+__global__ __launch_bounds__(NB) void k_moments(KParams p, const T* __restrict__ F,
+                                                const T* __restrict__ G,
+                                                const unsigned* __restrict__ phic,
+                                                const double* __restrict__ fphi,
+                                                double* __restrict__ rho_out,
+                                                double* __restrict__ u_out,
+                                                double* __restrict__ phi_out,
+                                                double* __restrict__ partials)
 {
     double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int s = xcd_block() * kBlock + threadIdx.x; s < p.nsites; s += gridDim.x * kBlock) {
+    for (XcdSweep w = xcd_sweep(p.nsites, NB); w.s < w.end; w.s += w.stride) {
+        const int s = w.s;
         const Geo q = geo_of(p, s);
         double fv[NV];
 #pragma unroll
         for (int i = 0; i < NV; i++) fv[i] = double(F[dist_pull(p, q, i)]);
-        const double ph = phi_at<T, REF>(p, q, G, phic);
+        const double ph = fphi ? fphi[s] : phi_at<T, REF>(p, q, G, phic);
         double b = 0.0;
 #pragma unroll
         for (int i = 0; i < NV; i++) b += fv[i];
@@ -93,7 +102,7 @@ __global__ __launch_bounds__(kBlock) void k_moments(KParams p, const T* __restri
         acc[3] += jy;
         acc[4] += jz;
     }
-    block_partials<5>(acc, partials);
+    if (partials) block_partials<5, NB>(acc, partials);
 }
 
 // Workgroup (k, b): out[b*ncomp + k] = the sum over nblocks partials of
@@ -165,10 +174,22 @@ __global__ __launch_bounds__(kBlock) void k_import(KParams p, T* __restrict__ F,
 
 int grid_for(const KParams& p) { return (p.nsites + kBlock - 1) / kBlock; }
 
-int reduction_grid(const KParams& p)
+// workgroups of a moments pass, with sums at most kMaxPartialBlocks
+int moments_grid(const KParams& p, bool sums)
 {
-    const int g = grid_for(p);
-    return g < kMaxPartialBlocks ? g : kMaxPartialBlocks;
+    const int g = (p.nsites + site_block(p) - 1) / site_block(p);
+    return sums && g > kMaxPartialBlocks ? kMaxPartialBlocks : g;
+}
+
+template <typename T>
+void moments(const KParams& p, int nb, const void* state, const double* fphi, double* rho,
+             double* u, double* phi, double* partials, hipStream_t s)
+{
+    constexpr bool F32 = sizeof(T) == 4;
+    Lvl<T> a = level<T>(const_cast<void*>(state), p, F32);
+    const int nt = site_block(p);
+    auto k = nt == 64 ? k_moments<T, F32, F32, 64> : k_moments<T, F32, F32, kBlock>;
+    k<<<nb, nt, 0, s>>>(p, a.F, a.G, a.phic, fphi, rho, u, phi, partials);
 }
 
 // The two-pass step's collision kernel reduces the sums itself, one block of
@@ -347,7 +368,7 @@ int step_variant(const KParams& p, const TileCfg& tc, bool fp32, int variant, bo
 int step_sums_blocks(const KParams& p, const TileCfg& tc, bool fp32, int variant)
 {
     variant = step_variant(p, tc, fp32, variant, true);
-    if (variant == 1) return collide_sums(p) ? collide_grid(p) : reduction_grid(p);
+    if (variant == 1) return collide_sums(p) ? collide_grid(p) : moments_grid(p, true);
     if (p.force) return force_sums_blocks(p, tc.seg_req);
     return tc.ntiles * tc.nseg;
 }
@@ -379,16 +400,9 @@ hipError_t launch_step(const KParams& p, const TileCfg& tc, bool fp32, int varia
         if (e != hipSuccess) return e;
         if (partials && !collide_sums(p)) {
             // more blocks than the partials may be: a moments pass of its own
-            const int nb = reduction_grid(p);
-            const double* fphi = p.force ? phi64 : nullptr;
-#define CALL                                                                                 \
-    {                                                                                        \
-        Lvl<T> a = level<T>(const_cast<void*>(src), p, REF);                                 \
-        k_moments<T, DEV, REF><<<nb, kBlock, 0, s>>>(p, a.F, a.G, a.phic, fphi, nullptr,     \
-                                                     nullptr, nullptr, partials);            \
-    }
-            LB_DISPATCH(fp32, CALL, CALL);
-#undef CALL
+            auto m = fp32 ? moments<float> : moments<double>;
+            m(p, moments_grid(p, true), src, p.force ? phi64 : nullptr, nullptr, nullptr, nullptr,
+              partials, s);
             partials = nullptr;
         }
     }
@@ -408,23 +422,19 @@ hipError_t launch_moments(const KParams& p, bool fp32, const void* state, double
                           double* phi, double* work, double* partials, int* nblocks_out,
                           hipStream_t s)
 {
-    const int nb = reduction_grid(p);
+    // phi alone: its own pass
+    if (phi && !rho && !u && !partials) return launch_phi(p, fp32, state, phi, s);
+    const int nb = moments_grid(p, partials != nullptr);
     *nblocks_out = nb;
     double* fphi = nullptr;
     if (p.force && (u || partials)) {
-        // F of this state: phi into the work field first
-        fphi = work;
-        hipError_t e = launch_phi(p, fp32, state, work, s);
+        // F of this state: phi into its output or the work field first
+        fphi = phi ? phi : work;
+        hipError_t e = launch_phi(p, fp32, state, fphi, s);
         if (e != hipSuccess) return e;
     }
-#define CALL                                                                                  \
-    {                                                                                         \
-        Lvl<T> a = level<T>(const_cast<void*>(state), p, REF);                                \
-        k_moments<T, DEV, REF><<<nb, kBlock, 0, s>>>(p, a.F, a.G, a.phic, fphi, rho, u, phi, \
-                                                     partials);                               \
-    }
-    LB_DISPATCH(fp32, CALL, CALL);
-#undef CALL
+    auto m = fp32 ? moments<float> : moments<double>;
+    m(p, nb, state, fphi, rho, u, fphi == phi ? nullptr : phi, partials, s);
     return hipGetLastError();
 }
 

@@ -153,3 +153,30 @@ def test_faces_packed_together_and_one_at_a_time_agree(yz, prec):
     lb.unpack_faces(both[1], None)
     lb.unpack_faces(None, both[0])
     assert torch.equal(lb.get_state(), want)
+
+
+@pytest.mark.parametrize("order_param", ["lb", "fd"])
+@pytest.mark.parametrize("coupling", ["stress", "force"])
+@pytest.mark.parametrize("prec", ["fp64", "fp32_dev"])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (3, 2, 7), (32, 32, 64), (41, 40, 40), (65, 64, 64)])
+def test_moments_alone_and_together_agree(shape, prec, coupling, order_param):
+    """lb_moments of any subset of its outputs gives the same values, phi alone
+    included (a pass of its own), and lb_sums is their sum: blocks of one wave
+    and of four, and more blocks than the sums' partials."""
+    print(f"[moments] {shape} {prec} {coupling} {order_param}", flush=True)
+    lb = make_lb(shape, precision=prec, tau_f=0.8, coupling=coupling, order_param=order_param)
+    lb.init_phi(lbinputs.spinodal_phi0(shape, seed=17, amp=0.3))
+    lb.step(3)
+    rho, u, phi = lb.moments()
+    for want in ((1, 0, 0), (0, 1, 0), (0, 0, 1), (1, 1, 0), (0, 1, 1), (1, 0, 1)):
+        got = [torch.full_like(v, 7.0) for v in (rho, u, phi)]
+        lb._call("lb_moments", *(v.data_ptr() if w else None for v, w in zip(got, want)))
+        for v, g, w in zip((rho, u, phi), got, want):
+            assert torch.equal(g, v if w else torch.full_like(v, 7.0))
+    s = lb.sums()
+    ref = torch.stack([rho.sum(), phi.sum(), *((rho * u[k]).sum() for k in range(3))])
+    # two orders of n FP64 terms: 2 n eps of the sum of their sizes, and one
+    # rounding each for the division by rho and the product with it
+    n = float(np.prod(shape))
+    size = torch.stack([rho.sum(), phi.abs().sum(), *((rho * u[k]).abs().sum() for k in range(3))])
+    assert bool(((s - ref).abs() <= (2.0 * n + 4.0) * 2.3e-16 * size).all())

@@ -312,14 +312,14 @@ lb_status lb_init_phi(lb_ctx* ctx, const double* phi0_dev)
 // One step from src to dst with the context's scheme; partials (may be null)
 // takes the block partials of src's conserved sums.
 static hipError_t one_step(lb_ctx* ctx, const void* src, void* dst, double* partials,
-                           double* phi_src_out = nullptr)
+                           double* phi_src_out = nullptr, int compact = 0)
 {
     double* work = static_cast<double*>(ctx->b.phi);
     if (ctx->kp.fd)
         return lbk::launch_fd_step(ctx->kp, ctx->tc, ctx->fp32, ctx->p.kernel, src, dst, work,
                                    partials, ctx->stream);
     return lbk::launch_step(ctx->kp, ctx->tc, ctx->fp32, ctx->p.kernel, src, dst, work, partials,
-                            phi_src_out, ctx->stream);
+                            phi_src_out, ctx->stream, compact);
 }
 
 // The partial blocks this context's steps reduce over.
@@ -351,12 +351,17 @@ static lb_status step_n(lb_ctx* ctx, int32_t nsteps, double* sums_dev, const cha
     if (ctx->kp.xh && nsteps > 1)
         return fail(LB_EINVAL, "an x-slab shard advances one step per call (its halo planes "
                                "are exchanged between steps); got nsteps = %d", nsteps);
-    const size_t nb = sums_dev ? sums_blocks(ctx) : 0;
+    // the levels between this call's steps can be compact
+    const bool between = nsteps > 1 && lbk::can_compact(ctx->kp, ctx->tc, ctx->fp32, ctx->p.kernel);
+    const size_t nb = !sums_dev ? 0 : between ? lbk::collide_grid(ctx->kp, true) : sums_blocks(ctx);
     const int32_t batch = sums_dev ? int32_t(std::min<size_t>(rows / nb, 4096)) : 1;
     int32_t held = 0;  // steps whose partials wait in part
     for (int32_t t = 0; t < nsteps; t++) {
+        const int compact = !between ? 0
+                                     : (t > 0 ? lbk::kCompactSrc : 0) |
+                                           (t + 1 < nsteps ? lbk::kCompactDst : 0);
         hipError_t e = one_step(ctx, ctx->b.state[ctx->cur], ctx->b.state[1 - ctx->cur],
-                                sums_dev ? part + size_t(held) * 5 * nb : nullptr);
+                                sums_dev ? part + size_t(held) * 5 * nb : nullptr, nullptr, compact);
         if (e != hipSuccess) return hip_fail(e, name);
         ctx->cur = 1 - ctx->cur;
         if (!sums_dev) continue;

@@ -1,0 +1,299 @@
+// Compact levels between the steps of one call, for omega_g = 1 (tau_g = 1).
+//
+// There g* = g^eq, a function of phi, mu and u of the site that collided: a
+// step that is followed by another in the same call leaves these five numbers
+// instead of the 19 populations, in the place of the level's g region (phi:
+// stride FP64 values, then mu, u_x, u_y, u_z of each site together), and the
+// next step's phi pass forms each population it pulls from its origin's five,
+// by the expressions that collide_g and collide_force_g store it with, so
+// every phi and every f is bit for bit that of full levels.  f stays as it is.
+// The levels that a call starts from and leaves are full.  Per site and step
+// that is 392 bytes instead of 608 in FP64 (and 208 of 312 in FP32 storage
+// with the force coupling): two passes, the first over five fields.  us per
+// step, full / compact: FP64 stress 90 x 75 x 100 86 / 49, 128^3 248 / 162,
+// 256^3 1830 / 1309; FP64 force 274 / 188 and 2083 / 1471, FP32 force 161 /
+// 126 and 1153 / 984.
+#pragma once
+
+#include "lb_device.h"
+
+namespace lbk {
+
+using namespace dev;
+
+template <typename T>
+struct alignas(4 * sizeof(T) < 16 ? 4 * sizeof(T) : 16) MuU {
+    T mu, ux, uy, uz;
+};
+
+template <typename T>
+__host__ __device__ inline double* compact_phi(T* G) { return reinterpret_cast<double*>(G); }
+template <typename T>
+__host__ __device__ inline MuU<T>* compact_mu_u(T* G, const KParams& p)
+{
+    return reinterpret_cast<MuU<T>*>(compact_phi(G) + p.stride);
+}
+
+namespace {
+
+// g*_i of a site (FP32 mode: its deviation h*) as collide_g<T, REF, true>
+// forms it (the same expressions, so that each rounds alike).
+template <typename T, bool REF>
+__device__ __forceinline__ T geq_stress(const KParams& p, int i, T phi, MuU<T> m)
+{
+    const T gam = T(p.gamma), mu = m.mu;
+    const T ux = m.ux, uy = m.uy, uz = m.uz;
+    const T h = T(4.5);
+    const T w0 = T(weight(0)), wf = T(weight(1)), we = T(weight(7));
+    const T wf3 = T(3.0 * weight(1)), we3 = T(3.0 * weight(7));
+    const T uu3 = (ux * ux + uy * uy + uz * uz) * T(1.0 / 3.0);
+    const T hp = h * phi;
+    static_assert(!REF, "FP32 storage adds g - g to g^eq in the stress coupling");
+    const T sg = gam * mu - phi * T(1.0 / 3.0);
+    if (i == 0) return w0 * (phi - h * sg - hp * uu3);
+    const int odd = i & 1;
+    if (i < 7) {
+        const T ef = phi - hp * uu3;
+        const T p3f = wf3 * phi;
+        const T v = i < 3 ? ux : (i < 5 ? uy : uz);
+        const T sx = wf * (ef + hp * v * v);
+        return odd ? sx + p3f * v : sx - p3f * v;
+    }
+    const T ee = phi + h * sg - hp * uu3;
+    const T p3e = we3 * phi;
+    const T c = i < 9 ? ux + uy : i < 11 ? ux - uy : i < 13 ? ux + uz : i < 15 ? ux - uz
+              : i < 17 ? uy + uz : uy - uz;
+    const T s = we * (ee + hp * c * c);
+    return odd ? s + p3e * c : s - p3e * c;
+}
+
+// The same as collide_force_g<T, REF, true>.
+template <typename T, bool REF>
+__device__ __forceinline__ T geq_force(const KParams& p, int i, T phi, MuU<T> m)
+{
+    const T mu = m.mu, ux = m.ux, uy = m.uy, uz = m.uz;
+    const T uu3 = (ux * ux + uy * uy + uz * uz) * T(1.0 / 3.0);
+    const T gm = T(p.gamma) * mu, sg = REF ? gm : gm - phi * T(1.0 / 3.0);
+    const T w = T(weight(i));
+    const T cu = T(CX[i]) * ux + T(CY[i]) * uy + T(CZ[i]) * uz;
+    const T q = cu * cu - uu3;
+    const T c2m1 = T(CX[i] * CX[i] + CY[i] * CY[i] + CZ[i] * CZ[i] - 1);
+    return w * ((REF ? T(0) : phi) + T(3) * phi * cu + T(4.5) * (sg * c2m1 + phi * q));
+}
+
+// phi of a compact level at every site (phi_at of the full one); with dphic
+// (FP32 mode) also the reference field phi_c of the level the step makes.
+template <typename T, bool REF, bool FORCE>
+__global__ __launch_bounds__(kBlock) void k_phi_compact(KParams p, const double* __restrict__ cphi,
+                                                        const MuU<T>* __restrict__ mu_u,
+                                                        double* __restrict__ phi,
+                                                        unsigned* __restrict__ dphic)
+{
+    const int s = xcd_block() * int(blockDim.x) + threadIdx.x;
+    if (s >= p.nsites) return;
+    const Geo q = geo_of(p, s);
+    const double pc = REF ? phic_round(cphi[s]) : 0.0;
+    double acc = 0.0;
+#pragma unroll
+    for (int i = 0; i < NV; i++) {
+        const int y = pull_site(p, q, i);
+        const double ph = cphi[y];
+        const MuU<T> m = mu_u[y];
+        T g;
+        if constexpr (FORCE)
+            g = geq_force<T, REF>(p, i, T(ph), m);
+        else
+            g = geq_stress<T, REF>(p, i, T(ph), m);
+        acc += double(REF ? T(__builtin_fma(rweight(i), ph - pc, double(g))) : g);
+    }
+    const double v = REF ? pc + acc : acc;
+    phi[s] = v;
+    if (REF && dphic) dphic[phic_site(p, q.x, q.y, q.z)] = phic_word(v);
+}
+
+// LDS of a cell: the 16 populations that leave its column (FP32 mode: their
+// deviations, and the phi of the cell).
+template <typename T, bool REF, int NC>
+struct CompactLds {
+    T g[NV - 3][NC];
+    double phi[REF ? NC : 1];
+};
+
+// A pulled population: FP64 its value, FP32 mode its deviation and the phi of
+// its origin, until the reference of the site it arrives at is known.
+template <typename T, bool REF>
+struct Pulled {
+    T h;
+    double ph;
+    __device__ __forceinline__ double at(int i, double pc) const
+    {
+        return REF ? double(T(__builtin_fma(rweight(i), ph - pc, double(h)))) : double(h);
+    }
+};
+
+// k_phi_compact as a march along x.  One site per thread reads five values
+// from each of 19 sites, 760 bytes in FP64, and is bound by the caches that
+// serve them (256^3 620 us, for 48 bytes per site from memory).  Here a
+// workgroup owns a tile of TY x TZ columns over a segment of planes, one
+// thread per cell of the tile and the ring around it.  Each cell's populations
+// are formed once and handed to their destinations through LDS; those that
+// leave for the planes on either side wait in the destination's registers.
+// Bound by its arithmetic and LDS traffic together, with 8 waves between two
+// barriers: 256^3 239 us.
+template <typename T, bool REF, bool FORCE, int TY, int TZ>
+__global__ __launch_bounds__(((TY + 2) * (TZ + 2) + 63) / 64 * 64) void k_phi_compact_march(
+    KParams p, int nty, int ntz, int sx, const double* __restrict__ cphi,
+    const MuU<T>* __restrict__ mu_u, double* __restrict__ phi, unsigned* __restrict__ dphic)
+{
+    constexpr int BZ = TZ + 2, NC = (TY + 2) * BZ;
+    __shared__ CompactLds<T, REF, NC> lds;
+    const int blk = xcd_block();
+    const int tile = blk % (nty * ntz), seg = blk / (nty * ntz);
+    // the last tiles of a plane are shifted back to end with it
+    const int ey = p.ny < TY ? p.ny : TY, ez = p.nz < TZ ? p.nz : TZ;
+    const int y0 = min(tile / ntz * TY, p.ny - ey), z0 = min(tile % ntz * TZ, p.nz - ez);
+    const int x0 = seg * sx, x1 = min(x0 + sx, p.nx);
+    const int c = threadIdx.x, r = c / BZ, l = c - r * BZ;
+    const bool cell = c < NC;
+    const bool own = cell && r >= 1 && r <= ey && l >= 1 && l <= ez;
+    const int y = wrap_any(y0 + r - 1, p.ny), z = wrap_any(z0 + l - 1, p.nz);
+    const int col = y * p.nz + z, plane = p.ny * p.nz;
+    double ph = 0.0, below = 0.0;  // phi of this plane's cell and of the one before
+    MuU<T> m{};
+    {
+        const int s = (x0 == 0 ? p.nx - 1 : x0 - 1) * plane + col;
+        if (cell) {
+            ph = cphi[s];
+            m = mu_u[s];
+        }
+    }
+    Pulled<T, REF> up[2][5], mid[9];
+    constexpr int UP[5] = {1, 7, 9, 11, 13};
+    constexpr int MID[9] = {0, 3, 4, 5, 6, 15, 16, 17, 18};
+    for (int X = x0 - 1; X <= x1; X++) {
+        T g[NV];
+        const double here = ph;
+        if constexpr (FORCE)
+            collide_force_g<T, REF, true>(p, g, ph, double(m.mu), Vel<T>{m.ux, m.uy, m.uz});
+        else
+            collide_g<T, REF, true>(p, g, T(ph), m.mu, Vel<T>{m.ux, m.uy, m.uz});
+        if (cell) {
+#pragma unroll
+            for (int i = 3; i < NV; i++) lds.g[i - 3][c] = g[i];
+            if (REF) lds.phi[c] = here;
+        }
+        if (cell && X < x1) {  // the next plane, while this one is exchanged
+            const int s = (X + 1 >= p.nx ? X + 1 - p.nx : X + 1) * plane + col;
+            ph = cphi[s];
+            m = mu_u[s];
+        }
+        lds_barrier();
+        if (own) {
+            auto pull = [&](int i) {
+                const int o = c - (CY[i] * BZ + CZ[i]);
+                return Pulled<T, REF>{lds.g[i - 3][o], REF ? lds.phi[o] : 0.0};
+            };
+            Pulled<T, REF> down[5];
+            down[0] = Pulled<T, REF>{g[2], here};
+#pragma unroll
+            for (int k = 1; k < 5; k++) down[k] = pull(UP[k] + 1);
+            if (X > x0) {
+                const double pc = REF ? phic_round(below) : 0.0;
+                double acc = 0.0;
+                acc += mid[0].at(0, pc);
+                acc += up[0][0].at(1, pc);
+                acc += down[0].at(2, pc);
+#pragma unroll
+                for (int k = 1; k < 5; k++) acc += mid[k].at(MID[k], pc);
+#pragma unroll
+                for (int k = 1; k < 5; k++) {
+                    acc += up[0][k].at(UP[k], pc);
+                    acc += down[k].at(UP[k] + 1, pc);
+                }
+#pragma unroll
+                for (int k = 5; k < 9; k++) acc += mid[k].at(MID[k], pc);
+                const double v = REF ? pc + acc : acc;
+                const int s = (X - 1) * plane + col;
+                phi[s] = v;
+                if (REF && dphic) dphic[phic_site(p, X - 1, y, z)] = phic_word(v);
+            }
+            mid[0] = Pulled<T, REF>{g[0], here};
+#pragma unroll
+            for (int k = 1; k < 9; k++) mid[k] = pull(MID[k]);
+#pragma unroll
+            for (int k = 0; k < 5; k++) {
+                up[0][k] = up[1][k];
+                up[1][k] = k ? pull(UP[k]) : Pulled<T, REF>{g[1], here};
+            }
+            below = here;
+        }
+        lds_barrier();
+    }
+}
+
+// Planes per segment of the march: the least work per resident workgroup.
+inline int compact_segment(const KParams& p, int ntiles, int resident)
+{
+    int best = p.nx;
+    long long cost = -1;
+    for (int nseg = 1; nseg <= p.nx && nseg <= 2 * resident; nseg++) {
+        const int sx = (p.nx + nseg - 1) / nseg;
+        const long long n = (long long)ntiles * ((p.nx + sx - 1) / sx);
+        const long long c = (n + resident - 1) / resident * (sx + 2);
+        if (cost < 0 || c < cost) {
+            cost = c;
+            best = sx;
+        }
+    }
+    return best;
+}
+
+// The march's tile: 12 x 32 sites and their ring are 8 waves of cells, two
+// workgroups of which fill a CU's LDS in FP64 (us per step of 256^3 FP64, the
+// collision's 1073 included: 8 x 64 1312, 8 x 48 1310, 4 x 64 1323, 16 x 32
+// 1335, 12 x 32 1312; of 151 x 105 x 150 207, 203, 210, 208, 199).
+constexpr int kCompactTY = 12, kCompactTZ = 32;
+constexpr int kCompactThreads = ((kCompactTY + 2) * (kCompactTZ + 2) + 63) / 64 * 64;
+constexpr int kCompactResident = 2 * 256;
+
+// The march runs on lattices that fill it, of at least 4 planes, and that its
+// tiles cover with at most 3/4 more cells than sites.  us per step, one site
+// per thread / march: FP64 stress 48^3 14.1 / 14.2, 60 x 52 x 70 23.8 / 21.5,
+// 96^3 87 / 70; FP64 force 56^3 21.0 / 21.7, 60 x 52 x 70 25.4 / 24.4, 96^3
+// 104 / 91; FP32 force 80^3 31.9 / 33.2, 90 x 75 x 100 41.0 / 40.6, 128^3
+// 143 / 127; 300 x 40 x 20, 1.9 cells per site, FP64 force 25.7 / 26.5.
+template <typename T, bool FORCE>
+bool compact_march(const KParams& p, int ntiles)
+{
+    const long long plane = (long long)p.ny * p.nz;
+    const int limit = sizeof(T) == 4 ? 650000 : FORCE ? 200000 : 160000;
+    return p.nsites >= limit && p.nx >= 4 && 4LL * ntiles * kCompactTY * kCompactTZ <= 7 * plane;
+}
+
+// phi of the compact level `state`; next (may be null): the level a step
+// makes, whose phi_c the pass stores.
+template <typename T, bool FORCE>
+hipError_t launch_phi_compact_t(const KParams& p, const void* state, double* phi, void* next,
+                                hipStream_t s)
+{
+    constexpr bool F32 = sizeof(T) == 4;
+    T* G = level<T>(const_cast<void*>(state), p, F32).G;
+    unsigned* dphic = next ? level<T>(next, p, F32).phic : nullptr;
+    const int nty = (p.ny + kCompactTY - 1) / kCompactTY;
+    const int ntz = (p.nz + kCompactTZ - 1) / kCompactTZ;
+    if (compact_march<T, FORCE>(p, nty * ntz)) {
+        const int sx = compact_segment(p, nty * ntz, kCompactResident);
+        const int nseg = (p.nx + sx - 1) / sx;
+        k_phi_compact_march<T, F32, FORCE, kCompactTY, kCompactTZ>
+            <<<nty * ntz * nseg, kCompactThreads, 0, s>>>(p, nty, ntz, sx, compact_phi(G),
+                                                          compact_mu_u(G, p), phi, dphic);
+    } else {
+        const int nb = site_block(p);
+        k_phi_compact<T, F32, FORCE><<<(p.nsites + nb - 1) / nb, nb, 0, s>>>(
+            p, compact_phi(G), compact_mu_u(G, p), phi, dphic);
+    }
+    return hipGetLastError();
+}
+
+}  // namespace
+}  // namespace lbk

@@ -411,15 +411,20 @@ __device__ __forceinline__ void collide_g(const KParams& p, T* g, T phi, T mu, V
     }
 }
 
+template <typename T>
+__device__ __forceinline__ T chem_potential(const KParams& p, const Stencil& st)
+{
+    const T A = T(p.A), B = T(p.B), kap = T(p.kappa);
+    const T phi = T(st.phi), lap = T(st.lap);
+    const T phi2 = phi * phi;
+    return A * phi + B * phi2 * phi - kap * lap;
+}
+
 template <typename T, bool DEV, bool REF, bool G1 = false>
 __device__ __forceinline__ void collide(const KParams& p, T* f, T* g, const Stencil& st)
 {
     const Vel<T> u = collide_f<T, DEV>(p, f, st);
-    const T A = T(p.A), B = T(p.B), kap = T(p.kappa);
-    const T phi = T(st.phi), lap = T(st.lap);
-    const T phi2 = phi * phi;
-    const T mu = A * phi + B * phi2 * phi - kap * lap;
-    collide_g<T, REF, G1>(p, g, phi, mu, u);
+    collide_g<T, REF, G1>(p, g, T(st.phi), chem_potential<T>(p, st), u);
 }
 
 // ---------------------------------------------------------------------------
@@ -522,17 +527,26 @@ __device__ __forceinline__ void collide_force_g(const KParams& p, T* g, double p
     const T uu3 = (ux * ux + uy * uy + uz * uz) * T(1.0 / 3.0);
     const T gm = T(p.gamma) * mu, sg = REF ? gm : gm - phi * T(1.0 / 3.0);
     const T omg = T(p.omega_g);
+    const T r = REF ? T(0) : phi;
+    T eq[NV];
+    eq[0] = T(weight(0)) * (r + T(4.5) * (phi * -uu3 - sg));
+    // directions i and i + 1 are opposite: the terms even in c are one value
 #pragma unroll
-    for (int i = 0; i < NV; i++) {
+    for (int i = 1; i < NV; i += 2) {
         const T w = T(weight(i));
         const T cu = T(CX[i]) * ux + T(CY[i]) * uy + T(CZ[i]) * uz;
         const T q = cu * cu - uu3;
         const T c2m1 = T(CX[i] * CX[i] + CY[i] * CY[i] + CZ[i] * CZ[i] - 1);
-        const T geq = w * ((REF ? T(0) : phi) + T(3) * phi * cu + T(4.5) * (sg * c2m1 + phi * q));
+        const T odd = T(3) * phi * cu, even = T(4.5) * (sg * c2m1 + phi * q);
+        eq[i] = w * (r + odd + even);
+        eq[i + 1] = w * (r - odd + even);
+    }
+#pragma unroll
+    for (int i = 0; i < NV; i++) {
         if (G1)
-            g[i] = geq;
+            g[i] = eq[i];
         else
-            g[i] += omg * (geq - g[i]);
+            g[i] += omg * (eq[i] - g[i]);
     }
 }
 

@@ -19,7 +19,9 @@
 // differently in different kernels, and the two forms must round alike.
 #pragma clang fp contract(off)
 
+#include "lb_compact.h"
 #include "lb_device.h"
+#include "lb_sweep.h"
 
 namespace lbk {
 
@@ -29,8 +31,9 @@ namespace {
 
 // The force-coupling collision and propagation, one site per thread; phi of
 // the source level (all sites) comes from k_phi.  SUMS: block partials of
-// [rho, phi, j + F/2] of the source level (0, or the block size).
-template <typename T, bool DEV, bool REF, bool G1, int SUMS>
+// [rho, phi, j + F/2] of the source level (0, or the block size).  COMPACT:
+// the new level is compact (lb_compact.h).
+template <typename T, bool DEV, bool REF, bool G1, int SUMS, bool COMPACT = false>
 __global__ __launch_bounds__(kBlock) void k_step_force(KParams p, const T* __restrict__ sF,
                                                        const T* __restrict__ sG,
                                                        const unsigned* __restrict__ sphic,
@@ -38,9 +41,8 @@ __global__ __launch_bounds__(kBlock) void k_step_force(KParams p, const T* __res
                                                        T* __restrict__ dF, T* __restrict__ dG,
                                                        double* __restrict__ partials)
 {
-    const int s = xcd_block() * int(blockDim.x) + threadIdx.x;
     double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    if (s < p.nsites) {
+    const auto site = [&](int s) {
         const Geo q = geo_of(p, s);
         T f[NV], g[NV];
 #pragma unroll
@@ -61,12 +63,24 @@ __global__ __launch_bounds__(kBlock) void k_step_force(KParams p, const T* __res
         double F[3];
         force_from_phi(p, q, phi, F);
         if (SUMS) site_sums<DEV>(p, f, c, F, acc);
-        collide_force<T, DEV, REF, G1>(p, f, g, c, mu, F);
+        if constexpr (COMPACT) {
+            const Vel<T> u = collide_force_f<T, DEV>(p, f, F);
+            compact_mu_u(dG, p)[s] = MuU<T>{T(mu), u.x, u.y, u.z};
+        } else {
+            collide_force<T, DEV, REF, G1>(p, f, g, c, mu, F);
+        }
 #pragma unroll
         for (int i = 0; i < NV; i++) {
             dF[dist_own(p, q, i)] = f[i];
-            dG[dist_own(p, q, i)] = REF ? to_dest_ref(i, g[i], c, phi[push_site(p, q, i)]) : g[i];
+            if (!COMPACT)
+                dG[dist_own(p, q, i)] = REF ? to_dest_ref(i, g[i], c, phi[push_site(p, q, i)]) : g[i];
         }
+    };
+    if constexpr (SUMS > 0) {
+        for (XcdSweep w = sums_sweep(p.nsites, SUMS); w.s < w.end; w.s += w.stride) site(w.s);
+    } else {
+        const int s = xcd_block() * int(blockDim.x) + threadIdx.x;
+        if (s < p.nsites) site(s);
     }
     if (SUMS) block_partials<5, SUMS ? SUMS : kBlock>(acc, partials);
 }
@@ -328,12 +342,13 @@ __global__ __launch_bounds__(kForceFused) void k_force_fused(KParams p, TileCfg 
 }
 
 // k_step_force of a storage type by what it reduces and its block
-template <typename T, bool G1>
-decltype(&k_step_force<T, false, false, G1, 0>) pick_step_force(bool sums, int nb)
+template <typename T, bool G1, bool COMPACT>
+decltype(&k_step_force<T, false, false, G1, 0, COMPACT>) pick_step_force(bool sums, int nb)
 {
     constexpr bool F32 = std::is_same<T, float>::value;
-    if (!sums) return k_step_force<T, F32, F32, G1, 0>;
-    return nb == kBlock ? k_step_force<T, F32, F32, G1, kBlock> : k_step_force<T, F32, F32, G1, 64>;
+    if (!sums) return k_step_force<T, F32, F32, G1, 0, COMPACT>;
+    return nb == kBlock ? k_step_force<T, F32, F32, G1, kBlock, COMPACT>
+                        : k_step_force<T, F32, F32, G1, 64, COMPACT>;
 }
 
 template <typename T, bool NT>
@@ -387,8 +402,8 @@ int force_sums_blocks(const KParams& p, int seg_req)
 }
 
 hipError_t launch_force_collide(const KParams& p, const TileCfg& tc, bool fp32, int variant,
-                                const void* src, void* dst, double* phi, double* partials,
-                                hipStream_t s)
+                                bool compact, const void* src, void* dst, double* phi,
+                                double* partials, hipStream_t s)
 {
     const TileCfg ft = force_tiles(p, tc.seg_req);
     const int nft = ft.ntiles * ft.nseg;
@@ -405,9 +420,10 @@ hipError_t launch_force_collide(const KParams& p, const TileCfg& tc, bool fp32, 
                         : pick_force_fused<float, false>(g1, partials);
             k<<<nft, kForceFused, 0, s>>>(p, ft, a.F, a.G, a.phic, d.phic, phi, d.F, d.G, partials);
         } else {
-            auto k = g1 ? pick_step_force<float, true>(partials, nb)
-                        : pick_step_force<float, false>(partials, nb);
-            k<<<(p.nsites + nb - 1) / nb, nb, 0, s>>>(p, a.F, a.G, a.phic, phi, d.F, d.G, partials);
+            auto k = compact ? pick_step_force<float, true, true>(partials, nb)
+                     : g1    ? pick_step_force<float, true, false>(partials, nb)
+                             : pick_step_force<float, false, false>(partials, nb);
+            k<<<collide_grid(p, partials), nb, 0, s>>>(p, a.F, a.G, a.phic, phi, d.F, d.G, partials);
         }
     } else {
         Lvl<double> a = level<double>(const_cast<void*>(src), p, false);
@@ -418,12 +434,20 @@ hipError_t launch_force_collide(const KParams& p, const TileCfg& tc, bool fp32, 
             k<<<nft, kForceFused, 0, s>>>(p, ft, a.F, a.G, nullptr, nullptr, phi, d.F, d.G,
                                           partials);
         } else {
-            auto k = g1 ? pick_step_force<double, true>(partials, nb)
-                        : pick_step_force<double, false>(partials, nb);
-            k<<<(p.nsites + nb - 1) / nb, nb, 0, s>>>(p, a.F, a.G, a.phic, phi, d.F, d.G, partials);
+            auto k = compact ? pick_step_force<double, true, true>(partials, nb)
+                     : g1    ? pick_step_force<double, true, false>(partials, nb)
+                             : pick_step_force<double, false, false>(partials, nb);
+            k<<<collide_grid(p, partials), nb, 0, s>>>(p, a.F, a.G, a.phic, phi, d.F, d.G, partials);
         }
     }
     return hipGetLastError();
+}
+
+hipError_t launch_phi_compact_force(const KParams& p, bool fp32, const void* state, double* phi,
+                                    void* next, hipStream_t s)
+{
+    return fp32 ? launch_phi_compact_t<float, true>(p, state, phi, next, s)
+                : launch_phi_compact_t<double, true>(p, state, phi, next, s);
 }
 
 }  // namespace lbk

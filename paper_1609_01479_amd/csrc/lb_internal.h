@@ -101,16 +101,24 @@ int step_variant(const KParams& p, const TileCfg& tc, bool fp32, int variant, bo
 int step_sums_blocks(const KParams& p, const TileCfg& tc, bool fp32, int variant);
 hipError_t launch_step(const KParams& p, const TileCfg& tc, bool fp32, int variant,
                        const void* src, void* dst, double* phi_work, double* partials,
-                       double* phi_src_out, hipStream_t s);
+                       double* phi_src_out, hipStream_t s, int compact = 0);
+// Whether a step of `variant` can start from or leave a compact level
+// (lb_compact.h); launch_step's `compact`: kCompactSrc if src is compact,
+// kCompactDst if dst is to be.
+constexpr int kCompactSrc = 1, kCompactDst = 2;
+bool can_compact(const KParams& p, const TileCfg& tc, bool fp32, int variant);
+hipError_t launch_phi_compact_f64(const KParams& p, const void* state, double* phi, hipStream_t s);
+hipError_t launch_phi_compact_force(const KParams& p, bool fp32, const void* state, double* phi,
+                                    void* next, hipStream_t s);
 // launch_step's kernels of the stress coupling, by storage precision; phi64
 // is the field that variant 1's phi pass left.  launch_phi_*: phi of `state`,
 // and if `next` is not null the phi_c of that level (FP32 mode).
-hipError_t launch_step_f32(const KParams& p, const TileCfg& tc, int variant, const void* src,
-                           void* dst, double* phi64, double* partials, double* phi_src_out,
-                           hipStream_t s);
-hipError_t launch_step_f64(const KParams& p, const TileCfg& tc, int variant, const void* src,
-                           void* dst, double* phi64, double* partials, double* phi_src_out,
-                           hipStream_t s);
+hipError_t launch_step_f32(const KParams& p, const TileCfg& tc, int variant, bool compact,
+                           const void* src, void* dst, double* phi64, double* partials,
+                           double* phi_src_out, hipStream_t s);
+hipError_t launch_step_f64(const KParams& p, const TileCfg& tc, int variant, bool compact,
+                           const void* src, void* dst, double* phi64, double* partials,
+                           double* phi_src_out, hipStream_t s);
 hipError_t launch_phi_f32(const KParams& p, const void* state, double* phi, void* next,
                           hipStream_t s);
 hipError_t launch_phi_f64(const KParams& p, const void* state, double* phi, void* next,
@@ -125,7 +133,7 @@ hipError_t launch_phi_f64(const KParams& p, const void* state, double* phi, void
 // src in `phi` and dst's phi_c, one site per thread, Pi formed at each face
 // neighbour (partials: one block per kBlock sites).  Bit-identical levels.
 hipError_t launch_force_collide(const KParams& p, const TileCfg& tc, bool fp32, int variant,
-                                const void* src, void* dst, double* phi, double* partials,
+                                bool compact, const void* src, void* dst, double* phi, double* partials,
                                 hipStream_t s);
 int force_sums_blocks(const KParams& p, int seg_req);
 // phi(x) of the post-propagation state held in `state`.
@@ -241,5 +249,13 @@ hipError_t launch_faces(const KParams& p, bool fp32, void* state, void* lo, void
 // reduction, and of an LB step that reduces in its two-pass collision.
 constexpr int kMaxPartialBlocks = 2048;
 constexpr int kMaxStepPartials = 4096;
+
+// Workgroups of the two-pass step's collision kernel, one site per thread;
+// with sums at most kMaxStepPartials, which then sweep the sites.
+inline int collide_grid(const KParams& p, bool sums)
+{
+    const int g = (p.nsites + site_block(p) - 1) / site_block(p);
+    return sums && g > kMaxStepPartials ? kMaxStepPartials : g;
+}
 
 }  // namespace lbk

@@ -5,6 +5,7 @@
 // tiling.  The step's own kernels are in lb_step.h (the stress coupling),
 // lb_force.hip (the force coupling) and lb_fd.hip (the finite-difference
 // order parameter).
+#include "lb_compact.h"
 #include "lb_device.h"
 #include "lb_sweep.h"
 
@@ -192,10 +193,6 @@ void moments(const KParams& p, int nb, const void* state, const double* fphi, do
     k<<<nb, nt, 0, s>>>(p, a.F, a.G, a.phic, fphi, rho, u, phi, partials);
 }
 
-// The two-pass step's collision kernel reduces the sums itself, one block of
-// partials per block of sites, up to kMaxStepPartials of them.
-int collide_grid(const KParams& p) { return (p.nsites + site_block(p) - 1) / site_block(p); }
-bool collide_sums(const KParams& p) { return collide_grid(p) <= kMaxStepPartials; }
 
 // Instantiation dispatch: FP64 mode <double, false, false>, FP32 mode <float, true, true>.
 #define LB_DISPATCH(fp32, CALL64, CALL32) \
@@ -358,7 +355,7 @@ int step_variant(const KParams& p, const TileCfg& tc, bool fp32, int variant, bo
     // a segment length asked for is the marching kernel's; shards have no
     // two-pass form
     if (variant != 0 || p.xh || tc.seg_req > 0) return variant;
-    if (sums && !collide_sums(p)) return 0;
+    if (sums && collide_grid(p, false) > kMaxStepPartials) return 0;
     const bool g1 = !fp32 && p.omega_g == 1.0;
     const int limit = p.force ? (g1 ? 7100000 : fp32 ? 1100000 : 1500000)
                               : (g1 ? 2000000 : fp32 ? 700000 : 300000);
@@ -368,7 +365,7 @@ int step_variant(const KParams& p, const TileCfg& tc, bool fp32, int variant, bo
 int step_sums_blocks(const KParams& p, const TileCfg& tc, bool fp32, int variant)
 {
     variant = step_variant(p, tc, fp32, variant, true);
-    if (variant == 1) return collide_sums(p) ? collide_grid(p) : moments_grid(p, true);
+    if (variant == 1) return collide_grid(p, true);
     if (p.force) return force_sums_blocks(p, tc.seg_req);
     return tc.ntiles * tc.nseg;
 }
@@ -385,32 +382,44 @@ hipError_t launch_init(const KParams& p, bool fp32, void* state, const double* p
     return hipGetLastError();
 }
 
+// Not FP32 storage with the stress coupling: its collision forms g + (g^eq -
+// g), which rounds with g.  Below 40000 sites the launches set the time, and
+// the compact phi pass's are the longer ones (us per step, full / compact:
+// 16^3 5.8 / 6.2, 32^3 7.4 / 7.5, 40^3 10.5 / 9.8).
+bool can_compact(const KParams& p, const TileCfg& tc, bool fp32, int variant)
+{
+    if (p.fd || p.xh || variant != 0 || tc.seg_req > 0 || p.omega_g != 1.0) return false;
+    return p.nsites >= 40000 && (!fp32 || p.force);
+}
+
 hipError_t launch_step(const KParams& p, const TileCfg& tc, bool fp32, int variant,
                        const void* src, void* dst, double* phi_work, double* partials,
-                       double* phi_src_out, hipStream_t s)
+                       double* phi_src_out, hipStream_t s, int compact)
 {
     // phi of src goes to phi_src_out if given (the work field otherwise,
-    // where a pass needs one)
+    // where a pass needs one), or into the compact level that it is part of
     double* phi64 = phi_src_out ? phi_src_out : phi_work;
-    variant = step_variant(p, tc, fp32, variant, partials != nullptr);
+    const bool to_compact = compact & kCompactDst;
+    if (to_compact)
+        phi64 = fp32 ? compact_phi(level<float>(dst, p, true).G)
+                     : compact_phi(level<double>(dst, p, false).G);
+    variant = compact ? 1 : step_variant(p, tc, fp32, variant, partials != nullptr);
     if (variant == 1) {
         // phi (and in FP32 mode the new level's phi_c) for the collision pass
-        hipError_t e = fp32 ? launch_phi_f32(p, src, phi64, dst, s)
-                            : launch_phi_f64(p, src, phi64, dst, s);
+        hipError_t e;
+        if (compact & kCompactSrc)
+            e = p.force ? launch_phi_compact_force(p, fp32, src, phi64, to_compact ? nullptr : dst, s)
+                        : launch_phi_compact_f64(p, src, phi64, s);
+        else
+            e = fp32 ? launch_phi_f32(p, src, phi64, to_compact ? nullptr : dst, s)
+                     : launch_phi_f64(p, src, phi64, dst, s);
         if (e != hipSuccess) return e;
-        if (partials && !collide_sums(p)) {
-            // more blocks than the partials may be: a moments pass of its own
-            auto m = fp32 ? moments<float> : moments<double>;
-            m(p, moments_grid(p, true), src, p.force ? phi64 : nullptr, nullptr, nullptr, nullptr,
-              partials, s);
-            partials = nullptr;
-        }
     }
     if (p.force)
-        return launch_force_collide(p, tc, fp32, variant, src, dst,
+        return launch_force_collide(p, tc, fp32, variant, to_compact, src, dst,
                                     variant == 1 ? phi64 : phi_src_out, partials, s);
-    return fp32 ? launch_step_f32(p, tc, variant, src, dst, phi64, partials, phi_src_out, s)
-                : launch_step_f64(p, tc, variant, src, dst, phi64, partials, phi_src_out, s);
+    auto step = fp32 ? launch_step_f32 : launch_step_f64;
+    return step(p, tc, variant, to_compact, src, dst, phi64, partials, phi_src_out, s);
 }
 
 hipError_t launch_phi(const KParams& p, bool fp32, const void* state, double* phi, hipStream_t s)

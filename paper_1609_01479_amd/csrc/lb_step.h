@@ -22,7 +22,9 @@
 
 #include <type_traits>
 
+#include "lb_compact.h"
 #include "lb_device.h"
+#include "lb_sweep.h"
 
 namespace lbk {
 
@@ -66,8 +68,9 @@ __global__ __launch_bounds__(kBlock) void k_phi(KParams p, const T* __restrict__
 // comes from k_phi.  G1 (FP64, omega_g = 1): g* = g^eq, so the collision
 // loads no g and the two passes move the single pass's 608 bytes per site
 // plus phi (776 otherwise).  SUMS: 0, or the block size, for block partials
-// of the source level's conserved sums.
-template <typename T, bool DEV, bool REF, bool G1, int SUMS>
+// of the source level's conserved sums.  COMPACT: the new level is compact
+// (lb_compact.h), its phi this step's phi field, written by the phi pass.
+template <typename T, bool DEV, bool REF, bool G1, int SUMS, bool COMPACT = false>
 __global__ __launch_bounds__(kBlock) void k_step_2s(KParams p, const T* __restrict__ sF,
                                                     const T* __restrict__ sG,
                                                     const unsigned* __restrict__ sphic,
@@ -75,9 +78,8 @@ __global__ __launch_bounds__(kBlock) void k_step_2s(KParams p, const T* __restri
                                                     T* __restrict__ dF, T* __restrict__ dG,
                                                     double* __restrict__ partials)
 {
-    const int s = xcd_block() * int(blockDim.x) + threadIdx.x;
     double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    if (s < p.nsites) {
+    const auto site = [&](int s) {
         const Geo q = geo_of(p, s);
         T f[NV], g[NV];
 #pragma unroll
@@ -95,12 +97,24 @@ __global__ __launch_bounds__(kBlock) void k_step_2s(KParams p, const T* __restri
 #pragma unroll
             for (int i = 0; i < NV; i++) g[i] = pre_collision_dev(i, g[i], dphi);
         }
-        collide<T, DEV, REF, G1>(p, f, g, st);
+        if constexpr (COMPACT) {
+            const Vel<T> u = collide_f<T, DEV>(p, f, st);
+            compact_mu_u(dG, p)[s] = MuU<T>{chem_potential<T>(p, st), u.x, u.y, u.z};
+        } else {
+            collide<T, DEV, REF, G1>(p, f, g, st);
+        }
 #pragma unroll
         for (int i = 0; i < NV; i++) {
             dF[dist_own(p, q, i)] = f[i];
-            dG[dist_own(p, q, i)] = REF ? to_dest_ref(i, g[i], c, phi[push_site(p, q, i)]) : g[i];
+            if (!COMPACT)
+                dG[dist_own(p, q, i)] = REF ? to_dest_ref(i, g[i], c, phi[push_site(p, q, i)]) : g[i];
         }
+    };
+    if constexpr (SUMS > 0) {
+        for (XcdSweep w = sums_sweep(p.nsites, SUMS); w.s < w.end; w.s += w.stride) site(w.s);
+    } else {
+        const int s = xcd_block() * int(blockDim.x) + threadIdx.x;
+        if (s < p.nsites) site(s);
     }
     if (SUMS) block_partials<5, SUMS ? SUMS : kBlock>(acc, partials);
 }
@@ -582,20 +596,21 @@ template <typename T>
 struct Fused;
 
 // k_step_2s of a storage type by what it reduces and its block.
-template <typename T, bool G1>
-decltype(&k_step_2s<T, false, false, G1, 0>) pick_2s(bool sums, int nb)
+template <typename T, bool G1, bool COMPACT>
+decltype(&k_step_2s<T, false, false, G1, 0, COMPACT>) pick_2s(bool sums, int nb)
 {
     constexpr bool F32 = std::is_same<T, float>::value;
-    if (!sums) return k_step_2s<T, F32, F32, G1, 0>;
-    return nb == kBlock ? k_step_2s<T, F32, F32, G1, kBlock> : k_step_2s<T, F32, F32, G1, 64>;
+    if (!sums) return k_step_2s<T, F32, F32, G1, 0, COMPACT>;
+    return nb == kBlock ? k_step_2s<T, F32, F32, G1, kBlock, COMPACT>
+                        : k_step_2s<T, F32, F32, G1, 64, COMPACT>;
 }
 
 // The step of one storage precision.  variant: 0 march, 1 two passes (phi64:
 // the phi field between them), 2 the march's free-streaming twin.
 template <typename T>
-hipError_t launch_step_t(const KParams& p, const TileCfg& tc, int variant, const void* src,
-                         void* dst, double* phi64, double* partials, double* phi_src_out,
-                         hipStream_t s)
+hipError_t launch_step_t(const KParams& p, const TileCfg& tc, int variant, bool compact,
+                         const void* src, void* dst, double* phi64, double* partials,
+                         double* phi_src_out, hipStream_t s)
 {
     constexpr bool F32 = std::is_same<T, float>::value;
     constexpr bool CAN_G1 = !F32;
@@ -604,8 +619,10 @@ hipError_t launch_step_t(const KParams& p, const TileCfg& tc, int variant, const
     const bool g1 = CAN_G1 && p.omega_g == 1.0;
     if (variant == 1) {
         const int nb = site_block(p);
-        auto k = g1 ? pick_2s<T, CAN_G1>(partials, nb) : pick_2s<T, false>(partials, nb);
-        k<<<(p.nsites + nb - 1) / nb, nb, 0, s>>>(p, a.F, a.G, a.phic, phi64, d.F, d.G, partials);
+        auto k = compact && g1 ? pick_2s<T, CAN_G1, CAN_G1>(partials, nb)
+                 : g1          ? pick_2s<T, CAN_G1, false>(partials, nb)
+                               : pick_2s<T, false, false>(partials, nb);
+        k<<<collide_grid(p, partials), nb, 0, s>>>(p, a.F, a.G, a.phic, phi64, d.F, d.G, partials);
     } else {
         const bool small = size_t(NV) * p.stride * sizeof(T) < (size_t(1) << 32);
         auto k = Fused<T>::get(small, tc.tz, variant == 0, g1, nt_stores(p, 2 * NV, sizeof(T), 144));

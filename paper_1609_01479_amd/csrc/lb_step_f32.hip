@@ -40,11 +40,11 @@ struct Fused<float> {
 
 }  // namespace
 
-hipError_t launch_step_f32(const KParams& p, const TileCfg& tc, int variant, const void* src,
-                           void* dst, double* phi64, double* partials, double* phi_src_out,
-                           hipStream_t s)
+hipError_t launch_step_f32(const KParams& p, const TileCfg& tc, int variant, bool compact,
+                           const void* src, void* dst, double* phi64, double* partials,
+                           double* phi_src_out, hipStream_t s)
 {
-    return launch_step_t<float>(p, tc, variant, src, dst, phi64, partials, phi_src_out, s);
+    return launch_step_t<float>(p, tc, variant, compact, src, dst, phi64, partials, phi_src_out, s);
 }
 
 hipError_t launch_phi_f32(const KParams& p, const void* state, double* phi, void* next,

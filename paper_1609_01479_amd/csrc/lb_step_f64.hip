@@ -44,17 +44,22 @@ struct Fused<double> {
 
 }  // namespace
 
-hipError_t launch_step_f64(const KParams& p, const TileCfg& tc, int variant, const void* src,
-                           void* dst, double* phi64, double* partials, double* phi_src_out,
-                           hipStream_t s)
+hipError_t launch_step_f64(const KParams& p, const TileCfg& tc, int variant, bool compact,
+                           const void* src, void* dst, double* phi64, double* partials,
+                           double* phi_src_out, hipStream_t s)
 {
-    return launch_step_t<double>(p, tc, variant, src, dst, phi64, partials, phi_src_out, s);
+    return launch_step_t<double>(p, tc, variant, compact, src, dst, phi64, partials, phi_src_out, s);
 }
 
 hipError_t launch_phi_f64(const KParams& p, const void* state, double* phi, void* next,
                           hipStream_t s)
 {
     return launch_phi_t<double>(p, state, phi, next, s);
+}
+
+hipError_t launch_phi_compact_f64(const KParams& p, const void* state, double* phi, hipStream_t s)
+{
+    return launch_phi_compact_t<double, false>(p, state, phi, nullptr, s);
 }
 
 }  // namespace lbk

@@ -33,5 +33,14 @@ __device__ __forceinline__ XcdSweep xcd_sweep(int nsites, int block_threads)
     return XcdSweep{begin + local * block_threads + int(threadIdx.x), end, per_xcd * block_threads};
 }
 
+// The sites of a kernel that reduces sums over at most a limited number of
+// workgroups: one each, in xcd_block()'s order, or a sweep where they are fewer.
+__device__ __forceinline__ XcdSweep sums_sweep(int nsites, int block_threads)
+{
+    const int n = int(gridDim.x) * block_threads;
+    if (n < nsites) return xcd_sweep(nsites, block_threads);
+    return XcdSweep{xcd_block() * block_threads + int(threadIdx.x), nsites, n};
+}
+
 }  // namespace dev
 }  // namespace lbk

@@ -180,3 +180,40 @@ def test_moments_alone_and_together_agree(shape, prec, coupling, order_param):
     n = float(np.prod(shape))
     size = torch.stack([rho.sum(), phi.abs().sum(), *((rho * u[k]).abs().sum() for k in range(3))])
     assert bool(((s - ref).abs() <= (2.0 * n + 4.0) * 2.3e-16 * size).all())
+
+
+# (shape): below and above the sites from which a call's steps hand each other
+# compact levels (40000), and from which their phi pass marches (FP64 160000,
+# with the force 200000, FP32 storage 650000): extents that its 12 x 32 tile
+# divides, covers once, shifts back or is larger than, thin slabs, few and many
+# planes, more sites than the sums have workgroups for
+COMPACT = [(33, 33, 36), (40, 25, 40), (34, 11, 107), (70, 48, 64), (4, 203, 257), (57, 61, 63),
+           (3, 200, 300), (41, 5, 1000), (9000, 11, 7), (88, 90, 83), (101, 97, 120)]
+
+
+@pytest.mark.parametrize("tau_f", [1.0, 0.8])
+@pytest.mark.parametrize("coupling,prec", [("stress", "fp64"), ("force", "fp64"),
+                                           ("force", "fp32_dev")])
+@pytest.mark.parametrize("shape", COMPACT)
+def test_steps_of_one_call_are_those_of_many(shape, coupling, prec, tau_f):
+    """Steps of one call hand each other compact levels (tau_g = 1); one step
+    per call makes full ones: the same levels bit for bit."""
+    print(f"[compact] {shape} {coupling} {prec} tau_f {tau_f}", flush=True)
+    phi0 = lbinputs.spinodal_phi0(shape, seed=23, amp=0.3)
+    one = make_lb(shape, precision=prec, tau_f=tau_f, coupling=coupling)
+    many = make_lb(shape, precision=prec, tau_f=tau_f, coupling=coupling)
+    one.init_phi(phi0)
+    many.init_phi(phi0)
+    sums = []
+    for _ in range(7):
+        sums.append(many.sums().cpu().numpy())
+        many.step(1)
+    one.step(2)
+    rows = one.step_sums(3).cpu().numpy()
+    one.step(2)
+    for a, b in zip(gpu_state(one), gpu_state(many)):
+        assert np.array_equal(a, b)
+    # five sums of n terms of order 1 in two orders: n eps of their scale n
+    n = float(np.prod(shape))
+    for t in range(3):
+        assert np.abs(rows[t] - sums[2 + t]).max() <= n * n * 2.3e-16

@@ -307,6 +307,14 @@ lb_status lb_step_from_phi(lb_ctx *ctx, const void *src_dev, void *dst_dev, doub
 lb_status lb_step_chain(lb_ctx *ctx, const void *src_dev, void *const *levels_dev,
                         double *const *phis_dev, int32_t nsteps);
 
+/* lb_step_chain for the reverse mode: only the last level is left a time level
+ * (and with last_state = 0 not that one either).  The others hold what
+ * lb_adjoint_chain reads of them where it is given their phi, and are no
+ * source of a later call.  phis_dev: a step's entry must differ from that of
+ * the step before. */
+lb_status lb_step_segment(lb_ctx *ctx, const void *src_dev, void *const *levels_dev,
+                          double *const *phis_dev, int32_t nsteps, int32_t last_state);
+
 /* phi of the caller's time level (device, N FP64 values in dense (x, y, z)
  * order, 256-byte aligned), without touching the context's current level.
  * LB_ESTATE on a shard.  Passage: Sec. 3.2.3, Fig. 2 (copyFromTarget); the

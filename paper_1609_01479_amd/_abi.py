@@ -22,7 +22,7 @@ NOALLOC_MAX_PARTIALS = 4096  # LB_NOALLOC_MAX_PARTIALS
 # Every symbol include/lb.h declares.
 EXPORTS = ("lb_abi_version", "lb_query_sizes", "lb_create", "lb_destroy", "lb_set_stream",
            "lb_init_phi", "lb_step", "lb_step_sums", "lb_step_sums_noalloc", "lb_step_from", "lb_step_from_phi",
-           "lb_step_chain", "lb_level_phi", "lb_moments", "lb_sums", "lb_get_state", "lb_set_state",
+           "lb_step_chain", "lb_step_segment", "lb_level_phi", "lb_moments", "lb_sums", "lb_get_state", "lb_set_state",
            "lb_export_dist", "lb_import_dist", "lb_adjoint_seed", "lb_adjoint_step",
            "lb_adjoint_step_phi", "lb_adjoint_chain", "lb_adjoint_phi0", "lb_adjoint_export", "lb_pack_faces",
            "lb_unpack_faces", "lb_copy_probe",
@@ -84,6 +84,7 @@ def lib():
         "lb_step_from": ([vp, vp, vp], ctypes.c_int),
         "lb_step_from_phi": ([vp, vp, vp, dp], ctypes.c_int),
         "lb_step_chain": ([vp, vp, P(vp), P(vp), i32], ctypes.c_int),
+        "lb_step_segment": ([vp, vp, P(vp), P(vp), i32, i32], ctypes.c_int),
         "lb_level_phi": ([vp, vp, dp], ctypes.c_int),
         "lb_step_sums": ([vp, i32, dp], ctypes.c_int),
         "lb_step_sums_noalloc": ([vp, i32, dp], ctypes.c_int),

@@ -312,14 +312,15 @@ lb_status lb_init_phi(lb_ctx* ctx, const double* phi0_dev)
 // One step from src to dst with the context's scheme; partials (may be null)
 // takes the block partials of src's conserved sums.
 static hipError_t one_step(lb_ctx* ctx, const void* src, void* dst, double* partials,
-                           double* phi_src_out = nullptr, int compact = 0)
+                           double* phi_src_out = nullptr, int compact = 0,
+                           const double* compact_src_phi = nullptr)
 {
     double* work = static_cast<double*>(ctx->b.phi);
     if (ctx->kp.fd)
         return lbk::launch_fd_step(ctx->kp, ctx->tc, ctx->fp32, ctx->p.kernel, src, dst, work,
                                    partials, ctx->stream);
     return lbk::launch_step(ctx->kp, ctx->tc, ctx->fp32, ctx->p.kernel, src, dst, work, partials,
-                            phi_src_out, ctx->stream, compact);
+                            phi_src_out, ctx->stream, compact, compact_src_phi);
 }
 
 // The partial blocks this context's steps reduce over.
@@ -428,8 +429,9 @@ lb_status lb_step_from_phi(lb_ctx* ctx, const void* src_dev, void* dst_dev, doub
     return e == hipSuccess ? LB_OK : hip_fail(e, "lb_step_from_phi");
 }
 
-lb_status lb_step_chain(lb_ctx* ctx, const void* src_dev, void* const* levels_dev,
-                        double* const* phis_dev, int32_t nsteps)
+// The checks of a chain of steps through the caller's levels.
+static lb_status check_chain(lb_ctx* ctx, const void* src_dev, void* const* levels_dev,
+                             double* const* phis_dev, int32_t nsteps)
 {
     if (!ctx || !src_dev) return fail(LB_EINVAL, "ctx and src_dev are required");
     if (nsteps < 0) return fail(LB_EINVAL, "nsteps must be >= 0 (got %d)", nsteps);
@@ -448,10 +450,39 @@ lb_status lb_step_chain(lb_ctx* ctx, const void* src_dev, void* const* levels_de
         if (ctx->kp.fd) return fail(LB_EINVAL, "phis_dev is for LB_OP_LB");
         if (!aligned(phi)) return fail(LB_EALIGN, "phis_dev[%d] is not 256-byte aligned", t);
     }
+    return LB_OK;
+}
+
+lb_status lb_step_chain(lb_ctx* ctx, const void* src_dev, void* const* levels_dev,
+                        double* const* phis_dev, int32_t nsteps)
+{
+    lb_status st = check_chain(ctx, src_dev, levels_dev, phis_dev, nsteps);
+    if (st != LB_OK) return st;
     for (int32_t t = 0; t < nsteps; t++) {
         hipError_t e = one_step(ctx, t ? levels_dev[t - 1] : src_dev, levels_dev[t], nullptr,
                                 phis_dev ? phis_dev[t] : nullptr);
         if (e != hipSuccess) return hip_fail(e, "lb_step_chain");
+    }
+    return LB_OK;
+}
+
+lb_status lb_step_segment(lb_ctx* ctx, const void* src_dev, void* const* levels_dev,
+                          double* const* phis_dev, int32_t nsteps, int32_t last_state)
+{
+    lb_status st = check_chain(ctx, src_dev, levels_dev, phis_dev, nsteps);
+    if (st != LB_OK) return st;
+    for (int32_t t = 1; phis_dev && t < nsteps; t++)
+        if (phis_dev[t] && phis_dev[t] == phis_dev[t - 1])
+            return fail(LB_EINVAL, "phis_dev[%d] is that of the step before", t);
+    const bool compact = lbk::can_compact(ctx->kp, ctx->tc, ctx->fp32, ctx->p.kernel);
+    for (int32_t t = 0; t < nsteps; t++) {
+        const int form = !compact ? 0
+                                  : (t > 0 ? lbk::kCompactSrc : 0) |
+                                        (t + 1 < nsteps || !last_state ? lbk::kCompactDst : 0);
+        hipError_t e = one_step(ctx, t ? levels_dev[t - 1] : src_dev, levels_dev[t], nullptr,
+                                phis_dev ? phis_dev[t] : nullptr, form,
+                                phis_dev && t ? phis_dev[t - 1] : nullptr);
+        if (e != hipSuccess) return hip_fail(e, "lb_step_segment");
     }
     return LB_OK;
 }

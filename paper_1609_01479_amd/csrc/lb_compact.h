@@ -270,14 +270,15 @@ bool compact_march(const KParams& p, int ntiles)
     return p.nsites >= limit && p.nx >= 4 && 4LL * ntiles * kCompactTY * kCompactTZ <= 7 * plane;
 }
 
-// phi of the compact level `state`; next (may be null): the level a step
-// makes, whose phi_c the pass stores.
+// phi of the compact level `state`, its own phi field cphi if that is given;
+// next (may be null): the level a step makes, whose phi_c the pass stores.
 template <typename T, bool FORCE>
-hipError_t launch_phi_compact_t(const KParams& p, const void* state, double* phi, void* next,
-                                hipStream_t s)
+hipError_t launch_phi_compact_t(const KParams& p, const void* state, const double* cphi,
+                                double* phi, void* next, hipStream_t s)
 {
     constexpr bool F32 = sizeof(T) == 4;
     T* G = level<T>(const_cast<void*>(state), p, F32).G;
+    if (!cphi) cphi = compact_phi(G);
     unsigned* dphic = next ? level<T>(next, p, F32).phic : nullptr;
     const int nty = (p.ny + kCompactTY - 1) / kCompactTY;
     const int ntz = (p.nz + kCompactTZ - 1) / kCompactTZ;
@@ -285,12 +286,12 @@ hipError_t launch_phi_compact_t(const KParams& p, const void* state, double* phi
         const int sx = compact_segment(p, nty * ntz, kCompactResident);
         const int nseg = (p.nx + sx - 1) / sx;
         k_phi_compact_march<T, F32, FORCE, kCompactTY, kCompactTZ>
-            <<<nty * ntz * nseg, kCompactThreads, 0, s>>>(p, nty, ntz, sx, compact_phi(G),
-                                                          compact_mu_u(G, p), phi, dphic);
+            <<<nty * ntz * nseg, kCompactThreads, 0, s>>>(p, nty, ntz, sx, cphi, compact_mu_u(G, p),
+                                                          phi, dphic);
     } else {
         const int nb = site_block(p);
         k_phi_compact<T, F32, FORCE><<<(p.nsites + nb - 1) / nb, nb, 0, s>>>(
-            p, compact_phi(G), compact_mu_u(G, p), phi, dphic);
+            p, cphi, compact_mu_u(G, p), phi, dphic);
     }
     return hipGetLastError();
 }

@@ -443,11 +443,11 @@ hipError_t launch_force_collide(const KParams& p, const TileCfg& tc, bool fp32, 
     return hipGetLastError();
 }
 
-hipError_t launch_phi_compact_force(const KParams& p, bool fp32, const void* state, double* phi,
-                                    void* next, hipStream_t s)
+hipError_t launch_phi_compact_force(const KParams& p, bool fp32, const void* state,
+                                    const double* cphi, double* phi, void* next, hipStream_t s)
 {
-    return fp32 ? launch_phi_compact_t<float, true>(p, state, phi, next, s)
-                : launch_phi_compact_t<double, true>(p, state, phi, next, s);
+    return fp32 ? launch_phi_compact_t<float, true>(p, state, cphi, phi, next, s)
+                : launch_phi_compact_t<double, true>(p, state, cphi, phi, next, s);
 }
 
 }  // namespace lbk

@@ -101,15 +101,18 @@ int step_variant(const KParams& p, const TileCfg& tc, bool fp32, int variant, bo
 int step_sums_blocks(const KParams& p, const TileCfg& tc, bool fp32, int variant);
 hipError_t launch_step(const KParams& p, const TileCfg& tc, bool fp32, int variant,
                        const void* src, void* dst, double* phi_work, double* partials,
-                       double* phi_src_out, hipStream_t s, int compact = 0);
+                       double* phi_src_out, hipStream_t s, int compact = 0,
+                       const double* compact_src_phi = nullptr);
 // Whether a step of `variant` can start from or leave a compact level
-// (lb_compact.h); launch_step's `compact`: kCompactSrc if src is compact,
-// kCompactDst if dst is to be.
+// (lb_compact.h); launch_step's `compact`: kCompactSrc if src is compact (its
+// phi in compact_src_phi if that is given: the phi_src_out of the step that
+// made it), kCompactDst if dst is to be.
 constexpr int kCompactSrc = 1, kCompactDst = 2;
 bool can_compact(const KParams& p, const TileCfg& tc, bool fp32, int variant);
-hipError_t launch_phi_compact_f64(const KParams& p, const void* state, double* phi, hipStream_t s);
-hipError_t launch_phi_compact_force(const KParams& p, bool fp32, const void* state, double* phi,
-                                    void* next, hipStream_t s);
+hipError_t launch_phi_compact_f64(const KParams& p, const void* state, const double* cphi,
+                                  double* phi, hipStream_t s);
+hipError_t launch_phi_compact_force(const KParams& p, bool fp32, const void* state,
+                                    const double* cphi, double* phi, void* next, hipStream_t s);
 // launch_step's kernels of the stress coupling, by storage precision; phi64
 // is the field that variant 1's phi pass left.  launch_phi_*: phi of `state`,
 // and if `next` is not null the phi_c of that level (FP32 mode).

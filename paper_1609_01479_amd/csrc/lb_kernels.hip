@@ -394,13 +394,14 @@ bool can_compact(const KParams& p, const TileCfg& tc, bool fp32, int variant)
 
 hipError_t launch_step(const KParams& p, const TileCfg& tc, bool fp32, int variant,
                        const void* src, void* dst, double* phi_work, double* partials,
-                       double* phi_src_out, hipStream_t s, int compact)
+                       double* phi_src_out, hipStream_t s, int compact,
+                       const double* compact_src_phi)
 {
     // phi of src goes to phi_src_out if given (the work field otherwise,
     // where a pass needs one), or into the compact level that it is part of
     double* phi64 = phi_src_out ? phi_src_out : phi_work;
     const bool to_compact = compact & kCompactDst;
-    if (to_compact)
+    if (to_compact && !phi_src_out)
         phi64 = fp32 ? compact_phi(level<float>(dst, p, true).G)
                      : compact_phi(level<double>(dst, p, false).G);
     variant = compact ? 1 : step_variant(p, tc, fp32, variant, partials != nullptr);
@@ -408,8 +409,9 @@ hipError_t launch_step(const KParams& p, const TileCfg& tc, bool fp32, int varia
         // phi (and in FP32 mode the new level's phi_c) for the collision pass
         hipError_t e;
         if (compact & kCompactSrc)
-            e = p.force ? launch_phi_compact_force(p, fp32, src, phi64, to_compact ? nullptr : dst, s)
-                        : launch_phi_compact_f64(p, src, phi64, s);
+            e = p.force ? launch_phi_compact_force(p, fp32, src, compact_src_phi, phi64,
+                                                   to_compact ? nullptr : dst, s)
+                        : launch_phi_compact_f64(p, src, compact_src_phi, phi64, s);
         else
             e = fp32 ? launch_phi_f32(p, src, phi64, to_compact ? nullptr : dst, s)
                      : launch_phi_f64(p, src, phi64, dst, s);

@@ -57,9 +57,10 @@ hipError_t launch_phi_f64(const KParams& p, const void* state, double* phi, void
     return launch_phi_t<double>(p, state, phi, next, s);
 }
 
-hipError_t launch_phi_compact_f64(const KParams& p, const void* state, double* phi, hipStream_t s)
+hipError_t launch_phi_compact_f64(const KParams& p, const void* state, const double* cphi,
+                                  double* phi, hipStream_t s)
 {
-    return launch_phi_compact_t<double, false>(p, state, phi, nullptr, s);
+    return launch_phi_compact_t<double, false>(p, state, cphi, phi, nullptr, s);
 }
 
 }  // namespace lbk

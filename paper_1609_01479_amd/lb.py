@@ -231,11 +231,13 @@ class LB:
         if t.numel() * t.element_size() != self.sizes.state_bytes:
             raise ValueError("state buffer has the wrong size")
 
-    def step_chain(self, src: torch.Tensor, levels, phis=None) -> None:
+    def step_chain(self, src: torch.Tensor, levels, phis=None, states: str = "all") -> None:
         """len(levels) steps in one call: from `src` into levels[0], from there
         into levels[1], and so on (caller buffers; two scratch levels may take
         turns).  phis (LB order parameter): for each step None or the FP64
-        tensor that receives phi of the level it leaves (lb_step_chain)."""
+        tensor that receives phi of the level it leaves (lb_step_chain).
+        states "last" or "none": only the last level is left a state, or none;
+        the others serve adjoint_chain with their phis only (lb_step_segment)."""
         self._check_level(src)
         for t in levels:
             self._check_level(t)
@@ -245,8 +247,14 @@ class LB:
             for t in phis:
                 if t is not None:
                     self._check_phi(t)
-        self._call("lb_step_chain", _ptr(src), _ptrs(levels),
-                   None if phis is None else _ptrs(phis), ctypes.c_int32(len(levels)))
+        args = (_ptr(src), _ptrs(levels), None if phis is None else _ptrs(phis),
+                ctypes.c_int32(len(levels)))
+        if states == "all":
+            self._call("lb_step_chain", *args)
+        elif states in ("last", "none"):
+            self._call("lb_step_segment", *args, ctypes.c_int32(states == "last"))
+        else:
+            raise ValueError('states must be "all", "last" or "none"')
 
     def level_phi(self, level: torch.Tensor) -> torch.Tensor:
         """phi of the time level in `level` (a caller buffer)."""

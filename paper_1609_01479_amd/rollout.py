@@ -5,12 +5,14 @@ backward(dL/dphi_T) returns dL/dphi0 and dL/d(A, B, kappa) from the
 hand-written adjoint kernels (lb_adjoint_step), with checkpointing and
 recomputation: the forward keeps the state every k steps (k = ceil(sqrt(T))
 by default); the backward takes each checkpoint in reverse order,
-recomputes the k - 1 later states of its segment (lb_step_chain: each
+recomputes the k - 1 later states of its segment (lb_step_segment: each
 written once, straight into its segment buffer), and walks the adjoint back
 through them (lb_adjoint_chain).  A segment is one native call each way: step
-by step from Python, a small lattice's rollout waited for the host.  Memory: ceil(T/k) + max(k - 1, 2) states instead of T (the
-checkpoints, and the segment buffers or the forward's two scratch levels),
-plus, for the LB order parameter, FP64 phi fields (8 bytes per site each) that hand phi of
+by step from Python, a small lattice's rollout waited for the host.  Only the
+checkpoints need to be states; the levels between them are left as the next
+step and the reverse step read them (lb_step_segment).  Memory: ceil(T/k) +
+max(k - 1, 2) states instead of T (the checkpoints, and the segment buffers or
+the forward's two scratch levels), plus, for the LB order parameter, FP64 phi fields (8 bytes per site each) that hand phi of
 each level to its reverse step, so that none runs a phi pass: k - 1 for the
 recomputed levels, and one per segment for its last level, stored by the
 forward step that leaves it.  The forward writes each checkpoint with the
@@ -91,7 +93,7 @@ class _Rollout(torch.autograd.Function):
             k = int(interval or default_interval(T))
         lb.init_phi(phi0.detach())
         # the steps write caller buffers, each segment in one call
-        # (lb_step_chain): a segment's last step straight into the next
+        # (lb_step_segment): a segment's last step straight into the next
         # checkpoint, its others into two scratch levels, so the checkpoints
         # cost no copies.  The context's own two levels are the first
         # checkpoint (where lb_init_phi put the initial state) and one of the
@@ -116,7 +118,7 @@ class _Rollout(torch.autograd.Function):
                     phis = [None] * n
                     phis[-1] = torch.empty(lb.shape, dtype=torch.float64, device=dev)
                     ends.append(phis[-1])
-                lb.step_chain(src, levels, phis)
+                lb.step_chain(src, levels, phis, states="last")
                 src = levels[-1]
         phiT = lb.level_phi(src)
         del work
@@ -148,7 +150,8 @@ class _Rollout(torch.autograd.Function):
                 phis = [torch.empty(lb.shape, dtype=torch.float64, device=dev) for _ in range(m)]
         for si in reversed(range(len(ckpts) if T > 0 else 0)):
             n = min(T - si * k, k)
-            lb.step_chain(ckpts[si], seg[:n - 1], phis[:n - 1] if phis else None)
+            lb.step_chain(ckpts[si], seg[:n - 1], phis[:n - 1] if phis else None,
+                          states="none")
             levels = [ckpts[si]] + seg[:n - 1]
             lb.adjoint_chain(levels[::-1], dtheta,
                              None if phis is None else [ends[si]] + phis[:n - 1][::-1])

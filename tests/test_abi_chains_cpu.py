@@ -48,3 +48,25 @@ def test_chains_validate_without_launching(abi, order_param):  # noqa: F811
         assert L.lb_adjoint_chain(ctx, two, None, 2, None) == abi.LB_ESTATE
     finally:
         L.lb_destroy(ctx)
+
+
+@pytest.mark.parametrize("last_state", [0, 1])
+def test_segment_validates_as_the_chain(abi, last_state):  # noqa: F811
+    L = abi.lib()
+    ctx = ctypes.c_void_p()
+    b = abi.LbBuffers()
+    b.state[0], b.state[1], b.phi, b.scratch = 0x1000, 0x2000, 0x3000, 0x4000
+    p = _params(abi)
+    assert L.lb_create(ctypes.byref(p), ctypes.byref(b), None, ctypes.byref(ctx)) == abi.LB_OK
+    try:
+        src = ctypes.c_void_p(0x10000)
+        two = _arr(0x20000, 0x30000)
+        assert L.lb_step_segment(None, src, two, None, 2, last_state) == abi.LB_EINVAL
+        assert L.lb_step_segment(ctx, src, _arr(0x20000, 0x20000), None, 2,
+                                 last_state) == abi.LB_EINVAL
+        assert L.lb_step_segment(ctx, src, two, _arr(None, 0x40010), 2, last_state) == abi.LB_EALIGN
+        assert L.lb_step_segment(ctx, src, two, _arr(0x40000, 0x40000), 2,
+                                 last_state) == abi.LB_EINVAL
+        assert L.lb_step_segment(ctx, src, None, None, 0, last_state) == abi.LB_OK
+    finally:
+        L.lb_destroy(ctx)

@@ -217,3 +217,27 @@ def test_steps_of_one_call_are_those_of_many(shape, coupling, prec, tau_f):
     n = float(np.prod(shape))
     for t in range(3):
         assert np.abs(rows[t] - sums[2 + t]).max() <= n * n * 2.3e-16
+
+
+@pytest.mark.parametrize("coupling,prec", [("stress", "fp64"), ("force", "fp64"),
+                                           ("force", "fp32_dev")])
+@pytest.mark.parametrize("shape", [(34, 36, 40), (70, 48, 64)])
+def test_rollout_through_compact_levels(shape, coupling, prec):
+    """A rollout hands its levels on compact within a segment; with a
+    checkpoint at every step each segment is one step and every level full.
+    The same phi and gradients bit for bit."""
+    from paper_1609_01479_amd.rollout import rollout
+    print(f"[compact rollout] {shape} {coupling} {prec}", flush=True)
+    got = []
+    for interval in (1, 3, 7):
+        phi0 = torch.tensor(lbinputs.spinodal_phi0(shape, seed=5, amp=0.3), device="cuda:0",
+                            requires_grad=True)
+        theta = [torch.tensor(v, dtype=torch.float64, device="cuda:0", requires_grad=True)
+                 for v in (-0.00625, 0.00625, 0.004)]
+        phi = rollout(phi0, *theta, 7, interval=interval, precision=prec, coupling=coupling,
+                      tau_f=0.8)
+        grads = torch.autograd.grad((phi ** 2).sum(), [phi0] + theta)
+        got.append([phi.detach()] + list(grads))
+    for other in got[1:]:
+        for a, b in zip(got[0], other):
+            assert torch.equal(a, b)

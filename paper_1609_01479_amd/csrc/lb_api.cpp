@@ -354,24 +354,32 @@ static lb_status step_n(lb_ctx* ctx, int32_t nsteps, double* sums_dev, const cha
                                "are exchanged between steps); got nsteps = %d", nsteps);
     // the levels between this call's steps can be compact
     const bool between = nsteps > 1 && lbk::can_compact(ctx->kp, ctx->tc, ctx->fp32, ctx->p.kernel);
-    const size_t nb = !sums_dev ? 0 : between ? lbk::collide_grid(ctx->kp, true) : sums_blocks(ctx);
-    const int32_t batch = sums_dev ? int32_t(std::min<size_t>(rows / nb, 4096)) : 1;
-    int32_t held = 0;  // steps whose partials wait in part
+    const bool f_too = between && lbk::compact_f(ctx->kp, ctx->fp32, sums_dev != nullptr);
+    // partial blocks of step t
+    auto blocks = [&](int32_t t) -> size_t {
+        if (f_too && t > 0) return lbk::compact_step_tiles(ctx->kp, ctx->fp32).blocks();
+        return between ? lbk::collide_grid(ctx->kp, true) : sums_blocks(ctx);
+    };
+    int32_t held = 0;  // steps whose partials wait in part, nb blocks each
+    size_t nb = sums_dev ? blocks(0) : 0;
     for (int32_t t = 0; t < nsteps; t++) {
         const int compact = !between ? 0
                                      : (t > 0 ? lbk::kCompactSrc : 0) |
-                                           (t + 1 < nsteps ? lbk::kCompactDst : 0);
+                                           (t + 1 < nsteps ? lbk::kCompactDst : 0) |
+                                           (f_too ? lbk::kCompactF : 0);
         hipError_t e = one_step(ctx, ctx->b.state[ctx->cur], ctx->b.state[1 - ctx->cur],
                                 sums_dev ? part + size_t(held) * 5 * nb : nullptr, nullptr, compact);
         if (e != hipSuccess) return hip_fail(e, name);
         ctx->cur = 1 - ctx->cur;
         if (!sums_dev) continue;
         held++;
-        if (held < batch && t + 1 < nsteps) continue;
+        const size_t next = t < 1 && nsteps > 1 ? blocks(t + 1) : nb;
+        if (t + 1 < nsteps && next == nb && held < std::min<size_t>(rows / nb, 4096)) continue;
         e = lbk::launch_sums_final(part, int(nb), 5, held, sums_dev + 5 * size_t(t + 1 - held),
                                    ctx->stream);
         if (e != hipSuccess) return hip_fail(e, name);
         held = 0;
+        nb = next;
     }
     return LB_OK;
 }

@@ -9,10 +9,15 @@
 // every phi and every f is bit for bit that of full levels.  f stays as it is.
 // The levels that a call starts from and leaves are full.  Per site and step
 // that is 392 bytes instead of 608 in FP64 (and 208 of 312 in FP32 storage
-// with the force coupling): two passes, the first over five fields.  us per
-// step, full / compact: FP64 stress 90 x 75 x 100 86 / 49, 128^3 248 / 162,
-// 256^3 1830 / 1309; FP64 force 274 / 188 and 2083 / 1471, FP32 force 161 /
-// 126 and 1153 / 984.
+// with the force coupling): two passes, the first over five fields.
+//
+// With omega_f = 1 too, f* is f^eq, and ten moments take the place of its 19
+// populations: 248 bytes (FP32 storage 136).
+//
+// us per step, full / g compact / both: FP64 stress 90 x 75 x 100 86 / 49 /
+// 42, 128^3 248 / 162 / 126, 256^3 1830 / 1309 / 982; FP64 force 128^3 274 /
+// 188 / 174, 256^3 2083 / 1471 / 1345; FP32 force 128^3 161 / 126 / 106,
+// 256^3 1153 / 984.
 #pragma once
 
 #include "lb_device.h"
@@ -34,7 +39,34 @@ __host__ __device__ inline MuU<T>* compact_mu_u(T* G, const KParams& p)
     return reinterpret_cast<MuU<T>*>(compact_phi(G) + p.stride);
 }
 
+// Two of f^eq's moments of a site; five fields of them in the level's f region.
+template <typename T>
+struct alignas(2 * sizeof(T)) Pair {
+    T a, b;
+};
+
 namespace {
+
+template <typename T>
+__device__ __forceinline__ FEq<T> load_feq(const KParams& p, const T* __restrict__ F, int s)
+{
+    const Pair<T>* q = reinterpret_cast<const Pair<T>*>(F) + s;
+    const size_t n = p.stride;
+    const Pair<T> v0 = q[0], v1 = q[n], v2 = q[2 * n], v3 = q[3 * n], v4 = q[4 * n];
+    return FEq<T>{v0.a, v0.b, v1.a, v1.b, v2.a, v2.b, v3.a, v3.b, v4.a, v4.b};
+}
+
+template <typename T>
+__device__ __forceinline__ void store_feq(const KParams& p, T* __restrict__ F, int s, const FEq<T>& e)
+{
+    Pair<T>* q = reinterpret_cast<Pair<T>*>(F) + s;
+    const size_t n = p.stride;
+    q[0] = Pair<T>{e.b, e.ax};
+    q[n] = Pair<T>{e.ay, e.az};
+    q[2 * n] = Pair<T>{e.xx, e.yy};
+    q[3 * n] = Pair<T>{e.zz, e.xy};
+    q[4 * n] = Pair<T>{e.xz, e.yz};
+}
 
 // g*_i of a site (FP32 mode: its deviation h*) as collide_g<T, REF, true>
 // forms it (the same expressions, so that each rounds alike).
@@ -140,12 +172,12 @@ struct Pulled {
 // leave for the planes on either side wait in the destination's registers.
 // Bound by its arithmetic and LDS traffic together, with 8 waves between two
 // barriers: 256^3 239 us.
-template <typename T, bool REF, bool FORCE, int TY, int TZ>
-__global__ __launch_bounds__(((TY + 2) * (TZ + 2) + 63) / 64 * 64) void k_phi_compact_march(
+template <typename T, bool REF, bool FORCE>
+__global__ __launch_bounds__(kCompactThreads) void k_phi_compact_march(
     KParams p, int nty, int ntz, int sx, const double* __restrict__ cphi,
     const MuU<T>* __restrict__ mu_u, double* __restrict__ phi, unsigned* __restrict__ dphic)
 {
-    constexpr int BZ = TZ + 2, NC = (TY + 2) * BZ;
+    constexpr int TY = kCompactTY, TZ = kCompactTZ, BZ = TZ + 2, NC = (TY + 2) * BZ;
     __shared__ CompactLds<T, REF, NC> lds;
     const int blk = xcd_block();
     const int tile = blk % (nty * ntz), seg = blk / (nty * ntz);
@@ -231,43 +263,126 @@ __global__ __launch_bounds__(((TY + 2) * (TZ + 2) + 63) / 64 * 64) void k_phi_co
     }
 }
 
-// Planes per segment of the march: the least work per resident workgroup.
-inline int compact_segment(const KParams& p, int ntiles, int resident)
+// The collision pass from a compact level with f's moments, as a march of
+// k_phi_compact_march's tiles: each cell's f is formed once from its ten
+// moments and handed over in LDS (one site per thread would read ten values
+// from each of 19 sites).  Bound by memory where two workgroups share a CU
+// (256^3 FP64, 200 bytes per site: 743 us, 4.5 TB/s; the pass it replaces
+// 1073), with the force coupling by the chain of one.  TO_FULL: the new level
+// is full.  SUMS: block partials of the source level's conserved sums.
+template <typename T, bool DEV, bool REF, bool FORCE, bool TO_FULL, bool SUMS>
+__global__ __launch_bounds__(kCompactThreads) void k_step_compact_march(
+    KParams p, int nty, int ntz, int sx, const T* __restrict__ sF, const double* __restrict__ phi,
+    T* __restrict__ dF, T* __restrict__ dG, double* __restrict__ partials)
 {
-    int best = p.nx;
-    long long cost = -1;
-    for (int nseg = 1; nseg <= p.nx && nseg <= 2 * resident; nseg++) {
-        const int sx = (p.nx + nseg - 1) / nseg;
-        const long long n = (long long)ntiles * ((p.nx + sx - 1) / sx);
-        const long long c = (n + resident - 1) / resident * (sx + 2);
-        if (cost < 0 || c < cost) {
-            cost = c;
-            best = sx;
+    constexpr int TY = kCompactTY, TZ = kCompactTZ, BZ = TZ + 2, NC = (TY + 2) * BZ;
+    __shared__ T lds[NV - 3][NC];
+    const int blk = xcd_block();
+    const int tile = blk % (nty * ntz), seg = blk / (nty * ntz);
+    // the last tiles of a plane are shifted back to end with it
+    const int ey = p.ny < TY ? p.ny : TY, ez = p.nz < TZ ? p.nz : TZ;
+    const int y0 = min(tile / ntz * TY, p.ny - ey), z0 = min(tile % ntz * TZ, p.nz - ez);
+    const int x0 = seg * sx, x1 = min(x0 + sx, p.nx);
+    const int c = threadIdx.x, r = c / BZ, l = c - r * BZ;
+    const bool cell = c < NC;
+    const bool own = cell && r >= 1 && r <= ey && l >= 1 && l <= ez;
+    const int y = wrap_any(y0 + r - 1, p.ny), z = wrap_any(z0 + l - 1, p.nz);
+    const int col = y * p.nz + z, plane = p.ny * p.nz;
+    // a site that two tiles share counts in the first one's sums
+    const bool counts = own && y0 + r > tile / ntz * TY && z0 + l > tile % ntz * TZ;
+    double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    FEq<T> e{};
+    if (cell) e = load_feq(p, sF, (x0 == 0 ? p.nx - 1 : x0 - 1) * plane + col);
+    T up[2][5], mid[9];
+    constexpr int UP[5] = {1, 7, 9, 11, 13};
+    constexpr int MID[9] = {0, 3, 4, 5, 6, 15, 16, 17, 18};
+    for (int X = x0 - 1; X <= x1; X++) {
+        T h[NV];
+        hermite_f(e, h);
+        if (cell) {
+#pragma unroll
+            for (int i = 3; i < NV; i++) lds[i - 3][c] = h[i];
         }
+        if (cell && X < x1)  // the next plane, while this one is exchanged
+            e = load_feq(p, sF, (X + 1 >= p.nx ? X + 1 - p.nx : X + 1) * plane + col);
+        const bool here = own && X > x0;  // plane X - 1 is complete now
+        Stencil st{};
+        double F[3] = {0.0, 0.0, 0.0}, mu_d = 0.0;
+        const Geo q = geo_xyz(p, X > x0 ? X - 1 : x0, y, z);
+        if (here) {
+            const double v = phi[site_of(p, q.x, q.y, q.z)];
+            if constexpr (FORCE) {
+                const double lap = (phi[site_of(p, q.xp, q.y, q.z)] + phi[site_of(p, q.xm, q.y, q.z)] - 2.0 * v)
+                                 + (phi[site_of(p, q.x, q.yp, q.z)] + phi[site_of(p, q.x, q.ym, q.z)] - 2.0 * v)
+                                 + (phi[site_of(p, q.x, q.y, q.zp)] + phi[site_of(p, q.x, q.y, q.zm)] - 2.0 * v);
+                mu_d = p.A * v + p.B * v * v * v - p.kappa * lap;
+                force_from_phi(p, q, phi, F);
+                st.phi = v;
+            } else {
+                st = stencil(v, phi[site_of(p, q.xp, q.y, q.z)], phi[site_of(p, q.xm, q.y, q.z)],
+                             phi[site_of(p, q.x, q.yp, q.z)], phi[site_of(p, q.x, q.ym, q.z)],
+                             phi[site_of(p, q.x, q.y, q.zp)], phi[site_of(p, q.x, q.y, q.zm)]);
+            }
+        }
+        lds_barrier();
+        if (own) {
+            auto pull = [&](int i) { return lds[i - 3][c - (CY[i] * BZ + CZ[i])]; };
+            T down[5];
+            down[0] = h[2];
+#pragma unroll
+            for (int k = 1; k < 5; k++) down[k] = pull(UP[k] + 1);
+            if (here) {
+                T f[NV];
+                f[0] = mid[0];
+#pragma unroll
+                for (int k = 0; k < 5; k++) {
+                    f[UP[k]] = up[0][k];
+                    f[UP[k] + 1] = down[k];
+                }
+#pragma unroll
+                for (int k = 1; k < 9; k++) f[MID[k]] = mid[k];
+                if (SUMS && counts) site_sums<DEV>(p, f, st.phi, FORCE ? F : nullptr, acc);
+                FEq<T> d;
+                Vel<T> u;
+                T mu;
+                if constexpr (FORCE) {
+                    u = feq_force<T, DEV>(p, f, F, d);
+                    mu = T(mu_d);
+                } else {
+                    u = feq_stress<T, DEV>(p, f, st, d);
+                    mu = chem_potential<T>(p, st);
+                }
+                if constexpr (TO_FULL) {
+                    T g[NV];
+                    hermite_f(d, f);
+#pragma unroll
+                    for (int i = 0; i < NV; i++) dF[dist_own(p, q, i)] = f[i];
+                    if constexpr (FORCE)
+                        collide_force_g<T, REF, true>(p, g, st.phi, mu_d, u);
+                    else
+                        collide_g<T, REF, true>(p, g, T(st.phi), mu, u);
+#pragma unroll
+                    for (int i = 0; i < NV; i++)
+                        dG[dist_own(p, q, i)] =
+                            REF ? to_dest_ref(i, g[i], st.phi, phi[push_site(p, q, i)]) : g[i];
+                } else {
+                    const int s = (X - 1) * plane + col;
+                    store_feq(p, dF, s, d);
+                    compact_mu_u(dG, p)[s] = MuU<T>{mu, u.x, u.y, u.z};
+                }
+            }
+            mid[0] = h[0];
+#pragma unroll
+            for (int k = 1; k < 9; k++) mid[k] = pull(MID[k]);
+#pragma unroll
+            for (int k = 0; k < 5; k++) {
+                up[0][k] = up[1][k];
+                up[1][k] = k ? pull(UP[k]) : h[1];
+            }
+        }
+        lds_barrier();
     }
-    return best;
-}
-
-// The march's tile: 12 x 32 sites and their ring are 8 waves of cells, two
-// workgroups of which fill a CU's LDS in FP64 (us per step of 256^3 FP64, the
-// collision's 1073 included: 8 x 64 1312, 8 x 48 1310, 4 x 64 1323, 16 x 32
-// 1335, 12 x 32 1312; of 151 x 105 x 150 207, 203, 210, 208, 199).
-constexpr int kCompactTY = 12, kCompactTZ = 32;
-constexpr int kCompactThreads = ((kCompactTY + 2) * (kCompactTZ + 2) + 63) / 64 * 64;
-constexpr int kCompactResident = 2 * 256;
-
-// The march runs on lattices that fill it, of at least 4 planes, and that its
-// tiles cover with at most 3/4 more cells than sites.  us per step, one site
-// per thread / march: FP64 stress 48^3 14.1 / 14.2, 60 x 52 x 70 23.8 / 21.5,
-// 96^3 87 / 70; FP64 force 56^3 21.0 / 21.7, 60 x 52 x 70 25.4 / 24.4, 96^3
-// 104 / 91; FP32 force 80^3 31.9 / 33.2, 90 x 75 x 100 41.0 / 40.6, 128^3
-// 143 / 127; 300 x 40 x 20, 1.9 cells per site, FP64 force 25.7 / 26.5.
-template <typename T, bool FORCE>
-bool compact_march(const KParams& p, int ntiles)
-{
-    const long long plane = (long long)p.ny * p.nz;
-    const int limit = sizeof(T) == 4 ? 650000 : FORCE ? 200000 : 160000;
-    return p.nsites >= limit && p.nx >= 4 && 4LL * ntiles * kCompactTY * kCompactTZ <= 7 * plane;
+    if (SUMS) block_partials<5, kCompactThreads>(acc, partials);
 }
 
 // phi of the compact level `state`, its own phi field cphi if that is given;
@@ -280,19 +395,34 @@ hipError_t launch_phi_compact_t(const KParams& p, const void* state, const doubl
     T* G = level<T>(const_cast<void*>(state), p, F32).G;
     if (!cphi) cphi = compact_phi(G);
     unsigned* dphic = next ? level<T>(next, p, F32).phic : nullptr;
-    const int nty = (p.ny + kCompactTY - 1) / kCompactTY;
-    const int ntz = (p.nz + kCompactTZ - 1) / kCompactTZ;
-    if (compact_march<T, FORCE>(p, nty * ntz)) {
-        const int sx = compact_segment(p, nty * ntz, kCompactResident);
-        const int nseg = (p.nx + sx - 1) / sx;
-        k_phi_compact_march<T, F32, FORCE, kCompactTY, kCompactTZ>
-            <<<nty * ntz * nseg, kCompactThreads, 0, s>>>(p, nty, ntz, sx, cphi, compact_mu_u(G, p),
-                                                          phi, dphic);
+    const CompactTiles t = compact_tiles(p, kCompactResident);
+    if (compact_march(p, F32)) {
+        k_phi_compact_march<T, F32, FORCE>
+            <<<t.blocks(), kCompactThreads, 0, s>>>(
+                p, t.nty, t.ntz, t.sx, cphi, compact_mu_u(G, p), phi, dphic);
     } else {
         const int nb = site_block(p);
         k_phi_compact<T, F32, FORCE><<<(p.nsites + nb - 1) / nb, nb, 0, s>>>(
             p, cphi, compact_mu_u(G, p), phi, dphic);
     }
+    return hipGetLastError();
+}
+
+// A step's collision pass from the compact level src with f's moments; phi:
+// that level's phi.
+template <typename T, bool FORCE>
+hipError_t launch_step_compact_t(const KParams& p, const void* src, void* dst, bool to_full,
+                                 const double* phi, double* partials, hipStream_t s)
+{
+    constexpr bool F32 = sizeof(T) == 4;
+    const T* F = level<T>(const_cast<void*>(src), p, F32).F;
+    Lvl<T> d = level<T>(dst, p, F32);
+    const CompactTiles t = compact_step_tiles(p, F32);
+    auto k = partials ? to_full ? k_step_compact_march<T, F32, F32, FORCE, true, true>
+                                : k_step_compact_march<T, F32, F32, FORCE, false, true>
+             : to_full ? k_step_compact_march<T, F32, F32, FORCE, true, false>
+                       : k_step_compact_march<T, F32, F32, FORCE, false, false>;
+    k<<<t.blocks(), kCompactThreads, 0, s>>>(p, t.nty, t.ntz, t.sx, F, phi, d.F, d.G, partials);
     return hipGetLastError();
 }
 

@@ -294,35 +294,24 @@ struct Vel {
     T x, y, z;
 };
 
-template <typename T, bool DEV>
-__device__ __forceinline__ Vel<T> collide_f(const KParams& p, T* f, const Stencil& st)
+// f^eq_i = w [b + 3 c.a + 9/2 (c c - I/3):M]: what the collision makes of a
+// site before it relaxes (with omega_f = 1: the collided f).
+template <typename T>
+struct FEq {
+    T b, ax, ay, az, xx, yy, zz, xy, xz, yz;
+};
+
+template <typename T>
+__device__ __forceinline__ void hermite_f(const FEq<T>& e, T* eq)
 {
-    const T A = T(p.A), B = T(p.B), kap = T(p.kappa);
-    const T omf = T(p.omega_f);
-    const T phi = T(st.phi), gx = T(st.gx), gy = T(st.gy), gz = T(st.gz), lap = T(st.lap);
-    const T phi2 = phi * phi;
-    const T iso = T(0.5) * A * phi2 + T(0.75) * B * phi2 * phi2 - kap * phi * lap
-                - T(0.5) * kap * (gx * gx + gy * gy + gz * gz);
-
-    const Moments<T> m = moments_of<T, DEV>(p, f);
-    const T b = m.b, jx = m.jx, jy = m.jy, jz = m.jz;
-    const T ri = T(1) / m.rho;
-    const T ux = jx * ri, uy = jy * ri, uz = jz * ri;
-
-    // M = Pi + rho u u
-    const T mxx = iso + kap * gx * gx + jx * ux;
-    const T myy = iso + kap * gy * gy + jy * uy;
-    const T mzz = iso + kap * gz * gz + jz * uz;
-    const T mxy = kap * gx * gy + jx * uy;
-    const T mxz = kap * gx * gz + jx * uz;
-    const T myz = kap * gy * gz + jy * uz;
+    const T b = e.b, jx = e.ax, jy = e.ay, jz = e.az;
+    const T mxx = e.xx, myy = e.yy, mzz = e.zz, mxy = e.xy, mxz = e.xz, myz = e.yz;
     const T tm = (mxx + myy + mzz) * T(1.0 / 3.0);
 
     const T h = T(4.5);
     const T w0 = T(weight(0)), wf = T(weight(1)), we = T(weight(7));
     const T wf3 = T(3.0 * weight(1)), we3 = T(3.0 * weight(7));
 
-    T eq[NV];
     eq[0] = w0 * (b - h * tm);
     {
         const T sx = wf * (b + h * (mxx - tm)), ax = wf3 * jx;
@@ -347,9 +336,48 @@ __device__ __forceinline__ Vel<T> collide_f(const KParams& p, T* f, const Stenci
         eq[15] = s15 + a15;  eq[16] = s15 - a15;
         eq[17] = s17 + a17;  eq[18] = s17 - a17;
     }
-#pragma unroll
-    for (int i = 0; i < NV; i++) f[i] += omf * (eq[i] - f[i]);
+}
+
+// The stress coupling's f^eq (a = j, M = Pi + rho u u); returns u = j/rho.
+template <typename T, bool DEV>
+__device__ __forceinline__ Vel<T> feq_stress(const KParams& p, const T* f, const Stencil& st,
+                                            FEq<T>& e)
+{
+    const T A = T(p.A), B = T(p.B), kap = T(p.kappa);
+    const T phi = T(st.phi), gx = T(st.gx), gy = T(st.gy), gz = T(st.gz), lap = T(st.lap);
+    const T phi2 = phi * phi;
+    const T iso = T(0.5) * A * phi2 + T(0.75) * B * phi2 * phi2 - kap * phi * lap
+                - T(0.5) * kap * (gx * gx + gy * gy + gz * gz);
+
+    const Moments<T> m = moments_of<T, DEV>(p, f);
+    const T b = m.b, jx = m.jx, jy = m.jy, jz = m.jz;
+    const T ri = T(1) / m.rho;
+    const T ux = jx * ri, uy = jy * ri, uz = jz * ri;
+
+    // M = Pi + rho u u
+    const T mxx = iso + kap * gx * gx + jx * ux;
+    const T myy = iso + kap * gy * gy + jy * uy;
+    const T mzz = iso + kap * gz * gz + jz * uz;
+    const T mxy = kap * gx * gy + jx * uy;
+    const T mxz = kap * gx * gz + jx * uz;
+    const T myz = kap * gy * gz + jy * uz;
+    e = FEq<T>{b, jx, jy, jz, mxx, myy, mzz, mxy, mxz, myz};
     return Vel<T>{ux, uy, uz};
+}
+
+template <typename T, bool DEV>
+__device__ __forceinline__ Vel<T> collide_f(const KParams& p, T* f, const Stencil& st)
+{
+    FEq<T> e;
+    const Vel<T> u = feq_stress<T, DEV>(p, f, st, e);
+    T eq[NV];
+    hermite_f(e, eq);
+    const T omf = T(p.omega_f);
+    // FP64 with omega_f = 1: f* = f^eq, as a compact level keeps it
+    const bool one = !DEV && omf == T(1);
+#pragma unroll
+    for (int i = 0; i < NV; i++) f[i] = one ? eq[i] : f[i] + omf * (eq[i] - f[i]);
+    return u;
 }
 
 // G1 (omega_g = 1): g* = g^eq, with no term in the pre-collision g.
@@ -460,7 +488,8 @@ __device__ __forceinline__ void chem_stress(const KParams& p, const Stencil& st,
 // one from the odd, then f*_i = (1 - omega_f) f_i + that (about half the
 // arithmetic of evaluating the two sums direction by direction).
 template <typename T, bool DEV>
-__device__ __forceinline__ Vel<T> collide_force_f(const KParams& p, T* f, const double Fd[3])
+__device__ __forceinline__ Vel<T> feq_force(const KParams& p, const T* f, const double Fd[3],
+                                           FEq<T>& e)
 {
     const Moments<T> m = moments_of<T, DEV>(p, f);
     const T F[3] = {T(Fd[0]), T(Fd[1]), T(Fd[2])};
@@ -481,39 +510,21 @@ __device__ __forceinline__ Vel<T> collide_force_f(const KParams& p, T* f, const 
     const T mxy = orho * ux * uy + (pux * F[1] + puy * F[0]);
     const T mxz = orho * ux * uz + (pux * F[2] + puz * F[0]);
     const T myz = orho * uy * uz + (puy * F[2] + puz * F[1]);
-    const T tm = (mxx + myy + mzz) * T(1.0 / 3.0);
-    const T h = T(4.5);
-    const T w0 = T(weight(0)), wf = T(weight(1)), we = T(weight(7));
-    const T wf3 = T(3.0 * weight(1)), we3 = T(3.0 * weight(7));
+    e = FEq<T>{ob, ax, ay, az, mxx, myy, mzz, mxy, mxz, myz};
+    return Vel<T>{ux, uy, uz};
+}
+
+template <typename T, bool DEV>
+__device__ __forceinline__ Vel<T> collide_force_f(const KParams& p, T* f, const double Fd[3])
+{
+    FEq<T> e;
+    const Vel<T> u = feq_force<T, DEV>(p, f, Fd, e);
     T x[NV];
-    x[0] = w0 * (ob - h * tm);
-    {
-        const T sx = wf * (ob + h * (mxx - tm)), vx = wf3 * ax;
-        const T sy = wf * (ob + h * (myy - tm)), vy = wf3 * ay;
-        const T sz = wf * (ob + h * (mzz - tm)), vz = wf3 * az;
-        x[1] = sx + vx; x[2] = sx - vx;
-        x[3] = sy + vy; x[4] = sy - vy;
-        x[5] = sz + vz; x[6] = sz - vz;
-    }
-    {
-        const T dxy = mxx + myy - tm, dxz = mxx + mzz - tm, dyz = myy + mzz - tm;
-        const T s7 = we * (ob + h * (dxy + T(2) * mxy)), v7 = we3 * (ax + ay);
-        const T s9 = we * (ob + h * (dxy - T(2) * mxy)), v9 = we3 * (ax - ay);
-        const T s11 = we * (ob + h * (dxz + T(2) * mxz)), v11 = we3 * (ax + az);
-        const T s13 = we * (ob + h * (dxz - T(2) * mxz)), v13 = we3 * (ax - az);
-        const T s15 = we * (ob + h * (dyz + T(2) * myz)), v15 = we3 * (ay + az);
-        const T s17 = we * (ob + h * (dyz - T(2) * myz)), v17 = we3 * (ay - az);
-        x[7] = s7 + v7;     x[8] = s7 - v7;
-        x[9] = s9 + v9;     x[10] = s9 - v9;
-        x[11] = s11 + v11;  x[12] = s11 - v11;
-        x[13] = s13 + v13;  x[14] = s13 - v13;
-        x[15] = s15 + v15;  x[16] = s15 - v15;
-        x[17] = s17 + v17;  x[18] = s17 - v17;
-    }
-    const T cf = T(1) - omf;
+    hermite_f(e, x);
+    const T cf = T(1) - T(p.omega_f);
 #pragma unroll
     for (int i = 0; i < NV; i++) f[i] = cf * f[i] + x[i];
-    return Vel<T>{ux, uy, uz};
+    return u;
 }
 
 // G1 (omega_g = 1): g* = g^eq, with no term in the pre-collision g, which

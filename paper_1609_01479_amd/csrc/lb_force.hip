@@ -32,8 +32,8 @@ namespace {
 // The force-coupling collision and propagation, one site per thread; phi of
 // the source level (all sites) comes from k_phi.  SUMS: block partials of
 // [rho, phi, j + F/2] of the source level (0, or the block size).  COMPACT:
-// the new level is compact (lb_compact.h).
-template <typename T, bool DEV, bool REF, bool G1, int SUMS, bool COMPACT = false>
+// 1: the new level is compact (lb_compact.h); 2: with f's moments.
+template <typename T, bool DEV, bool REF, bool G1, int SUMS, int COMPACT = 0>
 __global__ __launch_bounds__(kBlock) void k_step_force(KParams p, const T* __restrict__ sF,
                                                        const T* __restrict__ sG,
                                                        const unsigned* __restrict__ sphic,
@@ -63,7 +63,13 @@ __global__ __launch_bounds__(kBlock) void k_step_force(KParams p, const T* __res
         double F[3];
         force_from_phi(p, q, phi, F);
         if (SUMS) site_sums<DEV>(p, f, c, F, acc);
-        if constexpr (COMPACT) {
+        if constexpr (COMPACT == 2) {
+            FEq<T> e;
+            const Vel<T> u = feq_force<T, DEV>(p, f, F, e);
+            compact_mu_u(dG, p)[s] = MuU<T>{T(mu), u.x, u.y, u.z};
+            store_feq(p, dF, s, e);
+            return;
+        } else if constexpr (COMPACT == 1) {
             const Vel<T> u = collide_force_f<T, DEV>(p, f, F);
             compact_mu_u(dG, p)[s] = MuU<T>{T(mu), u.x, u.y, u.z};
         } else {
@@ -342,7 +348,7 @@ __global__ __launch_bounds__(kForceFused) void k_force_fused(KParams p, TileCfg 
 }
 
 // k_step_force of a storage type by what it reduces and its block
-template <typename T, bool G1, bool COMPACT>
+template <typename T, bool G1, int COMPACT>
 decltype(&k_step_force<T, false, false, G1, 0, COMPACT>) pick_step_force(bool sums, int nb)
 {
     constexpr bool F32 = std::is_same<T, float>::value;
@@ -402,7 +408,7 @@ int force_sums_blocks(const KParams& p, int seg_req)
 }
 
 hipError_t launch_force_collide(const KParams& p, const TileCfg& tc, bool fp32, int variant,
-                                bool compact, const void* src, void* dst, double* phi,
+                                int compact, const void* src, void* dst, double* phi,
                                 double* partials, hipStream_t s)
 {
     const TileCfg ft = force_tiles(p, tc.seg_req);
@@ -420,9 +426,10 @@ hipError_t launch_force_collide(const KParams& p, const TileCfg& tc, bool fp32, 
                         : pick_force_fused<float, false>(g1, partials);
             k<<<nft, kForceFused, 0, s>>>(p, ft, a.F, a.G, a.phic, d.phic, phi, d.F, d.G, partials);
         } else {
-            auto k = compact ? pick_step_force<float, true, true>(partials, nb)
-                     : g1    ? pick_step_force<float, true, false>(partials, nb)
-                             : pick_step_force<float, false, false>(partials, nb);
+            auto k = compact == 2   ? pick_step_force<float, true, 2>(partials, nb)
+                     : compact == 1 ? pick_step_force<float, true, 1>(partials, nb)
+                     : g1           ? pick_step_force<float, true, 0>(partials, nb)
+                                    : pick_step_force<float, false, 0>(partials, nb);
             k<<<collide_grid(p, partials), nb, 0, s>>>(p, a.F, a.G, a.phic, phi, d.F, d.G, partials);
         }
     } else {
@@ -434,9 +441,10 @@ hipError_t launch_force_collide(const KParams& p, const TileCfg& tc, bool fp32, 
             k<<<nft, kForceFused, 0, s>>>(p, ft, a.F, a.G, nullptr, nullptr, phi, d.F, d.G,
                                           partials);
         } else {
-            auto k = compact ? pick_step_force<double, true, true>(partials, nb)
-                     : g1    ? pick_step_force<double, true, false>(partials, nb)
-                             : pick_step_force<double, false, false>(partials, nb);
+            auto k = compact == 2   ? pick_step_force<double, true, 2>(partials, nb)
+                     : compact == 1 ? pick_step_force<double, true, 1>(partials, nb)
+                     : g1           ? pick_step_force<double, true, 0>(partials, nb)
+                                    : pick_step_force<double, false, 0>(partials, nb);
             k<<<collide_grid(p, partials), nb, 0, s>>>(p, a.F, a.G, a.phic, phi, d.F, d.G, partials);
         }
     }
@@ -448,6 +456,14 @@ hipError_t launch_phi_compact_force(const KParams& p, bool fp32, const void* sta
 {
     return fp32 ? launch_phi_compact_t<float, true>(p, state, cphi, phi, next, s)
                 : launch_phi_compact_t<double, true>(p, state, cphi, phi, next, s);
+}
+
+hipError_t launch_step_compact_force(const KParams& p, bool fp32, const void* src, void* dst,
+                                     bool to_full, const double* phi, double* partials,
+                                     hipStream_t s)
+{
+    return fp32 ? launch_step_compact_t<float, true>(p, src, dst, to_full, phi, partials, s)
+                : launch_step_compact_t<double, true>(p, src, dst, to_full, phi, partials, s);
 }
 
 }  // namespace lbk

@@ -107,19 +107,45 @@ hipError_t launch_step(const KParams& p, const TileCfg& tc, bool fp32, int varia
 // (lb_compact.h); launch_step's `compact`: kCompactSrc if src is compact (its
 // phi in compact_src_phi if that is given: the phi_src_out of the step that
 // made it), kCompactDst if dst is to be.
-constexpr int kCompactSrc = 1, kCompactDst = 2;
+// kCompactF: those compact levels hold f's moments, too (compact_f).
+constexpr int kCompactSrc = 1, kCompactDst = 2, kCompactF = 4;
+bool compact_f(const KParams& p, bool fp32, bool sums);
 bool can_compact(const KParams& p, const TileCfg& tc, bool fp32, int variant);
 hipError_t launch_phi_compact_f64(const KParams& p, const void* state, const double* cphi,
                                   double* phi, hipStream_t s);
 hipError_t launch_phi_compact_force(const KParams& p, bool fp32, const void* state,
                                     const double* cphi, double* phi, void* next, hipStream_t s);
+// The march's tile: 12 x 32 sites and their ring are 8 waves of cells, two
+// workgroups of which fill a CU's LDS in FP64 (us per step of 256^3 FP64, the
+// collision's 1073 included: 8 x 64 1312, 8 x 48 1310, 4 x 64 1323, 16 x 32
+// 1335, 12 x 32 1312; of 151 x 105 x 150 207, 203, 210, 208, 199).
+constexpr int kCompactTY = 12, kCompactTZ = 32;
+constexpr int kCompactThreads = ((kCompactTY + 2) * (kCompactTZ + 2) + 63) / 64 * 64;
+constexpr int kCompactResident = 2 * 256;
+
+
+// The march's tiles along y and z, and its segments of sx planes.
+struct CompactTiles {
+    int nty, ntz, sx, nseg;
+    int blocks() const { return nty * ntz * nseg; }
+};
+CompactTiles compact_tiles(const KParams& p, int resident);
+// Those of the collision pass.
+CompactTiles compact_step_tiles(const KParams& p, bool fp32);
+// Whether the phi pass from a compact level marches.
+bool compact_march(const KParams& p, bool fp32);
+hipError_t launch_step_compact_f64(const KParams& p, const void* src, void* dst, bool to_full,
+                                   const double* phi, double* partials, hipStream_t s);
+hipError_t launch_step_compact_force(const KParams& p, bool fp32, const void* src, void* dst,
+                                     bool to_full, const double* phi, double* partials,
+                                     hipStream_t s);
 // launch_step's kernels of the stress coupling, by storage precision; phi64
 // is the field that variant 1's phi pass left.  launch_phi_*: phi of `state`,
 // and if `next` is not null the phi_c of that level (FP32 mode).
-hipError_t launch_step_f32(const KParams& p, const TileCfg& tc, int variant, bool compact,
+hipError_t launch_step_f32(const KParams& p, const TileCfg& tc, int variant, int compact,
                            const void* src, void* dst, double* phi64, double* partials,
                            double* phi_src_out, hipStream_t s);
-hipError_t launch_step_f64(const KParams& p, const TileCfg& tc, int variant, bool compact,
+hipError_t launch_step_f64(const KParams& p, const TileCfg& tc, int variant, int compact,
                            const void* src, void* dst, double* phi64, double* partials,
                            double* phi_src_out, hipStream_t s);
 hipError_t launch_phi_f32(const KParams& p, const void* state, double* phi, void* next,
@@ -136,7 +162,7 @@ hipError_t launch_phi_f64(const KParams& p, const void* state, double* phi, void
 // src in `phi` and dst's phi_c, one site per thread, Pi formed at each face
 // neighbour (partials: one block per kBlock sites).  Bit-identical levels.
 hipError_t launch_force_collide(const KParams& p, const TileCfg& tc, bool fp32, int variant,
-                                bool compact, const void* src, void* dst, double* phi, double* partials,
+                                int compact, const void* src, void* dst, double* phi, double* partials,
                                 hipStream_t s);
 int force_sums_blocks(const KParams& p, int seg_req);
 // phi(x) of the post-propagation state held in `state`.

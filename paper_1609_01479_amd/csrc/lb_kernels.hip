@@ -5,6 +5,8 @@
 // tiling.  The step's own kernels are in lb_step.h (the stress coupling),
 // lb_force.hip (the force coupling) and lb_fd.hip (the finite-difference
 // order parameter).
+#include <algorithm>
+
 #include "lb_compact.h"
 #include "lb_device.h"
 #include "lb_sweep.h"
@@ -382,6 +384,68 @@ hipError_t launch_init(const KParams& p, bool fp32, void* state, const double* p
     return hipGetLastError();
 }
 
+// The march's segments: the least planes' work for as many segments as fill
+// the resident workgroups k times.
+CompactTiles compact_tiles(const KParams& p, int resident)
+{
+    CompactTiles t;
+    t.nty = (p.ny + kCompactTY - 1) / kCompactTY;
+    t.ntz = (p.nz + kCompactTZ - 1) / kCompactTZ;
+    const int tiles = t.nty * t.ntz;
+    long long cost = -1;
+    for (int k = 1; k <= 8; k++) {
+        const int want = std::min(p.nx, std::max(1, k * resident / tiles));
+        const int sx = (p.nx + want - 1) / want;
+        const int n = (p.nx + sx - 1) / sx;
+        const long long c = ((long long)tiles * n + resident - 1) / resident
+                          * (sx + 2);
+        if (cost >= 0 && c >= cost) continue;
+        cost = c;
+        t.sx = sx;
+        t.nseg = n;
+    }
+    return t;
+}
+
+// with the force coupling in FP64 one workgroup per CU, by its registers
+CompactTiles compact_step_tiles(const KParams& p, bool fp32)
+{
+    return compact_tiles(p, p.force && !fp32 ? kCompactResident / 2 : kCompactResident);
+}
+
+// The march runs on lattices that fill it, of at least 4 planes, and that its
+// tiles cover with at most 3/4 more cells than sites.  us per step, one site
+// per thread / march: FP64 stress 48^3 14.1 / 14.2, 60 x 52 x 70 23.8 / 21.5,
+// 96^3 87 / 70; FP64 force 56^3 21.0 / 21.7, 60 x 52 x 70 25.4 / 24.4, 96^3
+// 104 / 91; FP32 force 80^3 31.9 / 33.2, 90 x 75 x 100 41.0 / 40.6, 128^3
+// 143 / 127; 300 x 40 x 20, 1.9 cells per site, FP64 force 25.7 / 26.5.
+bool compact_march(const KParams& p, bool fp32)
+{
+    const CompactTiles t = compact_tiles(p, kCompactResident);
+    const long long plane = (long long)p.ny * p.nz;
+    const int limit = fp32 ? 650000 : p.force ? 200000 : 160000;
+    return p.nsites >= limit && p.nx >= 4 && 4LL * t.nty * t.ntz * kCompactTY * kCompactTZ <= 7 * plane;
+}
+
+// Where f's ten moments between steps beat the 19 populations.  Their pass is
+// a march, with the force coupling of one workgroup per CU (its F needs 160
+// registers; with sums also in FP32 storage), which loses to one site per
+// thread in small or ill-covered lattices.  us per step, populations /
+// moments: FP64 stress 64^3 22.2 / 22.1, 7 x 200 x 300 33.1 / 33.4, 90 x 75 x
+// 100 49 / 42, 128^3 162 / 126, 256^3 1311 / 982; FP64 force 90 x 75 x 100
+// (1.4 cells per site) 54 / 62, 96^3 91 / 61, 128^3 188 / 174, 256^3 1472 /
+// 1345; FP32 force 72 x 111 x 150 64 / 73, 128^3 126 / 106 (with sums 122 /
+// 128), 192^3 417 / 417, 256^3 919 / 926.
+bool compact_f(const KParams& p, bool fp32, bool sums)
+{
+    if (p.omega_f != 1.0 || !compact_march(p, fp32)) return false;
+    const CompactTiles t = compact_step_tiles(p, fp32);
+    if (sums && t.blocks() > kMaxStepPartials) return false;
+    if (!p.force) return p.nsites >= 450000;
+    if (4LL * t.nty * t.ntz * kCompactTY * kCompactTZ > 5LL * p.ny * p.nz) return false;
+    return fp32 ? !sums && p.nsites >= 1500000 && p.nsites < 5000000 : p.nsites >= 800000;
+}
+
 // Not FP32 storage with the stress coupling: its collision forms g + (g^eq -
 // g), which rounds with g.  Below 40000 sites the launches set the time, and
 // the compact phi pass's are the longer ones (us per step, full / compact:
@@ -417,11 +481,15 @@ hipError_t launch_step(const KParams& p, const TileCfg& tc, bool fp32, int varia
                      : launch_phi_f64(p, src, phi64, dst, s);
         if (e != hipSuccess) return e;
     }
+    if ((compact & kCompactF) && (compact & kCompactSrc))
+        return p.force ? launch_step_compact_force(p, fp32, src, dst, !to_compact, phi64, partials, s)
+                       : launch_step_compact_f64(p, src, dst, !to_compact, phi64, partials, s);
+    const int form = !to_compact ? 0 : compact & kCompactF ? 2 : 1;
     if (p.force)
-        return launch_force_collide(p, tc, fp32, variant, to_compact, src, dst,
+        return launch_force_collide(p, tc, fp32, variant, form, src, dst,
                                     variant == 1 ? phi64 : phi_src_out, partials, s);
     auto step = fp32 ? launch_step_f32 : launch_step_f64;
-    return step(p, tc, variant, to_compact, src, dst, phi64, partials, phi_src_out, s);
+    return step(p, tc, variant, form, src, dst, phi64, partials, phi_src_out, s);
 }
 
 hipError_t launch_phi(const KParams& p, bool fp32, const void* state, double* phi, hipStream_t s)

@@ -68,9 +68,10 @@ __global__ __launch_bounds__(kBlock) void k_phi(KParams p, const T* __restrict__
 // comes from k_phi.  G1 (FP64, omega_g = 1): g* = g^eq, so the collision
 // loads no g and the two passes move the single pass's 608 bytes per site
 // plus phi (776 otherwise).  SUMS: 0, or the block size, for block partials
-// of the source level's conserved sums.  COMPACT: the new level is compact
-// (lb_compact.h), its phi this step's phi field, written by the phi pass.
-template <typename T, bool DEV, bool REF, bool G1, int SUMS, bool COMPACT = false>
+// of the source level's conserved sums.  COMPACT: 1: the new level is compact
+// (lb_compact.h), its phi this step's phi field, written by the phi pass; 2:
+// with f's moments.
+template <typename T, bool DEV, bool REF, bool G1, int SUMS, int COMPACT = 0>
 __global__ __launch_bounds__(kBlock) void k_step_2s(KParams p, const T* __restrict__ sF,
                                                     const T* __restrict__ sG,
                                                     const unsigned* __restrict__ sphic,
@@ -97,7 +98,13 @@ __global__ __launch_bounds__(kBlock) void k_step_2s(KParams p, const T* __restri
 #pragma unroll
             for (int i = 0; i < NV; i++) g[i] = pre_collision_dev(i, g[i], dphi);
         }
-        if constexpr (COMPACT) {
+        if constexpr (COMPACT == 2) {
+            FEq<T> e;
+            const Vel<T> u = feq_stress<T, DEV>(p, f, st, e);
+            compact_mu_u(dG, p)[s] = MuU<T>{chem_potential<T>(p, st), u.x, u.y, u.z};
+            store_feq(p, dF, s, e);
+            return;
+        } else if constexpr (COMPACT == 1) {
             const Vel<T> u = collide_f<T, DEV>(p, f, st);
             compact_mu_u(dG, p)[s] = MuU<T>{chem_potential<T>(p, st), u.x, u.y, u.z};
         } else {
@@ -596,7 +603,7 @@ template <typename T>
 struct Fused;
 
 // k_step_2s of a storage type by what it reduces and its block.
-template <typename T, bool G1, bool COMPACT>
+template <typename T, bool G1, int COMPACT>
 decltype(&k_step_2s<T, false, false, G1, 0, COMPACT>) pick_2s(bool sums, int nb)
 {
     constexpr bool F32 = std::is_same<T, float>::value;
@@ -608,7 +615,7 @@ decltype(&k_step_2s<T, false, false, G1, 0, COMPACT>) pick_2s(bool sums, int nb)
 // The step of one storage precision.  variant: 0 march, 1 two passes (phi64:
 // the phi field between them), 2 the march's free-streaming twin.
 template <typename T>
-hipError_t launch_step_t(const KParams& p, const TileCfg& tc, int variant, bool compact,
+hipError_t launch_step_t(const KParams& p, const TileCfg& tc, int variant, int compact,
                          const void* src, void* dst, double* phi64, double* partials,
                          double* phi_src_out, hipStream_t s)
 {
@@ -619,9 +626,10 @@ hipError_t launch_step_t(const KParams& p, const TileCfg& tc, int variant, bool 
     const bool g1 = CAN_G1 && p.omega_g == 1.0;
     if (variant == 1) {
         const int nb = site_block(p);
-        auto k = compact && g1 ? pick_2s<T, CAN_G1, CAN_G1>(partials, nb)
-                 : g1          ? pick_2s<T, CAN_G1, false>(partials, nb)
-                               : pick_2s<T, false, false>(partials, nb);
+        auto k = compact == 2   ? pick_2s<T, CAN_G1, CAN_G1 ? 2 : 0>(partials, nb)
+                 : compact == 1 ? pick_2s<T, CAN_G1, CAN_G1 ? 1 : 0>(partials, nb)
+                 : g1           ? pick_2s<T, CAN_G1, 0>(partials, nb)
+                                : pick_2s<T, false, 0>(partials, nb);
         k<<<collide_grid(p, partials), nb, 0, s>>>(p, a.F, a.G, a.phic, phi64, d.F, d.G, partials);
     } else {
         const bool small = size_t(NV) * p.stride * sizeof(T) < (size_t(1) << 32);

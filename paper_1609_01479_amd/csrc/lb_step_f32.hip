@@ -40,7 +40,7 @@ struct Fused<float> {
 
 }  // namespace
 
-hipError_t launch_step_f32(const KParams& p, const TileCfg& tc, int variant, bool compact,
+hipError_t launch_step_f32(const KParams& p, const TileCfg& tc, int variant, int compact,
                            const void* src, void* dst, double* phi64, double* partials,
                            double* phi_src_out, hipStream_t s)
 {

@@ -44,7 +44,7 @@ struct Fused<double> {
 
 }  // namespace
 
-hipError_t launch_step_f64(const KParams& p, const TileCfg& tc, int variant, bool compact,
+hipError_t launch_step_f64(const KParams& p, const TileCfg& tc, int variant, int compact,
                            const void* src, void* dst, double* phi64, double* partials,
                            double* phi_src_out, hipStream_t s)
 {
@@ -61,6 +61,12 @@ hipError_t launch_phi_compact_f64(const KParams& p, const void* state, const dou
                                   double* phi, hipStream_t s)
 {
     return launch_phi_compact_t<double, false>(p, state, cphi, phi, nullptr, s);
+}
+
+hipError_t launch_step_compact_f64(const KParams& p, const void* src, void* dst, bool to_full,
+                                   const double* phi, double* partials, hipStream_t s)
+{
+    return launch_step_compact_t<double, false>(p, src, dst, to_full, phi, partials, s);
 }
 
 }  // namespace lbk

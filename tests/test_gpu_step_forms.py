@@ -186,9 +186,12 @@ def test_moments_alone_and_together_agree(shape, prec, coupling, order_param):
 # compact levels (40000), and from which their phi pass marches (FP64 160000,
 # with the force 200000, FP32 storage 650000): extents that its 12 x 32 tile
 # divides, covers once, shifts back or is larger than, thin slabs, few and many
-# planes, more sites than the sums have workgroups for
+# planes, more sites than the sums have workgroups for; and from which the
+# levels hold f's moments with tau_f = 1 (FP64 450000, with the force 800000,
+# FP32 storage 1500000)
 COMPACT = [(33, 33, 36), (40, 25, 40), (34, 11, 107), (70, 48, 64), (4, 203, 257), (57, 61, 63),
-           (3, 200, 300), (41, 5, 1000), (9000, 11, 7), (88, 90, 83), (101, 97, 120)]
+           (3, 200, 300), (41, 5, 1000), (9000, 11, 7), (88, 90, 83), (101, 97, 120),
+           (4, 352, 360), (75, 84, 96), (37, 203, 214)]
 
 
 @pytest.mark.parametrize("tau_f", [1.0, 0.8])

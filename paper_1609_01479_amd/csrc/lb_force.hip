@@ -19,6 +19,7 @@
 // differently in different kernels, and the two forms must round alike.
 #pragma clang fp contract(off)
 
+#include "lb_box.h"
 #include "lb_compact.h"
 #include "lb_device.h"
 #include "lb_sweep.h"
@@ -411,6 +412,8 @@ hipError_t launch_force_collide(const KParams& p, const TileCfg& tc, bool fp32, 
                                 int compact, const void* src, void* dst, double* phi,
                                 double* partials, hipStream_t s)
 {
+    if (variant == kStepBox)
+        return launch_box_t<float, true, true>(p, p.omega_g == 1.0, src, dst, phi, partials, s);
     const TileCfg ft = force_tiles(p, tc.seg_req);
     const int nft = ft.ntiles * ft.nseg;
     // omega_g = 1: g* = g^eq, so the collision loads no g (the single pass

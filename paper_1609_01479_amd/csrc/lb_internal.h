@@ -95,6 +95,16 @@ hipError_t launch_init(const KParams& p, bool fp32, void* state, const double* p
 // (step_sums_blocks blocks of 5), for launch_sums_final.
 // phi_src_out (may be null): also store phi of src there (N FP64 values in
 // site order, bit-identical to launch_phi's).
+// Boxes of the smallest lattices' step (variant kStepBox).
+constexpr int kBox = 4, kStepBox = 3;
+struct BoxCfg {
+    int nbx, nby, nbz;
+    int blocks() const { return nbx * nby * nbz; }
+};
+inline BoxCfg box_cfg(const KParams& p)
+{
+    return {(p.nx + kBox - 1) / kBox, (p.ny + kBox - 1) / kBox, (p.nz + kBox - 1) / kBox};
+}
 // The kernels a step of `variant` runs, with or without sums.
 int step_variant(const KParams& p, const TileCfg& tc, bool fp32, int variant, bool sums);
 // The number of partial blocks the LB-scheme step of `variant` reduces over.

@@ -352,6 +352,12 @@ TileCfg tile_config(const KParams& p, int segment_x, bool fp32)
 //     256^3 1999 / 2107; other tau_g: 96^3 155 / 134, 128^3 299 / 319
 // With sums, lattices whose collision pass cannot reduce them (a third pass)
 // march.
+// The smallest lattices, as long as each box has a CU to itself, take one
+// launch (us per step of back-to-back steps, two passes / boxes; a host that
+// is slower at launching gains more): stress FP32 16^3 6.6 / 5.2, 24^3 6.8 /
+// 5.9, 28^3 (343 boxes) 7.2 / 7.8; FP64 8^3 6.1 / 5.1, 16^3 6.0 / 5.3, 20^3
+// (125 boxes) 6.0 / 6.3; force FP32 16^3 7.9 / 6.1, 24^3 7.8 / 7.4; FP64 6.9 /
+// 6.9 and 7.4 / 9.0.
 int step_variant(const KParams& p, const TileCfg& tc, bool fp32, int variant, bool sums)
 {
     // a segment length asked for is the marching kernel's; shards have no
@@ -361,12 +367,14 @@ int step_variant(const KParams& p, const TileCfg& tc, bool fp32, int variant, bo
     const bool g1 = !fp32 && p.omega_g == 1.0;
     const int limit = p.force ? (g1 ? 7100000 : fp32 ? 1100000 : 1500000)
                               : (g1 ? 2000000 : fp32 ? 700000 : 300000);
+    if (box_cfg(p).blocks() <= (fp32 ? 256 : p.force ? 0 : 112)) return kStepBox;
     return p.nsites <= limit ? 1 : 0;
 }
 
 int step_sums_blocks(const KParams& p, const TileCfg& tc, bool fp32, int variant)
 {
     variant = step_variant(p, tc, fp32, variant, true);
+    if (variant == kStepBox) return box_cfg(p).blocks();
     if (variant == 1) return collide_grid(p, true);
     if (p.force) return force_sums_blocks(p, tc.seg_req);
     return tc.ntiles * tc.nseg;

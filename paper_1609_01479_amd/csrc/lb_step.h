@@ -2,7 +2,9 @@
 // the force coupling shares: instantiated for FP32 storage by
 // lb_step_f32.hip and for FP64 by lb_step_f64.hip.
 //
-// Two forms with bit-identical levels, chosen by step_variant():
+// Three forms with bit-identical levels, chosen by step_variant():
+//
+//   k_step_box (lb_box.h), for the smallest lattices.
 //
 //   k_phi + k_step_2s: a phi pass, then stencil, collision and propagation,
 //     one site per thread: the shortest chains from launch to store, for
@@ -22,6 +24,7 @@
 
 #include <type_traits>
 
+#include "lb_box.h"
 #include "lb_compact.h"
 #include "lb_device.h"
 #include "lb_sweep.h"
@@ -624,7 +627,9 @@ hipError_t launch_step_t(const KParams& p, const TileCfg& tc, int variant, int c
     Lvl<T> a = level<T>(const_cast<void*>(src), p, F32);
     Lvl<T> d = level<T>(dst, p, F32);
     const bool g1 = CAN_G1 && p.omega_g == 1.0;
-    if (variant == 1) {
+    if (variant == kStepBox) {
+        return launch_box_t<T, CAN_G1, false>(p, g1, src, dst, phi_src_out, partials, s);
+    } else if (variant == 1) {
         const int nb = site_block(p);
         auto k = compact == 2   ? pick_2s<T, CAN_G1, CAN_G1 ? 2 : 0>(partials, nb)
                  : compact == 1 ? pick_2s<T, CAN_G1, CAN_G1 ? 1 : 0>(partials, nb)

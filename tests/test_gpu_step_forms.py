@@ -244,3 +244,35 @@ def test_rollout_through_compact_levels(shape, coupling, prec):
     for other in got[1:]:
         for a, b in zip(got[0], other):
             assert torch.equal(a, b)
+
+
+# one box, boxes shifted back and larger than the lattice, as many boxes as the
+# form takes (FP32 256, FP64 112) and more
+BOX = [(1, 1, 1), (1, 2, 3), (4, 4, 4), (5, 4, 9), (3, 17, 6), (2, 70, 9), (13, 18, 11),
+       (16, 16, 28), (16, 16, 29), (32, 32, 16), (33, 32, 16)]
+
+
+@pytest.mark.parametrize("tau_g", [1.0, 1.3])
+@pytest.mark.parametrize("coupling,prec", [("stress", "fp64"), ("stress", "fp32_dev"),
+                                           ("force", "fp32_dev")])
+@pytest.mark.parametrize("shape", BOX)
+def test_box_step_and_two_passes_agree_bit_for_bit(shape, coupling, prec, tau_g):
+    print(f"[box] {shape} {coupling} {prec} tau_g {tau_g}", flush=True)
+    phi0 = lbinputs.spinodal_phi0(shape, seed=37, amp=0.3)
+    states, sums, phis = [], [], []
+    for kernel in ("fused", "two_pass"):
+        lb = make_lb(shape, precision=prec, tau_f=0.8, tau_g=tau_g, coupling=coupling, kernel=kernel)
+        lb.init_phi(phi0)
+        lb.step(2)
+        sums.append(lb.step_sums(3).cpu().numpy())
+        src, dst = lb.get_state(), lb.new_state()
+        phis.append(torch.empty(shape, dtype=torch.float64, device="cuda:0"))
+        lb.step_chain(src, [dst], [phis[-1]])
+        lb.set_state(dst)
+        states.append(gpu_state(lb))
+    for a, b in zip(*states):
+        assert np.array_equal(a, b)
+    assert torch.equal(*phis)
+    # five sums of n terms of order 1 in two orders: n eps of their scale n
+    n = float(np.prod(shape))
+    assert np.abs(sums[0] - sums[1]).max() <= max(n, 4.0) * n * 2.3e-16

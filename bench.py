@@ -43,18 +43,38 @@ def step_bytes_per_site(elem_bytes: int) -> dict:
     return {"method_min": 76 * elem_bytes, "kernel": 76 * elem_bytes + extra}
 
 
+def call_bytes_per_site(prec: str, steps: int, coupling: str = "stress") -> float:
+    """Bytes per site and step of one call of `steps` steps on the lattices
+    timed here (tau_f = tau_g = 1, 128^3 and up).  FP32 storage with the stress
+    coupling: the single pass, its method's minimum.  The others keep the
+    levels between a call's steps compact: phi, mu and u for g (FP64 40 B, FP32
+    storage 24) and in FP64 f's ten moments (80 B).  Two passes per step, the
+    first phi from phi, mu and u; the call's first step reads a full level and
+    its last one writes one."""
+    e = 8 if prec == "fp64" else 4
+    if prec != "fp64" and coupling == "stress":
+        return step_bytes_per_site(e)["method_min"]
+    if steps == 1:
+        return step_bytes_per_site(e)["method_min"]
+    f, g, cf, cg = 19 * e, 19 * e + (4 if e == 4 else 0), 10 * e if e == 8 else 19 * e, 4 * e
+    first = g + 8 + f + 8 + cf + cg
+    middle = (8 + cg + 8) + (cf + 8 + cf + cg)
+    last = (8 + cg + 8) + (cf + 8 + f + g)
+    return (first + middle * (steps - 2) + last) / steps
+
+
 # HBM bytes per launch of the single-pass step kernel on the 256^3 droplet,
 # from two rocprofv3 --pmc passes (FETCH_SIZE, WRITE_SIZE) over
 # `bench.py --steps 5 --warmup 1 --no-adjoint --no-cpu-baseline
-# --spinodal-steps 0 --force-steps 5 --fd-steps 5 --shard-steps 0
+# --spinodal-steps 0 --force-steps 0 --fd-steps 0 --shard-steps 0
 # --error-steps 0`, each scaled by the same counter's reading for the
 # library's copy kernel of known size (FETCH x 2.000, WRITE x 1.000).
 # They hold only for the kernel sources they were taken on (the hash below);
 # after any change to those sources the traffic is reported as null.
-TRAFFIC_SOURCES = ("lb_step.h", "lb_step_f32.hip", "lb_step_f64.hip", "lb_kernels.hip",
-                   "lb_device.h", "lb_internal.h")
-TRAFFIC_SHA256 = "d86d933167066445c0fd4198305be13ba6339a49ff7f7524e314d0ba5395c23f"
-TRAFFIC_BYTES = {"fp32_dev": 5350005418, "fp64": 10363384056}
+TRAFFIC_SOURCES = ("lb_step.h", "lb_step_f32.hip", "lb_kernels.hip", "lb_device.h",
+                   "lb_internal.h")
+TRAFFIC_SHA256 = "1816528597de3be99a1e967efc7e3016891d06612e6a14393328b8b6fb481138"
+TRAFFIC_BYTES = {"fp32_dev": 5356224512}
 
 
 def sources_sha256() -> str:
@@ -211,7 +231,8 @@ def footprint_sweep(args):
     streaming copy (read B, write B) and the single-pass step and its
     memory-only twin (read one time level, write the other) on droplet
     lattices of growing size.  GB/s count the kernels' own bytes (FP32
-    storage: 312 B per site with phi_c; FP64: 608)."""
+    storage: 312 B per site with phi_c; FP64: 608, and for a call of many
+    steps what call_bytes_per_site says)."""
     import torch
 
     import lbinputs
@@ -252,8 +273,9 @@ def footprint_sweep(args):
                 tm["stream"].append(time_steps(twin, k, 0) / k)
             for kern, v in tm.items():
                 ms = sorted(v)[1]
+                moved = call_bytes_per_site(prec, k) if e == 8 and kern == "fused" else kb
                 row[kern + "_ms"] = round(ms, 4)
-                row[kern + "_GBps"] = round(kb * nsites / (ms * 1e-3) / 1e9, 1)
+                row[kern + "_GBps"] = round(moved * nsites / (ms * 1e-3) / 1e9, 1)
             twin.close()
             del lb, twin
             torch.cuda.empty_cache()
@@ -413,23 +435,26 @@ def main():
 
     def roof(run, prec):
         e = run["elem"]
-        b = step_bytes_per_site(e)
-        # achieved = the method's algorithmic bytes per launch (304 or 608 B
-        # per site times the N sites one launch updates) / the kernel's
-        # average launch duration (plain steps: one launch each)
+        # achieved = the algorithmic bytes per step / the average duration of
+        # a plain step (FP32 storage: one launch each)
+        per_site = call_bytes_per_site(prec, args.steps)
+        kernel = step_bytes_per_site(e)["kernel"] if e == 4 else per_site
         t = run["ms_plain"] / args.steps * 1e-3
-        achieved = b["method_min"] * nsites / t / 1e9
+        achieved = per_site * nsites / t / 1e9
         return {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4),
                 "traffic": measured_traffic(prec, n, args.layout),
-                "bytes_per_site": b["method_min"],
-                "algorithmic_bytes_per_launch": b["method_min"] * nsites,
-                "kernel": "k_step_fused_f32" if e == 4 else "k_step_fused_f64",
+                "bytes_per_site": round(per_site, 1),
+                "algorithmic_bytes_per_launch" if e == 4 else "algorithmic_bytes_per_step":
+                    round(per_site * nsites),
+                "kernel": "k_step_fused_f32" if e == 4
+                          else "k_phi_compact_march + k_step_compact_march",
                 "kernel_ms": round(t * 1e3, 4),
                 "kernel_time_source": f"HIP events around {args.steps} plain steps "
-                                      "(one launch each) on the library's stream",
-                "kernel_bytes_per_site": b["kernel"],
-                "achieved_kernel_bytes_GBps": round(b["kernel"] * nsites / t / 1e9, 1)}
+                                      f"({'one launch' if e == 4 else 'two launches'} each) "
+                                      "on the library's stream",
+                "kernel_bytes_per_site": round(kernel, 1),
+                "achieved_kernel_bytes_GBps": round(kernel * nsites / t / 1e9, 1)}
 
     out = {
         "metric": "MLUPS & % peak HBM GB/s, D3Q19 binary 256^3: FP32 vs FP64; adjoint/forward cost",
@@ -464,7 +489,9 @@ def main():
 
     # the single-pass kernel's memory-only twin (LB_KERNEL_STREAM: the same
     # loads, phi sums and stores with the collision left out) on the same
-    # lattice: the memory-bound floor of this kernel's access pattern
+    # lattice: the memory-bound floor of this kernel's access pattern.  (In
+    # FP64 the twin moves full levels, 608 B per site, as a call of one step
+    # does; the step timed beside it, in calls of many, moves fewer.)
     out["stream_twin"] = {}
     for prec in precs:
         # the twin as a second context on the step's own buffers, the two
@@ -502,14 +529,13 @@ def main():
         del errrun
     del runs
 
-    # force coupling (body force -div Pi) on the same 256^3 droplet: one
-    # marching kernel per step (phi from its own pulls), f and g read and
-    # written once: the method's 608 B per site in FP64 and 304 in FP32
-    # storage (the kernel's own 312 with its reference field phi_c)
+    # force coupling (body force -div Pi) on the same 256^3 droplet, compact
+    # levels between the steps of the call
     if args.force_steps > 0:
         out["force_coupling"] = {}
         force_phi = {}
-        for prec, minimum, kbytes in (("fp32_dev", 304, 312), ("fp64", 608, 608)):
+        for prec in ("fp32_dev", "fp64"):
+            minimum = call_bytes_per_site(prec, args.force_steps, "force")
             lb = LB(shape, precision=prec, coupling="force", device="cuda:0", **lay, **params)
             lb.init_phi(phi0)
             log(f"{prec} force coupling {shape}: {args.force_steps} steps")
@@ -521,9 +547,9 @@ def main():
                 "ms_per_step": round(ms / args.force_steps, 4),
                 "achieved_GBps": round(minimum * nsites / t / 1e9, 1),
                 "frac": round(minimum * nsites / t / 1e9 / HBM_PEAK_GBPS, 4),
-                "bytes_per_site": minimum,
-                "kernel_bytes_per_site": kbytes,
-                "kernels": "k_force_fused"}
+                "bytes_per_site": round(minimum, 1),
+                "kernels": "k_phi_compact_march + " + ("k_step_force" if prec == "fp32_dev"
+                                                       else "k_step_compact_march")}
             force_phi[prec] = lb.phi().cpu().numpy()
             del lb
             torch.cuda.empty_cache()
@@ -641,11 +667,13 @@ def main():
         ms = time_steps(lb, args.spinodal_steps, args.warmup)
         t = ms / args.spinodal_steps * 1e-3
         n128 = 128 ** 3
+        moved = call_bytes_per_site("fp64", args.spinodal_steps)
         out["fp64_spinodal_128"] = {
             "value": round(n128 / t / 1e6, 1), "unit": "MLUPS", "steps": args.spinodal_steps,
             "ms_per_step": round(ms / args.spinodal_steps, 4),
-            "achieved_GBps": round(step_bytes_per_site(8)["method_min"] * n128 / t / 1e9, 1),
-            "frac": round(step_bytes_per_site(8)["method_min"] * n128 / t / 1e9 / HBM_PEAK_GBPS, 4)}
+            "achieved_GBps": round(moved * n128 / t / 1e9, 1),
+            "frac": round(moved * n128 / t / 1e9 / HBM_PEAK_GBPS, 4),
+            "bytes_per_site": round(moved, 1)}
         del lb
         torch.cuda.empty_cache()
 

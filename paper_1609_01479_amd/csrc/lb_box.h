@@ -18,13 +18,36 @@ using namespace dev;
 
 namespace {
 
-constexpr int box_cells(bool force)
+constexpr int box_cells(int h) { return (kBox + 2 * h) * (kBox + 2 * h) * (kBox + 2 * h); }
+constexpr int box_threads(int h) { return h == 1 ? 256 : 512; }
+static_assert(box_cells(1) <= box_threads(1) && box_cells(2) <= box_threads(2), "a thread per cell");
+
+// This thread's cell of its workgroup's box with H cells around it.
+struct BoxCell {
+    Geo q;
+    int c;        // cell, z fastest
+    bool own;     // a site of the box
+    bool counts;  // and of no box before this one
+};
+
+template <int H>
+__device__ __forceinline__ BoxCell box_cell(const KParams& p, const BoxCfg& bc)
 {
-    return (kBox + (force ? 4 : 2)) * (kBox + (force ? 4 : 2)) * (kBox + (force ? 4 : 2));
+    constexpr int BY = kBox + 2 * H, BX = BY * BY, NC = box_cells(H);
+    const int b = xcd_block(), t = threadIdx.x;
+    const int bz = b % bc.nbz, by = b / bc.nbz % bc.nby, bx = b / (bc.nbz * bc.nby);
+    // the last boxes along each axis are shifted back to end with it
+    const int ex = min(p.nx, kBox), ey = min(p.ny, kBox), ez = min(p.nz, kBox);
+    const int x0 = min(bx * kBox, p.nx - ex), y0 = min(by * kBox, p.ny - ey),
+              z0 = min(bz * kBox, p.nz - ez);
+    BoxCell k;
+    k.c = min(t, NC - 1);
+    const int lx = k.c / BX - H, ly = k.c / BY % BY - H, lz = k.c % BY - H;
+    k.own = t < NC && lx >= 0 && lx < ex && ly >= 0 && ly < ey && lz >= 0 && lz < ez;
+    k.counts = k.own && x0 + lx >= bx * kBox && y0 + ly >= by * kBox && z0 + lz >= bz * kBox;
+    k.q = geo_xyz(p, wrap_any(x0 + lx, p.nx), wrap_any(y0 + ly, p.ny), wrap_any(z0 + lz, p.nz));
+    return k;
 }
-constexpr int box_threads(bool force) { return force ? 512 : 256; }
-static_assert(box_cells(false) <= box_threads(false) && box_cells(true) <= box_threads(true),
-              "a thread per cell");
 
 // F = -div Pi at cell c of a box of phi, as force_from_phi forms it.
 template <int BX, int BY>
@@ -52,29 +75,21 @@ __device__ __forceinline__ void force_in_box(const KParams& p, const double* phi
 }
 
 template <typename T, bool DEV, bool REF, bool G1, bool FORCE, bool SUMS>
-__global__ __launch_bounds__(box_threads(FORCE)) void k_step_box(
+__global__ __launch_bounds__(box_threads(FORCE ? 2 : 1)) void k_step_box(
     KParams p, BoxCfg bc, const T* __restrict__ sF, const T* __restrict__ sG,
     const unsigned* __restrict__ sphic, T* __restrict__ dF, T* __restrict__ dG,
     unsigned* __restrict__ dphic, double* __restrict__ phi_out, double* __restrict__ partials)
 {
-    constexpr int H = FORCE ? 2 : 1, BY = kBox + 2 * H, BX = BY * BY, NC = box_cells(FORCE);
-    __shared__ double s_phi[NC];
-    const int b = xcd_block(), t = threadIdx.x;
-    const int bz = b % bc.nbz, by = b / bc.nbz % bc.nby, bx = b / (bc.nbz * bc.nby);
-    // the last boxes along each axis are shifted back to end with it
-    const int ex = min(p.nx, kBox), ey = min(p.ny, kBox), ez = min(p.nz, kBox);
-    const int x0 = min(bx * kBox, p.nx - ex), y0 = min(by * kBox, p.ny - ey),
-              z0 = min(bz * kBox, p.nz - ez);
-    const int c = min(t, NC - 1);
-    const int lx = c / BX - H, ly = c / BY % BY - H, lz = c % BY - H;
-    const bool own = t < NC && lx >= 0 && lx < ex && ly >= 0 && ly < ey && lz >= 0 && lz < ez;
-    const Geo q = geo_xyz(p, wrap_any(x0 + lx, p.nx), wrap_any(y0 + ly, p.ny),
-                          wrap_any(z0 + lz, p.nz));
+    constexpr int H = FORCE ? 2 : 1, BY = kBox + 2 * H, BX = BY * BY;
+    __shared__ double s_phi[box_cells(H)];
+    const BoxCell k = box_cell<H>(p, bc);
+    const Geo& q = k.q;
+    const int c = k.c;
     T f[NV], g[NV];
 #pragma unroll
     for (int i = 0; i < NV; i++) g[i] = sG[dist_pull(p, q, i)];
     const double pc = REF ? phic_value(sphic[phic_site(p, q.x, q.y, q.z)]) : 0.0;
-    if (own)
+    if (k.own)
 #pragma unroll
         for (int i = 0; i < NV; i++) f[i] = sF[dist_pull(p, q, i)];
     // phi as pull_g forms it
@@ -85,8 +100,7 @@ __global__ __launch_bounds__(box_threads(FORCE)) void k_step_box(
     s_phi[c] = v;
     lds_barrier();
     double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    if (own) {
-        const bool counts = x0 + lx >= bx * kBox && y0 + ly >= by * kBox && z0 + lz >= bz * kBox;
+    if (k.own) {
         if (phi_out) phi_out[site_of(p, q.x, q.y, q.z)] = v;
         if (REF) {
             if (!FORCE || !G1)
@@ -101,12 +115,12 @@ __global__ __launch_bounds__(box_threads(FORCE)) void k_step_box(
             const double mu = p.A * v + p.B * v * v * v - p.kappa * lap;
             double F[3];
             force_in_box<BX, BY>(p, s_phi, c, F);
-            if (SUMS && counts) site_sums<DEV>(p, f, v, F, acc);
+            if (SUMS && k.counts) site_sums<DEV>(p, f, v, F, acc);
             collide_force<T, DEV, REF, G1>(p, f, g, v, mu, F);
         } else {
             const Stencil st = stencil(v, s_phi[c + BX], s_phi[c - BX], s_phi[c + BY],
                                        s_phi[c - BY], s_phi[c + 1], s_phi[c - 1]);
-            if (SUMS && counts) site_sums<DEV>(p, f, v, nullptr, acc);
+            if (SUMS && k.counts) site_sums<DEV>(p, f, v, nullptr, acc);
             collide<T, DEV, REF, G1>(p, f, g, st);
         }
 #pragma unroll
@@ -116,7 +130,7 @@ __global__ __launch_bounds__(box_threads(FORCE)) void k_step_box(
                 REF ? to_dest_ref(i, g[i], v, s_phi[c + CX[i] * BX + CY[i] * BY + CZ[i]]) : g[i];
         }
     }
-    if (SUMS) block_partials<5, box_threads(FORCE)>(acc, partials);
+    if (SUMS) block_partials<5, box_threads(FORCE ? 2 : 1)>(acc, partials);
 }
 
 template <typename T, bool CAN_G1, bool FORCE>
@@ -131,7 +145,7 @@ hipError_t launch_box_t(const KParams& p, bool g1, const void* src, void* dst, d
                             : k_step_box<T, F32, F32, CAN_G1, FORCE, false>)
                 : (partials ? k_step_box<T, F32, F32, false, FORCE, true>
                             : k_step_box<T, F32, F32, false, FORCE, false>);
-    k<<<bc.blocks(), box_threads(FORCE), 0, s>>>(p, bc, a.F, a.G, a.phic, d.F, d.G, d.phic,
+    k<<<bc.blocks(), box_threads(FORCE ? 2 : 1), 0, s>>>(p, bc, a.F, a.G, a.phic, d.F, d.G, d.phic,
                                                  phi_src_out, partials);
     return hipGetLastError();
 }

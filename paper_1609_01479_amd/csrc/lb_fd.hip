@@ -41,6 +41,7 @@
 #include <type_traits>
 
 #include "lb_device.h"
+#include "lb_box.h"
 #include "lb_sweep.h"
 
 namespace lbk {
@@ -221,6 +222,62 @@ __global__ __launch_bounds__(kBlock) void k_fd_update_site(KParams p, const doub
              - fd_flux(phi[nb[a][1]], pc, u[nb[a][1]], uc, work[nb[a][1]], mc, M);
     }
     dphi[s] = pc - div;
+}
+
+// The step of the smallest lattices in one launch: a workgroup owns a box of
+// 4^3 sites, forms mu and u of the box and of the layer around it, a cell per
+// thread with k_fd_collide's instructions, and hands them over in LDS for the
+// flux update of its own sites.  Bound by the chain from launch to store; f is
+// pulled 3.4 times.  Measured at fd_variant.
+template <typename T, bool DEV, bool FORCE, bool SUMS>
+__global__ __launch_bounds__(box_threads(1)) void k_fd_box(KParams p, BoxCfg bc,
+                                                           const T* __restrict__ sF,
+                                                           const double* __restrict__ sphi,
+                                                           T* __restrict__ dF,
+                                                           double* __restrict__ dphi,
+                                                           double* __restrict__ partials)
+{
+    using W = FdWork<T, FORCE>;
+    constexpr int BY = kBox + 2, OFF[3] = {BY * BY, BY, 1};
+    __shared__ double s_f[5][box_cells(1)];  // phi, mu, u
+    const BoxCell k = box_cell<1>(p, bc);
+    const Geo& q = k.q;
+    const int c = k.c, s = site_of(p, q.x, q.y, q.z);
+    double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    T f[NV];
+#pragma unroll
+    for (int i = 0; i < NV; i++) f[i] = sF[dist_pull(p, q, i)];
+    const double pc = sphi[s];
+    const Stencil st = stencil(pc, sphi[site_of(p, q.xp, q.y, q.z)], sphi[site_of(p, q.xm, q.y, q.z)],
+                               sphi[site_of(p, q.x, q.yp, q.z)], sphi[site_of(p, q.x, q.ym, q.z)],
+                               sphi[site_of(p, q.x, q.y, q.zp)], sphi[site_of(p, q.x, q.y, q.zm)]);
+    double F[3] = {0.0, 0.0, 0.0};
+    if (FORCE) force_from_phi(p, q, sphi, F);
+    if (SUMS && k.counts) site_sums<DEV>(p, f, pc, FORCE ? F : nullptr, acc);
+    const Vel<T> u = FORCE ? collide_force_f<T, DEV>(p, f, F) : collide_f<T, DEV>(p, f, st);
+    if (k.own)
+#pragma unroll
+        for (int i = 0; i < NV; i++) dF[dist_own(p, q, i)] = f[i];
+    const double mc = double(W(fd_mu(p, pc, st.lap)));
+    s_f[0][c] = pc;
+    s_f[1][c] = mc;
+    s_f[2][c] = double(W(u.x));
+    s_f[3][c] = double(W(u.y));
+    s_f[4][c] = double(W(u.z));
+    lds_barrier();
+    if (k.own) {
+        const double M = p.mobility;
+        double div = 0.0;
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+            const int n = c + OFF[a], m = c - OFF[a];
+            const double uc = s_f[a + 2][c];
+            div += fd_flux(pc, s_f[0][n], uc, s_f[a + 2][n], mc, s_f[1][n], M)
+                 - fd_flux(s_f[0][m], pc, s_f[a + 2][m], uc, s_f[1][m], mc, M);
+        }
+        dphi[s] = pc - div;
+    }
+    if (SUMS) block_partials<5, box_threads(1)>(acc, partials);
 }
 
 // ---------------------------------------------------------------------------
@@ -1150,9 +1207,19 @@ static int fd_collide_grid(const KParams& p) { return (p.nsites + site_block(p) 
 // 72 x 111 x 150 95 / 101; force FP32 16^3 15 / 6.1, 96^3 45 / 38,
 // 72 x 111 x 150 57 / 51, 128^3 79 / 107; force FP64 16^3 17 / 6.3,
 // 64^3 29 / 22, 96^3 76 / 74, 72 x 111 x 150 100 / 108.
+// The smallest lattices take one launch (see step_variant); us of a whole run
+// of 5 / 100 steps, march / two passes / boxes: stress FP32 16^3 69 / 118 / 68
+// and 914 / 801 / 565, 32^3 69 / 119 / 68 and 905 / 855 / 709; FP64 32^3 82 / 119
+// / 67 and 1180 / 863 / 788; force FP32 16^3 101 / 118 / 67 and 1547 / 772 / 682,
+// 32^3 98 / 121 / 68 and 1477 / 901 / 906; FP64 32^3 114 / 119 / 72 and 1793 /
+// 938 / 979.  Above that the stress coupling marches as long as that keeps up
+// with two launches: FP32 40^3 73 / 119 and 965 / 934, 48^3 83 / 119 and 1118 /
+// 1060; FP64 40^3 86 / 119 and 1128 / 1014, 48^3 117 / 120 and 1769 / 1234.
 static int fd_variant(const KParams& p, const TileCfg& tc, bool fp32, int variant, bool sums)
 {
     if (variant != 0 || tc.seg_req > 0) return variant;
+    if (box_cfg(p).blocks() <= 512) return kStepBox;
+    if (!p.force && p.nsites <= (fp32 ? 120000 : 75000)) return 0;
     if (sums && fd_collide_grid(p) > kMaxStepPartials) return 0;
     const int limit = !fp32 ? 900000 : p.force ? 1300000 : 450000;
     return p.nsites <= limit ? 1 : 0;
@@ -1167,7 +1234,9 @@ int fd_step_partial_blocks(const KParams& p, int segment_x)
 
 int fd_sums_blocks(const KParams& p, const TileCfg& tc, bool fp32, int variant)
 {
-    if (fd_variant(p, tc, fp32, variant, true) != 0) return fd_collide_grid(p);
+    variant = fd_variant(p, tc, fp32, variant, true);
+    if (variant == kStepBox) return box_cfg(p).blocks();
+    if (variant != 0) return fd_collide_grid(p);
     return fd_march_blocks(p, tc);
 }
 
@@ -1219,12 +1288,20 @@ hipError_t launch_fd_step(const KParams& p, const TileCfg& tc, bool fp32, int va
                           hipStream_t s)
 {
     variant = fd_variant(p, tc, fp32, variant, partials != nullptr);
-    const bool nt = nt_stores(p, NV, fp32 ? 4 : 8, 96);
+    const bool nt = variant == 0 && !p.force ? march_nt(p, NV, fp32 ? 4 : 8, 96)
+                                             : nt_stores(p, NV, fp32 ? 4 : 8, 96);
 #define CALL                                                                                  \
     {                                                                                         \
         FdLvl<T> a = fd_level<T>(const_cast<void*>(src), p);                                  \
         FdLvl<T> d = fd_level<T>(dst, p);                                                     \
-        if (variant != 0) {                                                                   \
+        if (variant == kStepBox) {                                                            \
+            auto k = p.force ? (partials ? k_fd_box<T, DEV, true, true>                       \
+                                         : k_fd_box<T, DEV, true, false>)                     \
+                             : (partials ? k_fd_box<T, DEV, false, true>                      \
+                                         : k_fd_box<T, DEV, false, false>);                   \
+            const BoxCfg bc = box_cfg(p);                                                     \
+            k<<<bc.blocks(), box_threads(1), 0, s>>>(p, bc, a.F, a.phi, d.F, d.phi, partials); \
+        } else if (variant != 0) {                                                            \
             auto k = p.force ? (nt ? fd_two_pass<T, true, true> : fd_two_pass<T, true, false>) \
                              : (nt ? fd_two_pass<T, false, true>                              \
                                    : fd_two_pass<T, false, false>);                           \

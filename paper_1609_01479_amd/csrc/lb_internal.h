@@ -80,6 +80,14 @@ inline bool nt_stores(const KParams& p, int ncomp, size_t elem, int mb)
 {
     return p.cs * elem % 64 == 0 && size_t(ncomp) * p.nsites * elem > (size_t(mb) << 20);
 }
+// Those of a march: also on the smallest lattices it runs on, where a
+// workgroup's next plane waits behind its stores (us per 100 steps, non-temporal
+// / plain: FD FP32 48^3 1124 / 1230, FP64 40^3 1152 / 1213, LB FP32 40^3 1041 /
+// 1101).
+inline bool march_nt(const KParams& p, int ncomp, int elem, int mb)
+{
+    return p.nsites <= 120000 || nt_stores(p, ncomp, elem, mb);
+}
 
 // All launchers enqueue on `s` and return hipGetLastError().
 // `fp32` selects the FP32 deviation-storage instantiation; otherwise FP64.

@@ -318,11 +318,12 @@ TileCfg row_tile_config(const KParams& p, int segment_x)
 // or as many in segments of 8 or more.  FP64 192^3 831 / 843, 256^3 1831 / 1905
 // (flat tiles re-read more through L2), 100 x 120 x 240 340 / 346, but 96^3
 // 119 / 111, 151 x 105 x 150 409 / 354: flat where row tiles leave more than a
-// tenth of their lanes idle along z.
+// tenth of their lanes idle along z.  Up to 120000 sites, whose segments are
+// short, row tiles.
 TileCfg tile_config(const KParams& p, int segment_x, bool fp32)
 {
     const TileCfg rows = row_tile_config(p, segment_x);
-    if (!flat_fits(p, fp32)) return rows;
+    if (!flat_fits(p, fp32) || p.nsites <= 120000) return rows;
     TileCfg flat = rows;
     flat.tz = 0;
     flat.nty = 1;
@@ -352,12 +353,17 @@ TileCfg tile_config(const KParams& p, int segment_x, bool fp32)
 //     256^3 1999 / 2107; other tau_g: 96^3 155 / 134, 128^3 299 / 319
 // With sums, lattices whose collision pass cannot reduce them (a third pass)
 // march.
-// The smallest lattices, as long as each box has a CU to itself, take one
-// launch (us per step of back-to-back steps, two passes / boxes; a host that
-// is slower at launching gains more): stress FP32 16^3 6.6 / 5.2, 24^3 6.8 /
-// 5.9, 28^3 (343 boxes) 7.2 / 7.8; FP64 8^3 6.1 / 5.1, 16^3 6.0 / 5.3, 20^3
-// (125 boxes) 6.0 / 6.3; force FP32 16^3 7.9 / 6.1, 24^3 7.8 / 7.4; FP64 6.9 /
-// 6.9 and 7.4 / 9.0.
+// The smallest lattices take one launch: the first ten or so launches after
+// the host has waited cost it 10 us each, later ones 3.5, and two chains from
+// launch to store are longer than one.  Measured, us of a whole run (initial
+// state, 5 / 100 steps, moments), march / two passes / boxes: stress FP32 16^3
+// 73 / 117 / 68 and 993 / 800 / 605, 32^3 74 / 117 / 67 and 1007 / 870 / 781;
+// FP64 16^3 89 / 117 / 68 and 1299 / 790 / 596, 32^3 87 / 118 / 74 and 1228 /
+// 917 / 956; force FP32 16^3 131 / 125 / 105 and 1925 / 850 / 671, 28^3 (343
+// boxes) 125 / 121 / 127 and 1786 / 958 / 1020; force FP64 16^3 135 / 124 / 130
+// and 2047 / 871 / 900.  Above that, FP32 storage marches, one launch too, as
+// long as the march keeps up with two: 40^3 81 / 117 and 1015 / 1010, 48^3 104 /
+// 119 and 1519 / 1187.
 int step_variant(const KParams& p, const TileCfg& tc, bool fp32, int variant, bool sums)
 {
     // a segment length asked for is the marching kernel's; shards have no
@@ -367,7 +373,8 @@ int step_variant(const KParams& p, const TileCfg& tc, bool fp32, int variant, bo
     const bool g1 = !fp32 && p.omega_g == 1.0;
     const int limit = p.force ? (g1 ? 7100000 : fp32 ? 1100000 : 1500000)
                               : (g1 ? 2000000 : fp32 ? 700000 : 300000);
-    if (box_cfg(p).blocks() <= (fp32 ? 256 : p.force ? 0 : 112)) return kStepBox;
+    if (box_cfg(p).blocks() <= (!p.force ? 512 : fp32 ? 256 : 0)) return kStepBox;
+    if (!p.force && fp32 && p.nsites <= 75000) return 0;
     return p.nsites <= limit ? 1 : 0;
 }
 

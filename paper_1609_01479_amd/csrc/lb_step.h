@@ -638,7 +638,7 @@ hipError_t launch_step_t(const KParams& p, const TileCfg& tc, int variant, int c
         k<<<collide_grid(p, partials), nb, 0, s>>>(p, a.F, a.G, a.phic, phi64, d.F, d.G, partials);
     } else {
         const bool small = size_t(NV) * p.stride * sizeof(T) < (size_t(1) << 32);
-        auto k = Fused<T>::get(small, tc.tz, variant == 0, g1, nt_stores(p, 2 * NV, sizeof(T), 144));
+        auto k = Fused<T>::get(small, tc.tz, variant == 0, g1, march_nt(p, 2 * NV, sizeof(T), 144));
         k<<<tc.ntiles * tc.nseg, kFused, 0, s>>>(p, tc, a.F, a.G, a.phic, d.F, d.G, d.phic,
                                                  phi_src_out, partials);
     }

@@ -247,9 +247,9 @@ def test_rollout_through_compact_levels(shape, coupling, prec):
 
 
 # one box, boxes shifted back and larger than the lattice, as many boxes as the
-# form takes (FP32 256, FP64 112) and more
+# form takes (512, with the force coupling 256) and more
 BOX = [(1, 1, 1), (1, 2, 3), (4, 4, 4), (5, 4, 9), (3, 17, 6), (2, 70, 9), (13, 18, 11),
-       (16, 16, 28), (16, 16, 29), (32, 32, 16), (33, 32, 16)]
+       (32, 32, 16), (33, 32, 16), (32, 32, 32), (33, 32, 32)]
 
 
 @pytest.mark.parametrize("tau_g", [1.0, 1.3])
@@ -273,6 +273,29 @@ def test_box_step_and_two_passes_agree_bit_for_bit(shape, coupling, prec, tau_g)
     for a, b in zip(*states):
         assert np.array_equal(a, b)
     assert torch.equal(*phis)
+    # five sums of n terms of order 1 in two orders: n eps of their scale n
+    n = float(np.prod(shape))
+    assert np.abs(sums[0] - sums[1]).max() <= max(n, 4.0) * n * 2.3e-16
+
+
+@pytest.mark.parametrize("tau_g", [1.0, 1.3])
+@pytest.mark.parametrize("coupling", ["stress", "force"])
+@pytest.mark.parametrize("prec", ["fp64", "fp32_dev"])
+@pytest.mark.parametrize("shape", BOX)
+def test_fd_box_step_and_two_passes_agree_bit_for_bit(shape, prec, coupling, tau_g):
+    print(f"[fd box] {shape} {coupling} {prec} tau_g {tau_g}", flush=True)
+    phi0 = lbinputs.spinodal_phi0(shape, seed=41, amp=0.3)
+    states, sums = [], []
+    for kernel in ("fused", "two_pass"):
+        lb = make_lb(shape, precision=prec, tau_f=0.8, tau_g=tau_g, coupling=coupling,
+                     order_param="fd", kernel=kernel)
+        lb.init_phi(phi0)
+        lb.step(2)
+        sums.append(lb.step_sums(3).cpu().numpy())
+        f, _ = lb.export_dist()
+        states.append([f.cpu().numpy(), lb.phi().cpu().numpy()])
+    for a, b in zip(*states):
+        assert np.array_equal(a, b)
     # five sums of n terms of order 1 in two orders: n eps of their scale n
     n = float(np.prod(shape))
     assert np.abs(sums[0] - sums[1]).max() <= max(n, 4.0) * n * 2.3e-16

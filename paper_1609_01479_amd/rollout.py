@@ -150,8 +150,9 @@ class _Rollout(torch.autograd.Function):
                 phis = [torch.empty(lb.shape, dtype=torch.float64, device=dev) for _ in range(m)]
         for si in reversed(range(len(ckpts) if T > 0 else 0)):
             n = min(T - si * k, k)
-            lb.step_chain(ckpts[si], seg[:n - 1], phis[:n - 1] if phis else None,
-                          states="none")
+            if n > 1:
+                lb.step_chain(ckpts[si], seg[:n - 1], phis[:n - 1] if phis else None,
+                              states="none")
             levels = [ckpts[si]] + seg[:n - 1]
             lb.adjoint_chain(levels[::-1], dtheta,
                              None if phis is None else [ends[si]] + phis[:n - 1][::-1])

@@ -24,7 +24,8 @@
 // collides f with it, and the fluxes use u = (j + F/2)/rho: one marching
 // kernel, k_fd_force_fused, with Pi staged in LDS and mu, u and F also formed
 // on the tile's face ring (LB_KERNEL_FUSED), or k_fd_collide one site per
-// thread and then k_fd_update (LB_KERNEL_TWO_PASS), bit-identical.
+// thread and then k_fd_update (LB_KERNEL_TWO_PASS), bit-identical.  The
+// smallest lattices take one launch of boxes (k_fd_box) with either coupling.
 //
 // Time level: F (19*stride elements of T in the layout of didx(); FP32 mode
 // stores f - w rho0) followed by phi (stride FP64 values in site order).

@@ -107,6 +107,32 @@ lb_status validate(const lb_params* p)
     return LB_OK;
 }
 
+// The kernels' view of the parameters, with every field that the tiling and the
+// choice of a step's form read: the sizes that lb_query_sizes gives and the
+// steps of the context that lb_create makes follow from the same one.
+lbk::KParams kernel_params(const lb_params* p)
+{
+    lbk::KParams k{};
+    k.nx = p->nx;
+    k.ny = p->ny;
+    k.nz = p->nz;
+    k.nsites = p->nx * p->ny * p->nz;
+    k.stride = unsigned(stride_for(level_sites(p)));
+    lbk::set_layout(k, p->layout, p->aosoa_len);
+    k.A = p->A;
+    k.B = p->B;
+    k.kappa = p->kappa;
+    k.gamma = p->gamma;
+    k.omega_f = 1.0 / p->tau_f;
+    k.omega_g = 1.0 / p->tau_g;
+    k.rho0 = p->rho0;
+    k.force = p->coupling == LB_COUPLING_FORCE;
+    k.fd = p->order_param == LB_OP_FD;
+    k.mobility = p->gamma * (p->tau_g - 0.5);
+    k.xh = p->halo_x ? 2 : 0;
+    return k;
+}
+
 }  // namespace
 
 struct lb_ctx {
@@ -195,9 +221,9 @@ lb_status lb_query_sizes(const lb_params* p, lb_sizes* out)
     lb_status st = validate(p);
     if (st != LB_OK) return st;
     if (!out) return fail(LB_EINVAL, "out is NULL");
-    const long long n = (long long)p->nx * p->ny * p->nz;
     const size_t e = p->precision == LB_FP64 ? 8 : 4;
-    const size_t stride = stride_for(level_sites(p));
+    const lbk::KParams k = kernel_params(p);
+    const size_t stride = k.stride;
     out->elem_bytes = e;
     out->stride_elems = stride;
     const bool fd = p->order_param == LB_OP_FD;
@@ -212,14 +238,8 @@ lb_status lb_query_sizes(const lb_params* p, lb_sizes* out)
         out->phi_bytes = stride * 8;
     }
     // block partials of the reductions: 5 FP64 per block of the largest grid
-    lbk::KParams k{};
-    k.nx = p->nx;
-    k.ny = p->ny;
-    k.nz = p->nz;
-    k.fd = fd;
     const lbk::TileCfg tc = lbk::tile_config(k, p->segment_x, p->precision == LB_FP32_DEV);
     const lbk::TileCfg rows = lbk::row_tile_config(k, p->segment_x);
-    k.nsites = int(n);
     size_t nparts = std::max<size_t>(size_t(tc.ntiles) * tc.nseg, lbk::kMaxPartialBlocks);
     nparts = std::max<size_t>(nparts, size_t(rows.ntiles) * rows.nseg);
     // a two-pass step reduces over at most this many blocks
@@ -267,25 +287,8 @@ lb_status lb_create(const lb_params* p, const lb_buffers* b, void* hip_stream, l
     c->cur = 0;
     c->adj_cur = 0;
     c->has_adj = all_adj;
-    lbk::KParams& k = c->kp;
-    k.nx = p->nx;
-    k.ny = p->ny;
-    k.nz = p->nz;
-    k.nsites = p->nx * p->ny * p->nz;
-    k.stride = unsigned(sz.stride_elems);
-    lbk::set_layout(k, p->layout, p->aosoa_len);
-    k.A = p->A;
-    k.B = p->B;
-    k.kappa = p->kappa;
-    k.gamma = p->gamma;
-    k.omega_f = 1.0 / p->tau_f;
-    k.omega_g = 1.0 / p->tau_g;
-    k.rho0 = p->rho0;
-    k.force = p->coupling == LB_COUPLING_FORCE;
-    k.fd = p->order_param == LB_OP_FD;
-    k.mobility = p->gamma * (p->tau_g - 0.5);
-    k.xh = p->halo_x ? 2 : 0;
-    c->tc = lbk::tile_config(k, p->segment_x, c->fp32);
+    c->kp = kernel_params(p);
+    c->tc = lbk::tile_config(c->kp, p->segment_x, c->fp32);
     *out = c;
     return LB_OK;
 }
@@ -360,6 +363,10 @@ static lb_status step_n(lb_ctx* ctx, int32_t nsteps, double* sums_dev, const cha
         if (f_too && t > 0) return lbk::compact_step_tiles(ctx->kp, ctx->fp32).blocks();
         return between ? lbk::collide_grid(ctx->kp, true) : sums_blocks(ctx);
     };
+    for (int32_t t = 0; sums_dev && t < std::min(nsteps, 2); t++)
+        if (blocks(t) > rows)
+            return fail(LB_ESTATE, "%s: a step reduces over %zu partial blocks, the array holds %zu",
+                        name, blocks(t), rows);
     int32_t held = 0;  // steps whose partials wait in part, nb blocks each
     size_t nb = sums_dev ? blocks(0) : 0;
     for (int32_t t = 0; t < nsteps; t++) {

@@ -268,8 +268,8 @@ lb_status lb_step_sums(lb_ctx *ctx, int32_t nsteps, double *sums_dev);
  * 5 FP64 partials (160 KiB), one copy per GPU the library runs on, kept until
  * the process ends; its address on the current GPU is looked up on the first
  * call there.  LB_EINVAL if the context's steps reduce over more blocks
- * than that, or the marching pass over row tiles (8 x 64 or 4 x 128 columns)
- * would (every cube up to 479^3 fits, except with LB_OP_FD and
+ * than that, or the marching pass over row tiles (8 x 64 or 4 x 128 columns,
+ * in LB_FP32_DEV with nz = 256 2 x 256) would (every cube up to 479^3 fits, except with LB_OP_FD and
  * LB_KERNEL_TWO_PASS, whose collision pass reduces over one block per 256
  * sites: up to about 1.05e6 sites), LB_ESTATE if the current device is not
  * that of the context's stream.  Every block overwrites its own partials before they are summed,

@@ -238,8 +238,9 @@ lb_status lb_query_sizes(const lb_params* p, lb_sizes* out)
         out->phi_bytes = stride * 8;
     }
     // block partials of the reductions: 5 FP64 per block of the largest grid
-    const lbk::TileCfg tc = lbk::tile_config(k, p->segment_x, p->precision == LB_FP32_DEV);
-    const lbk::TileCfg rows = lbk::row_tile_config(k, p->segment_x);
+    const bool fp32 = p->precision == LB_FP32_DEV;
+    const lbk::TileCfg tc = lbk::tile_config(k, p->segment_x, fp32);
+    const lbk::TileCfg rows = lbk::row_tile_config(k, p->segment_x, fp32);
     size_t nparts = std::max<size_t>(size_t(tc.ntiles) * tc.nseg, lbk::kMaxPartialBlocks);
     nparts = std::max<size_t>(nparts, size_t(rows.ntiles) * rows.nseg);
     // a two-pass step reduces over at most this many blocks
@@ -338,7 +339,7 @@ static size_t sums_blocks(const lb_ctx* ctx)
 // limit is stated for, whichever form of the step runs.
 static size_t march_blocks(const lb_ctx* ctx)
 {
-    const lbk::TileCfg tc = lbk::row_tile_config(ctx->kp, ctx->p.segment_x);
+    const lbk::TileCfg tc = lbk::row_tile_config(ctx->kp, ctx->p.segment_x, ctx->fp32);
     if (ctx->p.kernel == LB_KERNEL_TWO_PASS) return 0;
     if (ctx->kp.fd) return size_t(lbk::fd_march_blocks(ctx->kp, tc));
     if (ctx->kp.force) return size_t(lbk::force_sums_blocks(ctx->kp, ctx->p.segment_x));

@@ -62,7 +62,7 @@ inline Lvl<T> level(void* state, const KParams& p, bool ref)
 // segment_x <= 0 picks the segment length automatically.  row_tile_config:
 // the row tiling, whatever tile_config picks.
 TileCfg tile_config(const KParams& p, int segment_x, bool fp32);
-TileCfg row_tile_config(const KParams& p, int segment_x);
+TileCfg row_tile_config(const KParams& p, int segment_x, bool fp32);
 
 // Fills the layout fields of k (nx, ny, nz and stride set) for an lb_layout.
 void set_layout(KParams& k, int layout, int aosoa_len);

@@ -271,7 +271,9 @@ static long long march_cost(const TileCfg& tc)
     return (long long)((tc.ntiles * (long long)tc.nseg + kCUs - 1) / kCUs) * (tc.sx + 2);
 }
 
-static TileCfg with_segments(const KParams& p, TileCfg tc, int segment_x)
+// Segments of a tiling; the automatic length keeps it within max_blocks
+// workgroups (0: any number; one segment always counts as within).
+static TileCfg with_segments(const KParams& p, TileCfg tc, int segment_x, long long max_blocks = 0)
 {
     tc.ntiles = tc.nty * tc.ntz;
     int sx = segment_x;
@@ -284,6 +286,7 @@ static TileCfg with_segments(const KParams& p, TileCfg tc, int segment_x)
         for (int nseg = 1; nseg <= p.nx; nseg++) {
             const int s = (p.nx + nseg - 1) / nseg;
             const long long nb = (long long)tc.ntiles * ((p.nx + s - 1) / s);
+            if (max_blocks > 0 && nseg > 1 && nb > max_blocks) break;
             const long long rounds = (nb + kCUs - 1) / kCUs;
             const long long cost = rounds * (s + 2);
             if (best < 0 || cost < best) {
@@ -299,16 +302,34 @@ static TileCfg with_segments(const KParams& p, TileCfg tc, int segment_x)
     return tc;
 }
 
-TileCfg row_tile_config(const KParams& p, int segment_x)
+static TileCfg row_tiles(const KParams& p, int tz, int segment_x)
 {
     TileCfg tc;
+    tc.tz = tz;
+    const int ty = kFused / tz;
+    tc.nty = (p.ny + ty - 1) / ty;
+    tc.ntz = (p.nz + tz - 1) / tz;
+    return with_segments(p, tc, segment_x);
+}
+
+TileCfg row_tile_config(const KParams& p, int segment_x, bool fp32)
+{
     // 128 wide unless 64 leaves fewer idle lanes along z
     const long long w128 = 128LL * ((p.nz + 127) / 128), w64 = 64LL * ((p.nz + 63) / 64);
-    tc.tz = w64 < w128 ? 64 : 128;
-    const int ty = kFused / tc.tz;
-    tc.nty = (p.ny + ty - 1) / ty;
-    tc.ntz = (p.nz + tc.tz - 1) / tc.tz;
-    return with_segments(p, tc, segment_x);
+    TileCfg tc = row_tiles(p, w64 < w128 ? 64 : 128, segment_x);
+    // FP32 storage with rows of 256 sites: the allocation-free sums take what
+    // whole rows in pairs would fit in their array.  The narrower tiles are one
+    // more in a plane where ny is odd; there their segments are as long as that
+    // takes.
+    if (fp32 && !p.fd && p.nz == 256 && tc.ntiles * (long long)tc.nseg > kMaxStepPartials) {
+        const TileCfg pairs = row_tiles(p, 256, segment_x);
+        if (pairs.ntiles * (long long)pairs.nseg <= kMaxStepPartials) {
+            const int most = kMaxStepPartials / tc.ntiles;
+            tc.sx = (p.nx + most - 1) / most;
+            tc.nseg = (p.nx + tc.sx - 1) / tc.sx;
+        }
+    }
+    return tc;
 }
 
 // Flat tiles or row tiles.  Measured (us per step, rows / flat): FP32 128^3
@@ -319,16 +340,20 @@ TileCfg row_tile_config(const KParams& p, int segment_x)
 // (flat tiles re-read more through L2), 100 x 120 x 240 340 / 346, but 96^3
 // 119 / 111, 151 x 105 x 150 409 / 354: flat where row tiles leave more than a
 // tenth of their lanes idle along z.  Up to 120000 sites, whose segments are
-// short, row tiles.
+// short, row tiles.  Flat tiles take no more workgroups than the array of the
+// allocation-free sums holds partials for, unless row tiles do too: what row
+// tiles can sum there, flat tiles can (there are never more flat tiles in a
+// plane than row tiles).
 TileCfg tile_config(const KParams& p, int segment_x, bool fp32)
 {
-    const TileCfg rows = row_tile_config(p, segment_x);
+    const TileCfg rows = row_tile_config(p, segment_x, fp32);
     if (!flat_fits(p, fp32) || p.nsites <= 120000) return rows;
     TileCfg flat = rows;
     flat.tz = 0;
     flat.nty = 1;
     flat.ntz = (p.ny * p.nz + kFused - 1) / kFused;
-    flat = with_segments(p, flat, segment_x);
+    flat = with_segments(p, flat, segment_x,
+                         std::max((long long)rows.ntiles * rows.nseg, (long long)kMaxStepPartials));
     if (fp32) {
         const long long r = march_cost(rows), f = march_cost(flat);
         return f < r || (f == r && flat.sx >= 8) ? flat : rows;

@@ -6,6 +6,7 @@ import ctypes
 import random
 import re
 
+import numpy as np
 import pytest
 
 from test_abi_cpu import _params, abi  # noqa: F401  (fixture)
@@ -63,3 +64,41 @@ def test_scratch_holds_the_partials_of_every_step(abi, prec, kw):  # noqa: F811
         need = _noalloc_blocks(abi, ctx)
         abi.lib().lb_destroy(ctx)
         assert rows >= need, (shape, rows, need)
+
+
+def _row_blocks(shape, prec, segment_x):
+    """Workgroups of the march over row tiles: 8 x 64 or 4 x 128 columns (FP32
+    storage with rows of 256 sites: 2 x 256), in segments of segment_x planes
+    or the fewest with the least rounds * (planes + 2)."""
+    nx, ny, nz = shape
+    tz = 64 if 64 * -(-nz // 64) < 128 * -(-nz // 128) else 128
+    if prec == 1 and nz == 256:
+        tz = 256
+    tiles = -(-ny // (512 // tz)) * -(-nz // tz)
+    if segment_x:
+        return tiles * -(-nx // min(segment_x, nx))
+    s = -(-nx // np.arange(1, nx + 1, dtype=np.int64))
+    blocks = tiles * -(-nx // s)
+    cost = -(-blocks // 256) * (s + 2)
+    return int(blocks[int(np.argmin(cost))])
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(tau_g=1.3), dict(kernel=2), dict(segment_x=2),
+                                dict(segment_x=5, halo_x=1)],
+                         ids=["default", "tau_g1.3", "stream", "segment2", "segment5-shard"])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_noalloc_sums_take_every_lattice_whose_row_tiles_fit(abi, prec, kw):  # noqa: F811
+    """Whatever tiling the march runs over."""
+    fits = 0
+    pairs = [(4182, 1, 256), (1106, 13, 256), (10606, 1, 256), (2, 8191, 256)]
+    for shape in FLAT + pairs + _random_shapes(400, seed=6):
+        if "halo_x" in kw and shape[0] < 2:
+            continue
+        ctx, _ = _create(abi, shape, precision=prec, **kw)
+        need = _noalloc_blocks(abi, ctx)
+        abi.lib().lb_destroy(ctx)
+        blocks = _row_blocks(shape, prec, kw.get("segment_x", 0))
+        fit = blocks <= abi.NOALLOC_MAX_PARTIALS
+        fits += fit
+        assert (need == 0) == fit, (shape, need, blocks)
+    assert fits > 150

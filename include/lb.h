@@ -196,8 +196,11 @@ typedef struct {
 } lb_sizes;
 
 /* Caller-owned device memory.  state[0..1] are the two time levels the step
- * ping-pongs between; the adjoint buffers may be NULL if lb_adjoint_* is never
- * called. */
+ * ping-pongs between: one of them holds the current level.  Between calls
+ * state[0] always holds a level, the current one or, if that is in state[1],
+ * the one a step before it; state[1] holds none while state[0] is current
+ * (steps of one call leave each other less than a level there).  The adjoint
+ * buffers may be NULL if lb_adjoint_* is never called. */
 typedef struct {
     void *state[2];
     void *phi;

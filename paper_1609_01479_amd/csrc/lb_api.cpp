@@ -356,32 +356,42 @@ static lb_status step_n(lb_ctx* ctx, int32_t nsteps, double* sums_dev, const cha
     if (ctx->kp.xh && nsteps > 1)
         return fail(LB_EINVAL, "an x-slab shard advances one step per call (its halo planes "
                                "are exchanged between steps); got nsteps = %d", nsteps);
-    // the levels between this call's steps can be compact
-    const bool between = nsteps > 1 && lbk::can_compact(ctx->kp, ctx->tc, ctx->fp32, ctx->p.kernel);
-    const bool f_too = between && lbk::compact_f(ctx->kp, ctx->fp32, sums_dev != nullptr);
-    // partial blocks of step t
-    auto blocks = [&](int32_t t) -> size_t {
-        if (f_too && t > 0) return lbk::compact_step_tiles(ctx->kp, ctx->fp32).blocks();
-        return between ? lbk::collide_grid(ctx->kp, true) : sums_blocks(ctx);
-    };
-    for (int32_t t = 0; sums_dev && t < std::min(nsteps, 2); t++)
-        if (blocks(t) > rows)
+    // Levels 1 .. last between this call's steps are compact.  state[0] is left a
+    // level whichever buffer the call ends in (a sibling context on these
+    // buffers starts there), so one more is full where it ends in state[1].
+    int32_t last = nsteps - 1 - ((ctx->cur + nsteps) & 1);
+    if (!lbk::can_compact(ctx->kp, ctx->tc, ctx->fp32, ctx->p.kernel)) last = 0;
+    const bool f_too = last > 0 && lbk::compact_f(ctx->kp, ctx->fp32, sums_dev != nullptr);
+    auto from_compact = [&](int32_t t) { return t > 0 && t <= last; };
+    auto to_compact = [&](int32_t t) { return t < last; };
+    // partial blocks of a step between full levels, of one that collides one
+    // site per thread, and of one from a level with f's moments
+    size_t nb_full = 0, nb_collide = 0, nb_moments = 0;
+    if (sums_dev) {
+        nb_full = sums_blocks(ctx);
+        if (last > 0) nb_collide = lbk::collide_grid(ctx->kp, true);
+        if (f_too) nb_moments = lbk::compact_step_tiles(ctx->kp, ctx->fp32).blocks();
+        const size_t most = std::max({nb_full, nb_collide, nb_moments});
+        if (most > rows)
             return fail(LB_ESTATE, "%s: a step reduces over %zu partial blocks, the array holds %zu",
-                        name, blocks(t), rows);
+                        name, most, rows);
+    }
+    auto blocks = [&](int32_t t) {
+        return from_compact(t) && f_too ? nb_moments
+               : from_compact(t) || to_compact(t) ? nb_collide : nb_full;
+    };
     int32_t held = 0;  // steps whose partials wait in part, nb blocks each
-    size_t nb = sums_dev ? blocks(0) : 0;
+    size_t nb = blocks(0);
     for (int32_t t = 0; t < nsteps; t++) {
-        const int compact = !between ? 0
-                                     : (t > 0 ? lbk::kCompactSrc : 0) |
-                                           (t + 1 < nsteps ? lbk::kCompactDst : 0) |
-                                           (f_too ? lbk::kCompactF : 0);
+        int compact = (from_compact(t) ? lbk::kCompactSrc : 0) | (to_compact(t) ? lbk::kCompactDst : 0);
+        if (compact && f_too) compact |= lbk::kCompactF;
         hipError_t e = one_step(ctx, ctx->b.state[ctx->cur], ctx->b.state[1 - ctx->cur],
                                 sums_dev ? part + size_t(held) * 5 * nb : nullptr, nullptr, compact);
         if (e != hipSuccess) return hip_fail(e, name);
         ctx->cur = 1 - ctx->cur;
         if (!sums_dev) continue;
         held++;
-        const size_t next = t < 1 && nsteps > 1 ? blocks(t + 1) : nb;
+        const size_t next = blocks(t + 1);
         if (t + 1 < nsteps && next == nb && held < std::min<size_t>(rows / nb, 4096)) continue;
         e = lbk::launch_sums_final(part, int(nb), 5, held, sums_dev + 5 * size_t(t + 1 - held),
                                    ctx->stream);

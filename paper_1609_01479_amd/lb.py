@@ -115,8 +115,9 @@ class LB:
         """A second context on this lattice's own device buffers and stream
         that steps with another kernel variant ("fused", "two_pass" or
         "stream"), e.g. to time a kernel and its memory-only twin on the same
-        memory.  It starts at time level 0 of the shared buffers; the caller
-        keeps the two contexts from stepping over each other's levels."""
+        memory.  It starts at time level 0 of the shared buffers (this
+        lattice's current level after an even number of steps, the one a step
+        before it after an odd one); the caller keeps the two contexts from stepping over each other's levels."""
         L = _abi.lib()
         sib = object.__new__(LB)
         sib.__dict__.update({k: v for k, v in self.__dict__.items() if k != "_ctx"})

@@ -412,6 +412,8 @@ hipError_t launch_force_collide(const KParams& p, const TileCfg& tc, bool fp32, 
                                 int compact, const void* src, void* dst, double* phi,
                                 double* partials, hipStream_t s)
 {
+    // (the box form exists in FP32 storage alone: step_variant)
+    if (variant == kStepBox && !fp32) return hipErrorInvalidValue;
     if (variant == kStepBox)
         return launch_box_t<float, true, true>(p, p.omega_g == 1.0, src, dst, phi, partials, s);
     const TileCfg ft = force_tiles(p, tc.seg_req);

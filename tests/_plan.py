@@ -32,16 +32,20 @@ int main()
 """
 
 
-def tilings(tmp_path, lattices):
-    """(tile width, tiles, segments) of the march of the LB scheme's step for
-    each (shape, segment_x, FP32 storage, tau_g); width 0: flat tiles."""
+def run(tmp_path, source, text=""):
+    """What a program against the library's internal header prints."""
     src, exe = tmp_path / "plan.cpp", tmp_path / "plan"
-    src.write_text(SOURCE)
+    src.write_text(source)
     subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
                     "-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG, "csrc"), str(src),
                     "-o", str(exe), os.path.join(PKG, "liblbmi.so"), f"-Wl,-rpath,{PKG}",
                     "-L/opt/rocm/lib", "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib"], check=True)
+    return subprocess.run([str(exe)], input=text, check=True, capture_output=True, text=True).stdout
+
+
+def tilings(tmp_path, lattices):
+    """(tile width, tiles, segments) of the march of the LB scheme's step for
+    each (shape, segment_x, FP32 storage, tau_g); width 0: flat tiles."""
     text = "".join(f"{x} {y} {z} {seg} {int(fp32)} {tau_g}\n"
                    for (x, y, z), seg, fp32, tau_g in lattices)
-    out = subprocess.run([str(exe)], input=text, check=True, capture_output=True, text=True).stdout
-    return [tuple(map(int, line.split())) for line in out.splitlines()]
+    return [tuple(map(int, line.split())) for line in run(tmp_path, SOURCE, text).splitlines()]

@@ -178,6 +178,8 @@ def rollout(phi0: torch.Tensor, A, B, kappa, nsteps: int, *, interval: int | str
     few recomputed steps.  The gradients do not depend on k (the recomputed
     states are bit-identical).  info (a dict, optional) receives "interval",
     the k used."""
+    if interval is not None and interval != "auto" and int(interval or 1) < 1:
+        raise ValueError(f"interval must be at least 1 (got {interval!r})")
     as_t = lambda v: v if torch.is_tensor(v) else torch.tensor(float(v), dtype=torch.float64)  # noqa: E731
     cfg = dict(nsteps=nsteps, interval=interval, memory_budget=memory_budget, gamma=gamma,
                tau_f=tau_f, tau_g=tau_g, rho0=rho0, precision=precision,

@@ -1215,12 +1215,19 @@ static int fd_collide_grid(const KParams& p) { return (p.nsites + site_block(p) 
 // 32^3 98 / 121 / 68 and 1477 / 901 / 906; FP64 32^3 114 / 119 / 72 and 1793 /
 // 938 / 979.  Above that the stress coupling marches as long as that keeps up
 // with two launches: FP32 40^3 73 / 119 and 965 / 934, 48^3 83 / 119 and 1118 /
-// 1060; FP64 40^3 86 / 119 and 1128 / 1014, 48^3 117 / 120 and 1769 / 1234.
+// 1060; FP64 40^3 86 / 119 and 1128 / 1014, 48^3 117 / 120 and 1769 / 1234.  FP32
+// storage keeps up again where the tiles leave no more than two planes to a
+// segment and the two passes have left their own launch time behind (runs of 5 /
+// 50 steps, march / two passes: 50^3 91 / 115 and 648 / 574, 56^3 92 / 116 and
+// 639 / 641, there 50-step rollouts 2363 / 2318; 64 x 50 x 64 92 / 118 and 637 /
+// 706, 64^3 99 / 113 and 721 / 736; with 4 planes 52 x 60 x 70 124 / 115 and 961
+// / 732).
 static int fd_variant(const KParams& p, const TileCfg& tc, bool fp32, int variant, bool sums)
 {
     if (variant != 0 || tc.seg_req > 0) return variant;
     if (box_cfg(p).blocks() <= 512) return kStepBox;
     if (!p.force && p.nsites <= (fp32 ? 120000 : 75000)) return 0;
+    if (!p.force && fp32 && p.nsites >= 200000 && p.nsites <= 270000 && march_cost(tc) <= 4) return 0;
     if (sums && fd_collide_grid(p) > kMaxStepPartials) return 0;
     const int limit = !fp32 ? 900000 : p.force ? 1300000 : 450000;
     return p.nsites <= limit ? 1 : 0;

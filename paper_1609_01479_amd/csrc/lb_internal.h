@@ -62,6 +62,8 @@ inline Lvl<T> level(void* state, const KParams& p, bool ref)
 // segment_x <= 0 picks the segment length automatically.  row_tile_config:
 // the row tiling, whatever tile_config picks.
 TileCfg tile_config(const KParams& p, int segment_x, bool fp32);
+// rounds of workgroups * (planes + 2): what a tiling's march takes, in planes
+long long march_cost(const TileCfg& tc);
 TileCfg row_tile_config(const KParams& p, int segment_x, bool fp32);
 
 // Fills the layout fields of k (nx, ny, nz and stride set) for an lb_layout.

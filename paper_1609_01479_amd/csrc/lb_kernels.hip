@@ -265,8 +265,7 @@ static bool flat_fits(const KParams& p, bool fp32)
     return 2 * p.nz + (fp32 && kFused % p.nz ? 4 : 0) <= kFused;
 }
 
-// rounds * (planes + 2) of a tiling: what its march takes, in planes
-static long long march_cost(const TileCfg& tc)
+long long march_cost(const TileCfg& tc)
 {
     return (long long)((tc.ntiles * (long long)tc.nseg + kCUs - 1) / kCUs) * (tc.sx + 2);
 }
@@ -387,8 +386,16 @@ TileCfg tile_config(const KParams& p, int segment_x, bool fp32)
 // 917 / 956; force FP32 16^3 131 / 125 / 105 and 1925 / 850 / 671, 28^3 (343
 // boxes) 125 / 121 / 127 and 1786 / 958 / 1020; force FP64 16^3 135 / 124 / 130
 // and 2047 / 871 / 900.  Above that, FP32 storage marches, one launch too, as
-// long as the march keeps up with two: 40^3 81 / 117 and 1015 / 1010, 48^3 104 /
-// 119 and 1519 / 1187.
+// long as the march keeps up with two: 40^3 81 / 117 and 1015 / 1010; further
+// where a segment is one plane (5 / 50 steps): 42 x 42 x 44 83 / 128 and 547 /
+// 578, 44 x 40 x 50 85 / 117 and 571 / 593, but 17 x 56 x 100 88 / 114 and 607 /
+// 588, and with two planes 44^3 103 / 114 and 756 / 605.
+// The number of steps does not enter.  In a run of 3 to 5 steps the host's wait
+// shows and the march would win further up (us of the run, two passes / march:
+// 40^3 FP64 3 steps 101 / 69, 5 114 / 96; 48^3 FP32 105 / 74, 117 / 104), but the
+// same steps called alone (44 / 53, 75 / 81; 44 / 58, 78 / 88) or one call after
+// another (36 / 42, 56 / 70; 36 / 47, 58 / 77) would lose, and a call does not
+// know which it is.
 int step_variant(const KParams& p, const TileCfg& tc, bool fp32, int variant, bool sums)
 {
     // a segment length asked for is the marching kernel's; shards have no
@@ -399,7 +406,8 @@ int step_variant(const KParams& p, const TileCfg& tc, bool fp32, int variant, bo
     const int limit = p.force ? (g1 ? 7100000 : fp32 ? 1100000 : 1500000)
                               : (g1 ? 2000000 : fp32 ? 700000 : 300000);
     if (box_cfg(p).blocks() <= (!p.force ? 512 : fp32 ? 256 : 0)) return kStepBox;
-    if (!p.force && fp32 && p.nsites <= 75000) return 0;
+    if (!p.force && fp32 && (p.nsites <= 75000 || (p.nsites <= 90000 && march_cost(tc) <= 3)))
+        return 0;
     return p.nsites <= limit ? 1 : 0;
 }
 

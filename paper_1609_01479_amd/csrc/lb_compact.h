@@ -298,7 +298,7 @@ __global__ __launch_bounds__(kCompactThreads) void k_step_compact_march(
     constexpr int MID[9] = {0, 3, 4, 5, 6, 15, 16, 17, 18};
     for (int X = x0 - 1; X <= x1; X++) {
         T h[NV];
-        hermite_f(e, h);
+        hermite_f<T, !DEV && !FORCE>(e, h);
         if (cell) {
 #pragma unroll
             for (int i = 3; i < NV; i++) lds[i - 3][c] = h[i];
@@ -354,7 +354,7 @@ __global__ __launch_bounds__(kCompactThreads) void k_step_compact_march(
                 }
                 if constexpr (TO_FULL) {
                     T g[NV];
-                    hermite_f(d, f);
+                    hermite_f<T, !DEV && !FORCE>(d, f);
 #pragma unroll
                     for (int i = 0; i < NV; i++) dF[dist_own(p, q, i)] = f[i];
                     if constexpr (FORCE)

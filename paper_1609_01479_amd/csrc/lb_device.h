@@ -301,7 +301,24 @@ struct FEq {
     T b, ax, ay, az, xx, yy, zz, xy, xz, yz;
 };
 
-template <typename T>
+// w q + a and w q - a of an opposite pair.  ONCE: each rounded once.
+template <bool ONCE, typename T>
+__device__ __forceinline__ void hermite_pair(T w, T q, T a, T* eq)
+{
+    if constexpr (ONCE) {
+        eq[0] = __builtin_fma(w, q, a);
+        eq[1] = __builtin_fma(w, q, -a);
+    } else {
+        const T s = w * q;
+        eq[0] = s + a;
+        eq[1] = s - a;
+    }
+}
+
+// ONCE: as the FP64 step of the stress coupling rounds it in every form.  Where
+// contraction stays within an expression (lb_step_f64.hip), w q would be rounded
+// on its own, and rho and u after 10 steps be 1.1 % further from exact values.
+template <typename T, bool ONCE = false>
 __device__ __forceinline__ void hermite_f(const FEq<T>& e, T* eq)
 {
     const T b = e.b, jx = e.ax, jy = e.ay, jz = e.az;
@@ -314,27 +331,27 @@ __device__ __forceinline__ void hermite_f(const FEq<T>& e, T* eq)
 
     eq[0] = w0 * (b - h * tm);
     {
-        const T sx = wf * (b + h * (mxx - tm)), ax = wf3 * jx;
-        const T sy = wf * (b + h * (myy - tm)), ay = wf3 * jy;
-        const T sz = wf * (b + h * (mzz - tm)), az = wf3 * jz;
-        eq[1] = sx + ax; eq[2] = sx - ax;
-        eq[3] = sy + ay; eq[4] = sy - ay;
-        eq[5] = sz + az; eq[6] = sz - az;
+        const T qx = b + h * (mxx - tm), ax = wf3 * jx;
+        const T qy = b + h * (myy - tm), ay = wf3 * jy;
+        const T qz = b + h * (mzz - tm), az = wf3 * jz;
+        hermite_pair<ONCE>(wf, qx, ax, eq + 1);
+        hermite_pair<ONCE>(wf, qy, ay, eq + 3);
+        hermite_pair<ONCE>(wf, qz, az, eq + 5);
     }
     {
         const T dxy = mxx + myy - tm, dxz = mxx + mzz - tm, dyz = myy + mzz - tm;
-        const T s7 = we * (b + h * (dxy + T(2) * mxy)), a7 = we3 * (jx + jy);
-        const T s9 = we * (b + h * (dxy - T(2) * mxy)), a9 = we3 * (jx - jy);
-        const T s11 = we * (b + h * (dxz + T(2) * mxz)), a11 = we3 * (jx + jz);
-        const T s13 = we * (b + h * (dxz - T(2) * mxz)), a13 = we3 * (jx - jz);
-        const T s15 = we * (b + h * (dyz + T(2) * myz)), a15 = we3 * (jy + jz);
-        const T s17 = we * (b + h * (dyz - T(2) * myz)), a17 = we3 * (jy - jz);
-        eq[7] = s7 + a7;     eq[8] = s7 - a7;
-        eq[9] = s9 + a9;     eq[10] = s9 - a9;
-        eq[11] = s11 + a11;  eq[12] = s11 - a11;
-        eq[13] = s13 + a13;  eq[14] = s13 - a13;
-        eq[15] = s15 + a15;  eq[16] = s15 - a15;
-        eq[17] = s17 + a17;  eq[18] = s17 - a17;
+        const T q7 = b + h * (dxy + T(2) * mxy), a7 = we3 * (jx + jy);
+        const T q9 = b + h * (dxy - T(2) * mxy), a9 = we3 * (jx - jy);
+        const T q11 = b + h * (dxz + T(2) * mxz), a11 = we3 * (jx + jz);
+        const T q13 = b + h * (dxz - T(2) * mxz), a13 = we3 * (jx - jz);
+        const T q15 = b + h * (dyz + T(2) * myz), a15 = we3 * (jy + jz);
+        const T q17 = b + h * (dyz - T(2) * myz), a17 = we3 * (jy - jz);
+        hermite_pair<ONCE>(we, q7, a7, eq + 7);
+        hermite_pair<ONCE>(we, q9, a9, eq + 9);
+        hermite_pair<ONCE>(we, q11, a11, eq + 11);
+        hermite_pair<ONCE>(we, q13, a13, eq + 13);
+        hermite_pair<ONCE>(we, q15, a15, eq + 15);
+        hermite_pair<ONCE>(we, q17, a17, eq + 17);
     }
 }
 
@@ -365,13 +382,13 @@ __device__ __forceinline__ Vel<T> feq_stress(const KParams& p, const T* f, const
     return Vel<T>{ux, uy, uz};
 }
 
-template <typename T, bool DEV>
+template <typename T, bool DEV, bool ONCE = false>
 __device__ __forceinline__ Vel<T> collide_f(const KParams& p, T* f, const Stencil& st)
 {
     FEq<T> e;
     const Vel<T> u = feq_stress<T, DEV>(p, f, st, e);
     T eq[NV];
-    hermite_f(e, eq);
+    hermite_f<T, ONCE>(e, eq);
     const T omf = T(p.omega_f);
     // FP64 with omega_f = 1: f* = f^eq, as a compact level keeps it
     const bool one = !DEV && omf == T(1);
@@ -451,7 +468,7 @@ __device__ __forceinline__ T chem_potential(const KParams& p, const Stencil& st)
 template <typename T, bool DEV, bool REF, bool G1 = false>
 __device__ __forceinline__ void collide(const KParams& p, T* f, T* g, const Stencil& st)
 {
-    const Vel<T> u = collide_f<T, DEV>(p, f, st);
+    const Vel<T> u = collide_f<T, DEV, !DEV>(p, f, st);
     collide_g<T, REF, G1>(p, g, T(st.phi), chem_potential<T>(p, st), u);
 }
 

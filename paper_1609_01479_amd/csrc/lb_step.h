@@ -108,7 +108,7 @@ __global__ __launch_bounds__(kBlock) void k_step_2s(KParams p, const T* __restri
             store_feq(p, dF, s, e);
             return;
         } else if constexpr (COMPACT == 1) {
-            const Vel<T> u = collide_f<T, DEV>(p, f, st);
+            const Vel<T> u = collide_f<T, DEV, !DEV>(p, f, st);
             compact_mu_u(dG, p)[s] = MuU<T>{chem_potential<T>(p, st), u.x, u.y, u.z};
         } else {
             collide<T, DEV, REF, G1>(p, f, g, st);

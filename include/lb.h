@@ -196,11 +196,10 @@ typedef struct {
 } lb_sizes;
 
 /* Caller-owned device memory.  state[0..1] are the two time levels the step
- * ping-pongs between: one of them holds the current level.  Between calls
- * state[0] always holds a level, the current one or, if that is in state[1],
- * the one a step before it; state[1] holds none while state[0] is current
- * (steps of one call leave each other less than a level there).  The adjoint
- * buffers may be NULL if lb_adjoint_* is never called. */
+ * ping-pongs between: one of them holds the current level, and after a call of
+ * several steps the other need hold none (the steps of one call leave each other
+ * less: lb_share_levels).  The adjoint buffers may be NULL if lb_adjoint_* is
+ * never called. */
 typedef struct {
     void *state[2];
     void *phi;
@@ -346,6 +345,14 @@ lb_status lb_sums(lb_ctx *ctx, double *out5_dev);
  * Sec. 3.2.3. */
 lb_status lb_get_state(lb_ctx *ctx, void *dst_dev);
 lb_status lb_set_state(lb_ctx *ctx, const void *src_dev);
+
+/* For a second context on this context's buffers, which starts at state[0]:
+ * makes state[0] a level, the current one or (where that is in state[1]) the one
+ * a step before it, and every later call leaves it one.  Needs the buffer
+ * tmp_dev (state_bytes, 256-byte aligned, free again once the stream has passed
+ * this call) only if state[0] holds no level now: LB_ESTATE if it is NULL then.
+ * Both contexts need the call.  Passage: none (a project extension). */
+lb_status lb_share_levels(lb_ctx *ctx, void *tmp_dev);
 
 /* Current state as dense FP64 post-propagation distributions, each of shape
  * (19, nx, ny, nz); either pointer may be NULL.  LB_OP_FD has no g: g_dev

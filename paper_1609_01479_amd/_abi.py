@@ -22,7 +22,7 @@ NOALLOC_MAX_PARTIALS = 4096  # LB_NOALLOC_MAX_PARTIALS
 # Every symbol include/lb.h declares.
 EXPORTS = ("lb_abi_version", "lb_query_sizes", "lb_create", "lb_destroy", "lb_set_stream",
            "lb_init_phi", "lb_step", "lb_step_sums", "lb_step_sums_noalloc", "lb_step_from", "lb_step_from_phi",
-           "lb_step_chain", "lb_step_segment", "lb_level_phi", "lb_moments", "lb_sums", "lb_get_state", "lb_set_state",
+           "lb_step_chain", "lb_step_segment", "lb_level_phi", "lb_moments", "lb_sums", "lb_get_state", "lb_set_state", "lb_share_levels",
            "lb_export_dist", "lb_import_dist", "lb_adjoint_seed", "lb_adjoint_step",
            "lb_adjoint_step_phi", "lb_adjoint_chain", "lb_adjoint_phi0", "lb_adjoint_export", "lb_pack_faces",
            "lb_unpack_faces", "lb_copy_probe",
@@ -92,6 +92,7 @@ def lib():
         "lb_sums": ([vp, dp], ctypes.c_int),
         "lb_get_state": ([vp, vp], ctypes.c_int),
         "lb_set_state": ([vp, vp], ctypes.c_int),
+        "lb_share_levels": ([vp, vp], ctypes.c_int),
         "lb_export_dist": ([vp, dp, dp], ctypes.c_int),
         "lb_import_dist": ([vp, dp, dp], ctypes.c_int),
         "lb_adjoint_seed": ([vp, dp], ctypes.c_int),

@@ -144,6 +144,9 @@ struct lb_ctx {
     lbk::TileCfg tc;
     bool fp32;
     int cur;      // time level holding the current state
+    int other;    // what state[1 - cur] holds: 0 a level (or nothing yet), else the
+                  // form of the compact level there (kCompactSrc, kCompactF)
+    bool shared;  // other contexts start from state[0] (lb_share_levels)
     int adj_cur;  // adjoint level holding the current lambda
     bool has_adj;
 };
@@ -286,6 +289,8 @@ lb_status lb_create(const lb_params* p, const lb_buffers* b, void* hip_stream, l
     c->stream = static_cast<hipStream_t>(hip_stream);
     c->fp32 = p->precision == LB_FP32_DEV;
     c->cur = 0;
+    c->other = 0;
+    c->shared = false;
     c->adj_cur = 0;
     c->has_adj = all_adj;
     c->kp = kernel_params(p);
@@ -307,6 +312,7 @@ lb_status lb_init_phi(lb_ctx* ctx, const double* phi0_dev)
 {
     if (!ctx || !phi0_dev) return fail(LB_EINVAL, "ctx and phi0_dev are required");
     ctx->cur = 0;
+    ctx->other = 0;
     hipError_t e = ctx->kp.fd
                        ? lbk::launch_fd_init(ctx->kp, ctx->fp32, ctx->b.state[0], phi0_dev, ctx->stream)
                        : lbk::launch_init(ctx->kp, ctx->fp32, ctx->b.state[0], phi0_dev, ctx->stream);
@@ -356,10 +362,9 @@ static lb_status step_n(lb_ctx* ctx, int32_t nsteps, double* sums_dev, const cha
     if (ctx->kp.xh && nsteps > 1)
         return fail(LB_EINVAL, "an x-slab shard advances one step per call (its halo planes "
                                "are exchanged between steps); got nsteps = %d", nsteps);
-    // Levels 1 .. last between this call's steps are compact.  state[0] is left a
-    // level whichever buffer the call ends in (a sibling context on these
-    // buffers starts there), so one more is full where it ends in state[1].
-    int32_t last = nsteps - 1 - ((ctx->cur + nsteps) & 1);
+    // Levels 1 .. last between this call's steps are compact; where the buffers
+    // are shared, not the last one if it stays in state[0].
+    int32_t last = nsteps - 1 - (ctx->shared ? (ctx->cur + nsteps) & 1 : 0);
     if (!lbk::can_compact(ctx->kp, ctx->tc, ctx->fp32, ctx->p.kernel)) last = 0;
     const bool f_too = last > 0 && lbk::compact_f(ctx->kp, ctx->fp32, sums_dev != nullptr);
     auto from_compact = [&](int32_t t) { return t > 0 && t <= last; };
@@ -389,6 +394,7 @@ static lb_status step_n(lb_ctx* ctx, int32_t nsteps, double* sums_dev, const cha
                                 sums_dev ? part + size_t(held) * 5 * nb : nullptr, nullptr, compact);
         if (e != hipSuccess) return hip_fail(e, name);
         ctx->cur = 1 - ctx->cur;
+        ctx->other = from_compact(t) ? compact & (lbk::kCompactF | lbk::kCompactSrc) : 0;
         if (!sums_dev) continue;
         held++;
         const size_t next = blocks(t + 1);
@@ -569,6 +575,30 @@ lb_status lb_set_state(lb_ctx* ctx, const void* src_dev)
     hipError_t e = hipMemcpyAsync(ctx->b.state[ctx->cur], src_dev, ctx->sz.state_bytes,
                                   hipMemcpyDeviceToDevice, ctx->stream);
     return e == hipSuccess ? LB_OK : hip_fail(e, "lb_set_state");
+}
+
+lb_status lb_share_levels(lb_ctx* ctx, void* tmp_dev)
+{
+    if (!ctx) return fail(LB_EINVAL, "ctx is NULL");
+    void* level0 = ctx->b.state[0];
+    if (ctx->cur == 1 && ctx->other) {
+        if (!tmp_dev) return fail(LB_ESTATE, "state[0] holds no level: a buffer is needed to make one");
+        if (!aligned(tmp_dev)) return fail(LB_EALIGN, "tmp_dev is not 256-byte aligned");
+        if (tmp_dev == level0 || tmp_dev == ctx->b.state[1])
+            return fail(LB_EINVAL, "tmp_dev is one of the context's levels");
+        const bool moments = ctx->other & lbk::kCompactF;
+        hipError_t e = ctx->kp.force ? lbk::launch_full_level_force(ctx->kp, ctx->fp32, moments, level0,
+                                                                    tmp_dev, ctx->stream)
+                                     : lbk::launch_full_level_f64(ctx->kp, moments, level0, tmp_dev,
+                                                                  ctx->stream);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(level0, tmp_dev, ctx->sz.state_bytes, hipMemcpyDeviceToDevice,
+                               ctx->stream);
+        if (e != hipSuccess) return hip_fail(e, "lb_share_levels");
+        ctx->other = 0;
+    }
+    ctx->shared = true;
+    return LB_OK;
 }
 
 lb_status lb_export_dist(lb_ctx* ctx, double* f_dev, double* g_dev)

@@ -385,6 +385,40 @@ __global__ __launch_bounds__(kCompactThreads) void k_step_compact_march(
     if (SUMS) block_partials<5, kCompactThreads>(acc, partials);
 }
 
+// The full level of a compact one, as the step that left it would have written
+// it: one site per thread, bound by memory (once, when the buffers come to be
+// shared).  MOMENTS: f as its ten moments.
+template <typename T, bool REF, bool FORCE, bool MOMENTS>
+__global__ __launch_bounds__(kBlock) void k_full_level(KParams p, const T* __restrict__ sF,
+                                                       const double* __restrict__ cphi,
+                                                       const MuU<T>* __restrict__ mu_u,
+                                                       T* __restrict__ dF, T* __restrict__ dG,
+                                                       unsigned* __restrict__ dphic)
+{
+    const int s = xcd_block() * int(blockDim.x) + threadIdx.x;
+    if (s >= p.nsites) return;
+    const Geo q = geo_of(p, s);
+    T f[NV], g[NV];
+    if constexpr (MOMENTS) {
+        hermite_f<T, !REF && !FORCE>(load_feq(p, sF, s), f);
+    } else {
+#pragma unroll
+        for (int i = 0; i < NV; i++) f[i] = sF[dist_own(p, q, i)];
+    }
+    const double ph = cphi[s];
+    const MuU<T> m = mu_u[s];
+    if constexpr (FORCE)
+        collide_force_g<T, REF, true>(p, g, ph, double(m.mu), Vel<T>{m.ux, m.uy, m.uz});
+    else
+        collide_g<T, REF, true>(p, g, T(ph), m.mu, Vel<T>{m.ux, m.uy, m.uz});
+#pragma unroll
+    for (int i = 0; i < NV; i++) {
+        dF[dist_own(p, q, i)] = f[i];
+        dG[dist_own(p, q, i)] = REF ? to_dest_ref(i, g[i], ph, cphi[push_site(p, q, i)]) : g[i];
+    }
+    if (REF) dphic[phic_site(p, q.x, q.y, q.z)] = phic_word(ph);
+}
+
 // phi of the compact level `state`, its own phi field cphi if that is given;
 // next (may be null): the level a step makes, whose phi_c the pass stores.
 template <typename T, bool FORCE>
@@ -423,6 +457,20 @@ hipError_t launch_step_compact_t(const KParams& p, const void* src, void* dst, b
              : to_full ? k_step_compact_march<T, F32, F32, FORCE, true, false>
                        : k_step_compact_march<T, F32, F32, FORCE, false, false>;
     k<<<t.blocks(), kCompactThreads, 0, s>>>(p, t.nty, t.ntz, t.sx, F, phi, d.F, d.G, partials);
+    return hipGetLastError();
+}
+
+template <typename T, bool FORCE>
+hipError_t launch_full_level_t(const KParams& p, bool moments, const void* src, void* dst,
+                               hipStream_t s)
+{
+    constexpr bool F32 = sizeof(T) == 4;
+    const Lvl<T> a = level<T>(const_cast<void*>(src), p, F32);
+    const Lvl<T> d = level<T>(dst, p, F32);
+    const int nb = site_block(p);
+    auto k = moments ? k_full_level<T, F32, FORCE, true> : k_full_level<T, F32, FORCE, false>;
+    k<<<(p.nsites + nb - 1) / nb, nb, 0, s>>>(p, a.F, compact_phi(a.G), compact_mu_u(a.G, p), d.F,
+                                              d.G, d.phic);
     return hipGetLastError();
 }
 

@@ -471,4 +471,11 @@ hipError_t launch_step_compact_force(const KParams& p, bool fp32, const void* sr
                 : launch_step_compact_t<double, true>(p, src, dst, to_full, phi, partials, s);
 }
 
+hipError_t launch_full_level_force(const KParams& p, bool fp32, bool moments, const void* src,
+                                   void* dst, hipStream_t s)
+{
+    return fp32 ? launch_full_level_t<float, true>(p, moments, src, dst, s)
+                : launch_full_level_t<double, true>(p, moments, src, dst, s);
+}
+
 }  // namespace lbk

@@ -159,6 +159,11 @@ hipError_t launch_step_compact_f64(const KParams& p, const void* src, void* dst,
 hipError_t launch_step_compact_force(const KParams& p, bool fp32, const void* src, void* dst,
                                      bool to_full, const double* phi, double* partials,
                                      hipStream_t s);
+// The full level `dst` of the compact level `src` (moments: with f's moments).
+hipError_t launch_full_level_f64(const KParams& p, bool moments, const void* src, void* dst,
+                                 hipStream_t s);
+hipError_t launch_full_level_force(const KParams& p, bool fp32, bool moments, const void* src,
+                                   void* dst, hipStream_t s);
 // launch_step's kernels of the stress coupling, by storage precision; phi64
 // is the field that variant 1's phi pass left.  launch_phi_*: phi of `state`,
 // and if `next` is not null the phi_c of that level (FP32 mode).

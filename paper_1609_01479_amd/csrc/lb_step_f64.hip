@@ -69,4 +69,10 @@ hipError_t launch_step_compact_f64(const KParams& p, const void* src, void* dst,
     return launch_step_compact_t<double, false>(p, src, dst, to_full, phi, partials, s);
 }
 
+hipError_t launch_full_level_f64(const KParams& p, bool moments, const void* src, void* dst,
+                                 hipStream_t s)
+{
+    return launch_full_level_t<double, false>(p, moments, src, dst, s);
+}
+
 }  // namespace lbk

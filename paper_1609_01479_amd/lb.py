@@ -12,7 +12,7 @@ import numpy as np
 import torch
 
 from . import _abi
-from ._abi import LB_FP32_DEV, LB_FP64, NVEL, check
+from ._abi import LB_ESTATE, LB_FP32_DEV, LB_FP64, NVEL, check
 
 
 # distribution layouts (lb_layout); every layout gives bit-identical results
@@ -119,6 +119,7 @@ class LB:
         lattice's current level after an even number of steps, the one a step
         before it after an odd one); the caller keeps the two contexts from stepping over each other's levels."""
         L = _abi.lib()
+        self._share_levels()
         sib = object.__new__(LB)
         sib.__dict__.update({k: v for k, v in self.__dict__.items() if k != "_ctx"})
         sib.params = _abi.LbParams.from_buffer_copy(self.params)
@@ -142,7 +143,18 @@ class LB:
             check(L.lb_create(ctypes.byref(sib.params), ctypes.byref(bufs),
                               ctypes.c_void_p(self.stream.cuda_stream), ctypes.byref(sib._ctx)),
                   "lb_create")
+        sib._share_levels()
         return sib
+
+    def _share_levels(self) -> None:
+        """Level 0 holds a level from now on (lb_share_levels)."""
+        with torch.cuda.device(self.device):
+            st = _abi.lib().lb_share_levels(self._ctx, None)
+        if st == LB_ESTATE:
+            # allocated on this stream, so it is reused in its order only
+            self._call("lb_share_levels", _ptr(self.new_state()))
+        else:
+            check(st, "lb_share_levels")
 
     # -- lifetime -----------------------------------------------------------
     def close(self):

@@ -53,3 +53,35 @@ def test_sibling_starts_at_the_level_in_the_first_buffer(shape, coupling, prec):
                 got = torch.cat(rows)[:, 0]
                 rho = torch.stack([w[-3].sum() for w in want[:t]])
                 assert bool(((got - rho).abs() <= n * n * 2.3e-16).all())
+
+
+@pytest.mark.parametrize("shape", [(40, 40, 40), (80, 76, 75)])
+@pytest.mark.parametrize("coupling,prec", [("stress", "fp64"), ("force", "fp64"),
+                                           ("force", "fp32_dev")])
+def test_an_earlier_sibling_finds_a_level_in_the_first_buffer(shape, coupling, prec):
+    """With a sibling made before, every later call of either context leaves a
+    level in the first buffer."""
+    phi0 = lbinputs.spinodal_phi0(shape, seed=31, amp=0.3)
+    ref = make_lb(shape, precision=prec, coupling=coupling)
+    ref.init_phi(phi0)
+    want = []
+    for _ in range(9):
+        want.append(_values(ref))
+        ref.step(1)
+    lb = make_lb(shape, precision=prec, coupling=coupling)
+    lb.init_phi(phi0)
+    sib = lb.sibling("fused")
+    t = 0
+    for k in (3, 2, 3):
+        print(f"[sibling] {shape} {coupling} {prec} step {t} + {k}", flush=True)
+        lb.step(k)
+        t += k
+        for a, b in zip(_values(sib), want[t - t % 2]):
+            assert torch.equal(a, b)
+        for a, b in zip(_values(lb), want[t]):
+            assert torch.equal(a, b)
+    # and so do the sibling's own steps, from that state (ref is one step on)
+    sib.step(3)
+    ref.step(1)
+    for a, b in zip(_values(lb.sibling("fused")), _values(ref)):
+        assert torch.equal(a, b)

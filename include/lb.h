@@ -86,10 +86,14 @@ typedef enum {
 typedef enum {
     LB_KERNEL_FUSED = 0,   /* the fastest form of the step: one marching pass
                               (phi, gradients, stress, collision and
-                              propagation in one kernel), or on lattices too
-                              small for it the two passes below, with the
-                              same levels bit for bit (segment_x > 0 always
-                              marches)                                     */
+                              propagation in one kernel); on lattices too
+                              small for it the two passes below, on the
+                              smallest one launch of boxes; and in a call of
+                              several steps with LB_OP_LB and tau_g = 1 (in
+                              LB_FP32_DEV with LB_COUPLING_FORCE) two passes
+                              between levels that hold phi, mu and u for g.
+                              The same levels bit for bit (segment_x > 0
+                              always marches)                              */
     LB_KERNEL_TWO_PASS = 1, /* a phi pass, then the stencil/collision pass */
     LB_KERNEL_STREAM = 2    /* measurement twin of LB_KERNEL_FUSED: the same
                                kernel, loads, phi sums and stores with the

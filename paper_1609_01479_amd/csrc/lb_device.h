@@ -638,13 +638,6 @@ __device__ __forceinline__ void lds_barrier()
 }
 
 // ---------------------------------------------------------------------------
-// Block reduction of K FP64 values (fixed order): wavefront butterfly, then
-// the block's NB/64 waves as a pairwise tree.  Thread 0 writes component k to
-// out[k*gridDim.x + blockIdx.x].  Needs blockDim.x == NB.  Only LDS crosses
-// the barrier: a __syncthreads() here would hold every wave until the stores
-// it issued before have completed (the two-pass FP64 step with sums took 376
-// us at 128^3 so, or with the reduction ahead of the collision, where it
-// split the loads in two rounds; 256 without sums).
 // Final reduction of `nblocks` block partials of `ncomp` (at most 5)
 // components, laid out as block_partials writes them, by one workgroup of NB
 // threads (one wave or four) in a fixed order (strided per-thread sums, a
@@ -682,6 +675,13 @@ __device__ __forceinline__ void reduce_partials_block(const double* __restrict__
     }
 }
 
+// Block reduction of K FP64 values (fixed order): wavefront butterfly, then
+// the block's NB/64 waves as a pairwise tree.  Thread 0 writes component k to
+// out[k*gridDim.x + blockIdx.x].  Needs blockDim.x == NB.  Only LDS crosses
+// the barrier: a __syncthreads() here would hold every wave until the stores
+// it issued before have completed (the two-pass FP64 step with sums took 376
+// us at 128^3 so, or with the reduction ahead of the collision, where it
+// split the loads in two rounds; 256 without sums).
 template <int K, int NB = kBlock>
 __device__ __forceinline__ void block_partials(double (&v)[K], double* out)
 {

@@ -185,7 +185,8 @@ hipError_t launch_phi_f64(const KParams& p, const void* state, double* phi, void
 // [rho, phi, j + F/2] of src there (force_sums_blocks(p, tc.seg_req) blocks
 // of 5).  variant 1: after the phi pass, which left phi (all sites, FP64) of
 // src in `phi` and dst's phi_c, one site per thread, Pi formed at each face
-// neighbour (partials: one block per kBlock sites).  Bit-identical levels.
+// neighbour (partials: collide_grid(p, true) blocks of site_block(p) threads).
+// kStepBox: boxes, FP32 storage only.  Bit-identical levels.
 hipError_t launch_force_collide(const KParams& p, const TileCfg& tc, bool fp32, int variant,
                                 int compact, const void* src, void* dst, double* phi, double* partials,
                                 hipStream_t s);

@@ -339,7 +339,8 @@ TileCfg row_tile_config(const KParams& p, int segment_x, bool fp32)
 // (flat tiles re-read more through L2), 100 x 120 x 240 340 / 346, but 96^3
 // 119 / 111, 151 x 105 x 150 409 / 354: flat where row tiles leave more than a
 // tenth of their lanes idle along z.  Up to 120000 sites, whose segments are
-// short, row tiles.  Flat tiles take no more workgroups than the array of the
+// short, row tiles (shards of 8 x 100 x 100 in FP64 16.5 / 17.4, 10 x 75 x 100 15.5
+// / 16.7).  Flat tiles take no more workgroups than the array of the
 // allocation-free sums holds partials for, unless row tiles do too: what row
 // tiles can sum there, flat tiles can (there are never more flat tiles in a
 // plane than row tiles).
@@ -370,7 +371,8 @@ TileCfg tile_config(const KParams& p, int segment_x, bool fp32)
 //     12.5 / 6.1, 64^3 33 / 26, 96^3 111 / 104, 72 x 111 x 150 183 / 159,
 //     128^3 248 / 255, 192^3 832 / 861
 //   stress, FP64, other tau_g (608 / 784 B): 16^3 12.8 / 6.1, 64^3 33.8 / 31.9,
-//     90 x 75 x 100 101 / 100, 96^3 112 / 126
+//     68^3 37.6 / 40.0, 72^3 42 / 46, 80^3 73 / 70, 88^3 98 / 100, 90 x 75 x 100
+//     101 / 100, 96^3 112 / 126
 //   force, FP32: 16^3 19 / 7.7, 64^3 25 / 21, 96^3 78 / 69, 72 x 111 x 150
 //     110 / 111, 128^3 161 / 171, 151 x 105 x 150 219 / 226
 //   force, FP64, tau_g = 1: 64^3 43 / 27, 128^3 290 / 275, 192^3 942 / 913,
@@ -482,8 +484,10 @@ bool compact_march(const KParams& p, bool fp32)
 // moments: FP64 stress 64^3 22.2 / 22.1, 7 x 200 x 300 33.1 / 33.4, 90 x 75 x
 // 100 49 / 42, 128^3 162 / 126, 256^3 1311 / 982; FP64 force 90 x 75 x 100
 // (1.4 cells per site) 54 / 62, 96^3 91 / 61, 128^3 188 / 174, 256^3 1472 /
-// 1345; FP32 force 72 x 111 x 150 64 / 73, 128^3 126 / 106 (with sums 122 /
-// 128), 192^3 417 / 417, 256^3 919 / 926.
+// 1345; FP32 force 72 x 111 x 150 64 / 73, 112^3 94 / 90, 116^3 112 / 91, 120^3
+// 122 / 92, 128^3 126 / 106 (with sums 122 / 128), 151 x 105 x 150 166 / 140, 160^3
+// 247 / 242, 168^3 321 / 289, 192^3 417 / 417 (in a later run 416 / 401), 256^3
+// 919 / 926.
 bool compact_f(const KParams& p, bool fp32, bool sums)
 {
     if (p.omega_f != 1.0 || !compact_march(p, fp32)) return false;

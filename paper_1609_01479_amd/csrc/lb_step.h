@@ -186,7 +186,8 @@ __device__ __forceinline__ T ldc(const T* __restrict__ base, OffT<SMALL> pl, int
 // would go to memory in parts, where plain stores let L2 join them (us per
 // step, NT / plain: FP32 151 x 105 x 150, rows of 600 bytes, 228 / 189,
 // 90 x 75 x 100 64 / 47, 96^3 64 / 60, 128^3 131 / 136, 256^3 944 / 983; FP64
-// 32 x 128 x 128 68 / 71).
+// 32 x 128 x 128 68 / 71).  The march also stores so on lattices of at most
+// 120000 sites, whatever their rows (march_nt).
 template <bool SMALL, bool NT, typename T>
 __device__ __forceinline__ void stc(T* __restrict__ base, OffT<SMALL> pl, int i, unsigned compb,
                                     unsigned row, T v)
